@@ -561,10 +561,10 @@ int lodgs_server_stats_read(const lodgs_server* server, lodgs_server_stats* out)
  * counts per stage since the last read, and clears the record. */
 #define LODGS_STAGE_SELECT 0      /* upper cut, SPT binary search, compaction */
 #define LODGS_STAGE_PROJECT 1     /* gather + EWA + SH                          */
-#define LODGS_STAGE_DEPTH_SORT 2  /* radix sort of splats by depth              */
-#define LODGS_STAGE_DUPLICATE 3   /* tile-count scan + instance emission        */
-#define LODGS_STAGE_TILE_SORT 4   /* radix sort of instances by tile            */
-#define LODGS_STAGE_RANGES 5      /* per-tile ranges                            */
+#define LODGS_STAGE_DEPTH_SORT 2  /* sort of each tile's instances by depth     */
+#define LODGS_STAGE_DUPLICATE 3   /* drawn-splat scan + instance emission       */
+#define LODGS_STAGE_TILE_SORT 4   /* instances into their tile's range          */
+#define LODGS_STAGE_RANGES 5      /* per-tile ranges and the tile order         */
 #define LODGS_STAGE_BLEND 6       /* forward blend                              */
 #define LODGS_STAGE_BLEND_BWD 7   /* backward blend (2D gradients)              */
 #define LODGS_STAGE_PROJECT_BWD 8 /* projection / SH backward + scatter         */

@@ -80,25 +80,38 @@ void stage_end(lodgs_frame* f, hipStream_t st) {
 
 namespace {
 __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                           int64_t cap) {
+                           int64_t cap, ViewClear clear) {
+  int64_t n = 0;
+  if (mode == kViewRender) {
+    n = *d_count;
+    n = n < 0 ? 0 : (n > cap ? cap : n);
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t words = 2 * ((n + kDrawnTile - 1) / kDrawnTile), ntiles = (int64_t)v.tiles_x * v.tiles_y;
+    for (int64_t i = t0; i < words; i += stride) clear.scan_words[i] = 0ull;
+    for (int64_t i = t0; i < ntiles; i += stride) clear.tile_count[i] = 0u;
+    if (t0 != 0) return;
+  }
   *dst = v;
   if (mode == kViewSelect) {
     ctr->n_spt_visible = 0;
     ctr->n_upper_selected = 0;
     ctr->sum_high = 0;
   } else if (mode == kViewRender) {
-    int64_t n = *d_count;
-    n = n < 0 ? 0 : (n > cap ? cap : n);
     ctr->n_render = (int32_t)n;
     ctr->n_drawn = 0;
+    ctr->n_instances = 0;
     ctr->n_long = 0;
+    ctr->n_big = 0;
+    ctr->drawn_ticket = 0;
   }
 }
 }  // namespace
 
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_view, dim3(1), dim3(1), 0, st, v, dst, ctr, mode, d_count, cap);
+                     int64_t cap, const ViewClear& clear, hipStream_t st) {
+  // a render's clearing: a few thousand words, spread over 32 workgroups
+  const int grid = mode == kViewRender ? 32 : 1, block = mode == kViewRender ? kBlock : 1;
+  hipLaunchKernelGGL(k_set_view, dim3(grid), dim3(block), 0, st, v, dst, ctr, mode, d_count, cap, clear);
 }
 
 void launch_blend_count(lodgs_frame* f, hipStream_t st);
@@ -192,10 +205,14 @@ size_t frame_bytes(const lodgs_scene* scene, const lodgs_frame_caps& caps) {
 
 namespace {
 
-// Selection position of each instance in tile order.
-__global__ void k_instance_positions(const uint2* info_k, int64_t m, int32_t* pos) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (int64_t)gridDim.x * blockDim.x)
+// Tile id and selection position of each instance in tile order, one
+// workgroup per tile.
+__global__ void k_instance_list(const uint2* ranges, const uint2* info_k, int64_t m, int32_t* tile, int32_t* pos) {
+  const uint2 rg = ranges[blockIdx.x];
+  for (int64_t k = (int64_t)rg.x + threadIdx.x; k < rg.y && k < m; k += blockDim.x) {
+    tile[k] = (int32_t)blockIdx.x;
     pos[k] = (int32_t)info_k[k].x;
+  }
 }
 
 }  // namespace
@@ -285,6 +302,8 @@ int lodgs_frame_create(const lodgs_scene* scene, const lodgs_frame_caps* caps, l
       caps->max_instances > (int64_t)INT32_MAX - 1 || caps->max_width <= 0 || caps->max_height <= 0 ||
       caps->max_width > 16384 || caps->max_height > 16384)
     return set_error(LODGS_E_INVALID, "lodgs_frame_create: capacities out of range");
+  const int rc = lodgs::render_kernel_limits();
+  if (rc != LODGS_OK) return rc;
   lodgs_frame* f = new (std::nothrow) lodgs_frame();
   if (!f) return set_error(LODGS_E_OOM, "lodgs_frame_create: out of host memory");
   f->scene = scene;
@@ -485,13 +504,9 @@ int lodgs_frame_read_instances(lodgs_frame* f, int32_t* d_tile, int32_t* d_pos, 
   *n_out = c.n_instances;
   int64_t m = c.n_inst_clamped < capacity ? c.n_inst_clamped : capacity;
   if (m > 0) {
-    e = hipMemcpyAsync(d_tile, f->sorted_ikey, sizeof(int32_t) * m, hipMemcpyDeviceToDevice, st);
-    if (e == hipSuccess) {
-      const int64_t g = (m + lodgs::kBlock - 1) / lodgs::kBlock;
-      hipLaunchKernelGGL(k_instance_positions, dim3((unsigned)(g < 4096 ? g : 4096)), dim3(lodgs::kBlock), 0, st,
-                         f->sorted_info, m, d_pos);
-      e = hipGetLastError();
-    }
+    hipLaunchKernelGGL(k_instance_list, dim3((unsigned)(f->view.tiles_x * f->view.tiles_y)), dim3(lodgs::kBlock), 0, st,
+                       f->ranges, f->info_k, m, d_tile, d_pos);
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_fail(e, "lodgs_frame_read_instances");
   }
@@ -580,6 +595,7 @@ struct lodgs_graph {
   const int32_t* count_sel;
   const int32_t* count_ren;
   int64_t cap_sel, cap_ren;
+  lodgs::ViewClear clear_sel, clear_ren;
   int32_t width, height;
   // the forward blend node: its output image argument is replaced when a
   // replay writes to another image
@@ -615,8 +631,8 @@ int graph_launch(lodgs_graph* g, const lodgs_camera* cam, float tau, float* d_rg
   if (!std::isfinite(tau) || tau < 0.0f) return set_error(LODGS_E_INVALID, "lodgs_graph_launch: bad tau");
   ViewConst vs = make_view(*cam, tau), vr = make_view(*cam, 0.0f);
   vs.spt_scale = g->frame->spt_scale;  // the frame's LoD noise at this launch
-  void* args_s[6] = {&vs, &g->dst_sel, &g->ctr_sel, &g->mode_sel, &g->count_sel, &g->cap_sel};
-  void* args_r[6] = {&vr, &g->dst_ren, &g->ctr_ren, &g->mode_ren, &g->count_ren, &g->cap_ren};
+  void* args_s[7] = {&vs, &g->dst_sel, &g->ctr_sel, &g->mode_sel, &g->count_sel, &g->cap_sel, &g->clear_sel};
+  void* args_r[7] = {&vr, &g->dst_ren, &g->ctr_ren, &g->mode_ren, &g->count_ren, &g->cap_ren, &g->clear_ren};
   hipKernelNodeParams ps = g->p_sel, pr = g->p_ren;
   ps.kernelParams = args_s;
   pr.kernelParams = args_r;
@@ -676,6 +692,7 @@ static int capture(lodgs_graph* g, hipStream_t st, const char* who, Launch launc
     const int mode = *reinterpret_cast<int*>(p.kernelParams[3]);
     const int32_t* cnt = *reinterpret_cast<const int32_t**>(p.kernelParams[4]);
     const int64_t cap = *reinterpret_cast<int64_t*>(p.kernelParams[5]);
+    const ViewClear clear = *reinterpret_cast<ViewClear*>(p.kernelParams[6]);
     if (dst == f->d_view_sel) {
       g->node_sel = nodes[k];
       g->p_sel = p;
@@ -684,6 +701,7 @@ static int capture(lodgs_graph* g, hipStream_t st, const char* who, Launch launc
       g->mode_sel = mode;
       g->count_sel = cnt;
       g->cap_sel = cap;
+      g->clear_sel = clear;
     } else if (dst == f->d_view_ren) {
       g->node_ren = nodes[k];
       g->p_ren = p;
@@ -692,6 +710,7 @@ static int capture(lodgs_graph* g, hipStream_t st, const char* who, Launch launc
       g->mode_ren = mode;
       g->count_ren = cnt;
       g->cap_ren = cap;
+      g->clear_ren = clear;
     }
   }
   if (e != hipSuccess) return hip_fail(e, who);

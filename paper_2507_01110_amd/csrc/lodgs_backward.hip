@@ -111,7 +111,9 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
   // banks (the rows are 128 words apart)
   __shared__ float acc[NW][NP][NB];
   __shared__ uint32_t wave_active[NW];  // per wave: some pixel still blends
-  const int tile = (int)tile_order[blockIdx.x];
+  const uint32_t place = tile_order[blockIdx.x];
+  if (place == kNoTile) return;  // block-uniform
+  const int tile = (int)place;
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, row = lane >> 4;
   int px = 0;
@@ -493,12 +495,12 @@ __device__ __forceinline__ void splat_mean64(const Splat* splats, int64_t i, dou
 
 // Splats with more than kLongSegment instances: one workgroup per splat turns
 // its instance partials into the splat's 2D sums (add_instance) in grad2d at
-// its selection position (and its contributing pixels in contrib).  Per-thread FP64 sums over independent unrolled loads, a
+// its rank among the drawn splats (and its contributing pixels in contrib).  Per-thread FP64 sums over independent unrolled loads, a
 // butterfly over the wave, the waves in order: a fixed order, so
 // deterministic.
 template <int NP>
 __global__ void __launch_bounds__(kBlock) k_long_sums(const FrameCounters* ctr, const uint32_t* long_list,
-                                                      const uint32_t* order,
+                                                      const uint32_t* list,
                                                       const uint32_t* inst_off, const float* __restrict__ partial,
                                                       const Splat* __restrict__ splats, const ushort4* rect,
                                                       double* grad2d, int32_t* contrib) {
@@ -508,7 +510,7 @@ __global__ void __launch_bounds__(kBlock) k_long_sums(const FrameCounters* ctr, 
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   for (int64_t li = blockIdx.x; li < nl; li += gridDim.x) {  // block-uniform
     const int64_t r = long_list[li];
-    const int64_t i = order[r];
+    const int64_t i = list[r];
     const int64_t a0 = inst_off[r];
     int64_t a = a0, b = r + 1 < n ? (int64_t)inst_off[r + 1] : n_inst;
     a = a < n_cl ? a : n_cl;
@@ -544,7 +546,7 @@ __global__ void __launch_bounds__(kBlock) k_long_sums(const FrameCounters* ctr, 
       double sum = part[0][threadIdx.x];
 #pragma unroll
       for (int w = 1; w < kBlock / 64; ++w) sum += part[w][threadIdx.x];
-      if (threadIdx.x < 9) grad2d[9 * i + threadIdx.x] = sum;
+      if (threadIdx.x < 9) grad2d[9 * r + threadIdx.x] = sum;
       else if (NP == 11) contrib[i] = (int32_t)sum;  // a count, exact in FP64
     }
     __syncthreads();
@@ -553,36 +555,25 @@ __global__ void __launch_bounds__(kBlock) k_long_sums(const FrameCounters* ctr, 
 
 // Every drawn splat that the duplication kernel did not put on the long list
 // (those with more than kLongSegment tiles whose first instance was emitted):
-// one thread per splat, in depth order, so neighbouring threads read
+// one thread per splat, in selection order, so neighbouring threads read
 // neighbouring partials; FP64 sums in instance order (add_instance) into
-// grad2d at the splat's selection position (zero for a splat that an
+// grad2d at the splat's rank among the drawn ones (zero for a splat that an
 // instance overflow left without instances), and its number of contributing
 // pixels into contrib.
 template <int NP>
-__global__ void __launch_bounds__(kBlock) k_splat_sums(const FrameCounters* ctr, const uint32_t* order,
+__global__ void __launch_bounds__(kBlock) k_splat_sums(const FrameCounters* ctr, const uint32_t* list,
                                                        const uint32_t* inst_off,
                                                        const float* __restrict__ partial,
                                                        const Splat* __restrict__ splats, const ushort4* rect,
-                                                       const uint4* rank_info, double* grad2d, int32_t* contrib) {
+                                                       double* grad2d, int32_t* contrib) {
   const int64_t n = ctr->n_drawn;
   const int64_t n_inst = (uint32_t)ctr->n_instances, n_cl = ctr->n_inst_clamped;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
     const int64_t a0 = inst_off[r];
-    int64_t i;
-    ushort4 q;
+    const int64_t i = list[r];
+    const ushort4 q = rect[i];
     double mx, my;
-    if (a0 < n_cl) {  // the duplication kernel wrote the rank's record with the first instance
-      const uint4 w0 = rank_info[2 * r], w1 = rank_info[2 * r + 1];
-      i = w0.x;
-      q = make_ushort4((unsigned short)(w0.z & 0xFFFFu), (unsigned short)(w0.z >> 16),
-                       (unsigned short)(w0.w & 0xFFFFu), (unsigned short)(w0.w >> 16));
-      mx = (double)__uint_as_float(w1.x) + (double)__uint_as_float(w1.y);
-      my = (double)__uint_as_float(w1.z) + (double)__uint_as_float(w1.w);
-    } else {  // left without instances by an overflow: zero sums
-      i = order[r];
-      q = rect[i];
-      mx = my = 0.0;
-    }
+    splat_mean64(splats, i, mx, my);
     if ((uint32_t)(q.y - q.x) * (uint32_t)(q.w - q.z) > kLongSegment && a0 < n_cl) continue;  // k_long_sums
     int64_t b = r + 1 < n ? (int64_t)inst_off[r + 1] : n_inst;
     const int64_t a = a0 < n_cl ? a0 : n_cl;
@@ -594,7 +585,7 @@ __global__ void __launch_bounds__(kBlock) k_splat_sums(const FrameCounters* ctr,
       for (int c = 0; c < NP; ++c) t[c] = partial[NP * k + c];
       add_instance<NP>(g, t, (uint32_t)(k - a0), q, mx, my);
     }
-    double* dst = grad2d + 9 * i;
+    double* dst = grad2d + 9 * r;
 #pragma unroll
     for (int c = 0; c < 9; ++c) dst[c] = g[c];
     if (NP == 11) contrib[i] = (int32_t)g[9];
@@ -626,7 +617,7 @@ __global__ void __launch_bounds__(kBlock) k_color_bwd(const int32_t* idx, const 
     const int64_t i = drawn_list[dr];
     float gc[3], acc3[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int c = 0; c < 3; ++c) gc[c] = (float)grad2d[9 * i + 6 + c];
+    for (int c = 0; c < 3; ++c) gc[c] = (float)grad2d[9 * dr + 6 + c];
     const float4* rec = reinterpret_cast<const float4*>(dcol + kColorRec * i);
     const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
     const float J[9] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w, r2.x};
@@ -678,9 +669,9 @@ __global__ void __launch_bounds__(kBlock) k_color_bwd(const int32_t* idx, const 
       for (int a = 0; a < 3; ++a)
         dd[a] = __builtin_fmaf(dRGB[2], J[6 + a], __builtin_fmaf(dRGB[1], J[3 + a], dRGB[0] * J[a]));
       const float dot = __builtin_fmaf(dd[0], d0, __builtin_fmaf(dd[1], d1, dd[2] * d2));
-      grad2d[9 * i + 6] = (double)((dd[0] - d0 * dot) * il);
-      grad2d[9 * i + 7] = (double)((dd[1] - d1 * dot) * il);
-      grad2d[9 * i + 8] = (double)((dd[2] - d2 * dot) * il);
+      grad2d[9 * dr + 6] = (double)((dd[0] - d0 * dot) * il);
+      grad2d[9 * dr + 7] = (double)((dd[1] - d1 * dot) * il);
+      grad2d[9 * dr + 8] = (double)((dd[2] - d2 * dot) * il);
     }
   }
 }
@@ -709,9 +700,9 @@ __global__ void __launch_bounds__(kBlock) k_project_bwd(SceneDev S, const ViewCo
         if (cs.count) cs.count[node] += c;
       }
     }
-    double g2[9];  // 2D sums of the splat (selection position i), see add_instance
+    double g2[9];  // 2D sums of the splat, see add_instance
 #pragma unroll
-    for (int c = 0; c < 9; ++c) g2[c] = grad2d[9 * i + c];
+    for (int c = 0; c < 9; ++c) g2[c] = grad2d[9 * r + c];
     const double gdir[3] = {g2[6], g2[7], g2[8]};
     double gm[3] = {0, 0, 0}, gls[3] = {0, 0, 0}, gq[4] = {0, 0, 0, 0}, go = 0.0;
     Proj64 P;
@@ -805,10 +796,10 @@ __global__ void __launch_bounds__(kBlock) k_project_bwd(SceneDev S, const ViewCo
 // The per-splat 2D sums of the instance partials (frame-local outputs).
 template <int NP>
 static void launch_splat_sums(lodgs_frame* f, hipStream_t st) {
-  hipLaunchKernelGGL(k_long_sums<NP>, dim3(1024), dim3(kBlock), 0, st, f->ctr, f->long_list, f->sorted_order,
+  hipLaunchKernelGGL(k_long_sums<NP>, dim3(1024), dim3(kBlock), 0, st, f->ctr, f->long_list, f->drawn_list,
                      f->inst_off, f->inst_grad, f->splats, f->rect, f->grad2d, f->contrib);
-  hipLaunchKernelGGL(k_splat_sums<NP>, dim3(2048), dim3(kBlock), 0, st, f->ctr, f->sorted_order, f->inst_off,
-                     f->inst_grad, f->splats, f->rect, f->rank_info, f->grad2d, f->contrib);
+  hipLaunchKernelGGL(k_splat_sums<NP>, dim3(2048), dim3(kBlock), 0, st, f->ctr, f->drawn_list, f->inst_off,
+                     f->inst_grad, f->splats, f->rect, f->grad2d, f->contrib);
 }
 
 // Colour and projection backward into the gradient arrays (and the node
@@ -829,21 +820,21 @@ static void launch_scatter_deg(const SceneDev& S, lodgs_frame* f, const lodgs_gr
 template <int NP>
 static void launch_blend_bwd_np(lodgs_frame* f, const float* d_dL, hipStream_t st) {
   const ViewConst& v = f->view;
-  const int ntiles = v.tiles_x * v.tiles_y;
+  const int ntiles = tile_places(v.tiles_x * v.tiles_y);
   switch (f->blend_px_bwd) {
     case 1:
       hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_ival, f->sorted_info, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
+                         f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->inst_grad);
       break;
     case 4:
       hipLaunchKernelGGL((k_blend_bwd<4, NP>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_ival, f->sorted_info, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
+                         f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->inst_grad);
       break;
     default:
       hipLaunchKernelGGL((k_blend_bwd<2, NP>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_ival, f->sorted_info, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
+                         f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->inst_grad);
       break;
   }

@@ -190,26 +190,31 @@ __device__ __forceinline__ void sh_basis_grad(int deg, float x, float y, float z
 
 // Smallest value of -power = a1 u1^2 + a2 u2^2 (a = -h > 0, u the splat's
 // eigenbasis coordinates of the offset from its mean) over the pixel-centre
-// rectangle [x0, x1] x [y0, y1]: zero when the mean lies inside, otherwise
-// the smallest of the four edge minima (a convex quadratic on a segment).
-__device__ __forceinline__ float splat_rect_min(const Splat& s, float x0, float x1, float y0, float y1) {
+// rectangle [x0, x0 + len] x [y0, y0 + len].  The quadratic is convex with its
+// minimum at the mean, so over the rectangle it is least on a side that faces
+// the mean: on the vertical line nearest to it or on the horizontal one (zero
+// when the mean lies inside, where both lines pass through it).  rx and ry are
+// the reciprocals of the quadratic's second derivatives (halved) along x and
+// y; their rounding moves a point on a line, where the quadratic is flat.
+__device__ __forceinline__ float splat_rect_min(const Splat& s, float mx, float my, float rx, float ry, float x0,
+                                                float y0, float len) {
   const float a1 = -s.h1, a2 = -s.h2;
-  const float mx = s.mxh + s.mxl, my = s.myh + s.myl;
-  if (mx >= x0 && mx <= x1 && my >= y0 && my <= y1) return 0.0f;
-  float best = 3.0e38f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    // edges: bottom/top (along x) and left/right (along y)
-    const bool along_x = k < 2;
-    const float px = (k == 3) ? x1 : x0, py = (k == 1) ? y1 : y0;
-    const float len = along_x ? x1 - x0 : y1 - y0;
-    const float dx = (px - s.mxh) - s.mxl, dy = (py - s.myh) - s.myl;
-    const float c1 = __builtin_fmaf(s.se, dy, s.ce * dx), c2 = __builtin_fmaf(-s.se, dx, s.ce * dy);
-    const float e1 = along_x ? s.ce : s.se, e2 = along_x ? -s.se : s.ce;
-    const float den = __builtin_fmaf(a1 * e1, e1, a2 * e2 * e2);
-    float t = den > 0.0f ? -__builtin_fmaf(a1 * c1, e1, a2 * c2 * e2) / den : 0.0f;
+  const float ex = fminf(fmaxf(mx, x0), x0 + len), ey = fminf(fmaxf(my, y0), y0 + len);
+  const float dx = (ex - s.mxh) - s.mxl, dy = (ey - s.myh) - s.myl;    // the nearest lines
+  const float bx = (x0 - s.mxh) - s.mxl, by = (y0 - s.myh) - s.myl;    // the lines' start
+  float best;
+  {  // vertical line: (dx, by + t)
+    const float c1 = __builtin_fmaf(s.se, by, s.ce * dx), c2 = __builtin_fmaf(-s.se, dx, s.ce * by);
+    float t = -__builtin_fmaf(a1 * c1, s.se, a2 * c2 * s.ce) * ry;
     t = fminf(fmaxf(t, 0.0f), len);
-    const float u1 = __builtin_fmaf(t, e1, c1), u2 = __builtin_fmaf(t, e2, c2);
+    const float u1 = __builtin_fmaf(t, s.se, c1), u2 = __builtin_fmaf(t, s.ce, c2);
+    best = __builtin_fmaf(a1 * u1, u1, a2 * u2 * u2);
+  }
+  {  // horizontal line: (bx + t, dy)
+    const float c1 = __builtin_fmaf(s.se, dy, s.ce * bx), c2 = __builtin_fmaf(-s.se, bx, s.ce * dy);
+    float t = -__builtin_fmaf(a1 * c1, s.ce, a2 * c2 * -s.se) * rx;
+    t = fminf(fmaxf(t, 0.0f), len);
+    const float u1 = __builtin_fmaf(t, s.ce, c1), u2 = __builtin_fmaf(-t, s.se, c2);
     best = fminf(best, __builtin_fmaf(a1 * u1, u1, a2 * u2 * u2));
   }
   return best;
@@ -260,30 +265,28 @@ __device__ __forceinline__ MaskSetup block_mask_setup(const Splat& s) {
 __device__ __forceinline__ uint32_t splat_block_mask(const Splat& s, const MaskSetup& ms, int tx, int ty) {
   if (!ms.ok) return 0u;
   uint32_t quarters = 0u;
+  const float ax = -__builtin_fmaf(s.h1 * s.ce, s.ce, s.h2 * s.se * s.se);
+  const float ay = -__builtin_fmaf(s.h1 * s.se, s.se, s.h2 * s.ce * s.ce);
+  const float rx = ax > 0.0f ? __builtin_amdgcn_rcpf(ax) : 0.0f, ry = ay > 0.0f ? __builtin_amdgcn_rcpf(ay) : 0.0f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const float x0 = (float)(tx * kTile + 8 * (q & 1)) + 0.5f, y0 = (float)(ty * kTile + 8 * (q >> 1)) + 0.5f;
-    if (splat_rect_min(s, x0, x0 + 7.0f, y0, y0 + 7.0f) <= ms.K) quarters |= 1u << q;
+    if (splat_rect_min(s, ms.mx, ms.my, rx, ry, x0, y0, 7.0f) <= ms.K) quarters |= 1u << q;
   }
   if (quarters == 0u) return 0u;
+  // the blocks of the columns and rows that the box meets, as block bits
   uint32_t cols = 0u, rows = 0u;
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
+    const uint32_t column = block_bit(k, 0) | block_bit(k, 1) | block_bit(k, 2) | block_bit(k, 3);
+    const uint32_t row = block_bit(0, k) | block_bit(1, k) | block_bit(2, k) | block_bit(3, k);
     const float x0 = (float)(tx * kTile + 4 * k) + 0.5f, y0 = (float)(ty * kTile + 4 * k) + 0.5f;
-    if (x0 <= ms.mx + ms.hx && x0 + 3.0f >= ms.mx - ms.hx) cols |= 1u << k;
-    if (y0 <= ms.my + ms.hy && y0 + 3.0f >= ms.my - ms.hy) rows |= 1u << k;
+    if (x0 <= ms.mx + ms.hx && x0 + 3.0f >= ms.mx - ms.hx) cols |= column;
+    if (y0 <= ms.my + ms.hy && y0 + 3.0f >= ms.my - ms.hy) rows |= row;
   }
-  uint32_t m = 0u;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (!((quarters >> q) & 1u)) continue;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int bx = 2 * (q & 1) + (b & 1), by = 2 * (q >> 1) + (b >> 1);
-      if (((cols >> bx) & 1u) && ((rows >> by) & 1u)) m |= 1u << (4 * q + b);
-    }
-  }
-  return m;
+  // quarter q's four bits are nibble q
+  const uint32_t q4 = (quarters & 1u) | (quarters & 2u) << 3 | (quarters & 4u) << 6 | (quarters & 8u) << 9;
+  return cols & rows & (15u * q4);
 }
 
 // Pixel layout of the blend kernels: a 16x16 tile is one workgroup of 4/PX

@@ -112,7 +112,9 @@ struct FrameCounters {
   int32_t n_chunks;      // SPT candidate chunks of the last select
   int32_t seg_total;     // compaction segments of the last select
   int32_t n_long;        // drawn splats with more than kLongSegment instances
-  int32_t pad;
+  int32_t n_big;         // chunks of tiles too large for one workgroup's sort
+  int32_t drawn_ticket;  // next tile of the drawn-splat scan
+  int32_t pad[3];
 };
 
 struct lodgs_frame {
@@ -139,31 +141,30 @@ struct lodgs_frame {
   // render
   lodgs::Splat* splats;   // [max_selected]
   uint32_t* depth_key;    // [max_selected]
-  uint32_t* depth_key2;
-  uint32_t* order;        // [max_selected]
-  uint32_t* order2;
   uint32_t* tiles;        // [max_selected]
-  uint32_t* inst_off;     // [max_selected] instance offsets of the drawn splats in depth order
+  unsigned long long* scan_words;  // [2 * drawn_scan_tiles(max_selected)] look-back words of the drawn-splat scan
+  uint32_t* inst_off;     // [max_selected] first instance of each drawn splat (selection order)
+  uint32_t* chunk_first;  // [max_instances / 64 + 1] rank of the splat holding each 64-instance chunk's first
   uint32_t* drawn_list;   // [max_selected] selection positions of the drawn splats (selection order)
   ushort4* rect;          // [max_selected]
-  uint32_t* ikey;         // [max_instances]
-  uint32_t* ival;
-  uint32_t* ikey2;
-  uint32_t* ival2;
-  uint2* inst_info;       // [max_instances] (selection position of the splat, block mask) (emission order),
-                          // then a ping-pong buffer of the tile sort's payload
+  uint2* inst_key;        // [max_instances] (tile, depth bits) in emission order
+  uint2* inst_info;       // [max_instances] (selection position of the splat, block mask), emission order
+  unsigned long long* bucket_key;  // [max_instances] (depth bits << 32 | emission index) by tile
+  uint32_t* ival;         // [max_instances] emission index of each instance, in (tile, depth) order
+  uint2* info_k;          // [max_instances] the instances' words in that order
   float* inst_grad;       // [max_instances][kPartial] per-instance partials (emission order)
   uint32_t* inst_event;   // [max_instances] forward events, byte q for quarter q's 4x4 blocks (tile order)
-  uint2* info_k;          // [max_instances] the other ping-pong buffer of that payload
-  uint4* rank_info;       // [max_selected][2] per depth rank: (splat, 0, rect x0|x1<<16, y0|y1<<16),
-                          // (mean x hi, lo, y hi, lo); written with the splat's first instance
-  double* grad2d;         // [max_selected][9] per-drawn-splat 2D sums (selection position)
+  double* grad2d;         // [max_selected][9] per-drawn-splat 2D sums (by rank among the drawn ones)
   float* dcol;            // [max_selected][kColorRec] colour backward record of each drawn splat (selection
                           // position): d colour / d view direction (9), unit view direction (3), 1 / distance,
                           // clamp bits, 2 unused
-  uint32_t* long_list;    // [max_selected] depth ranks of the splats with many instances
+  uint32_t* long_list;    // [max_selected] ranks (among the drawn ones) of the splats with many instances
   uint2* ranges;          // [max tiles]
-  uint32_t* tile_order;   // [max tiles] tiles, heaviest first
+  uint32_t* tile_order;   // [tile_places(max tiles)] tiles, heaviest of each chunk first, chunks interleaved
+  uint32_t* tile_count;   // [max tiles] instances of each tile
+  uint32_t* tile_cursor;  // [max tiles] next place in each tile's range
+  uint32_t* tile_mid;     // [chunks of the tile order] tiles of more than 64 instances
+  uint2* big_list;        // [max_instances / kSortChunkHalf + 1] (tile, chunk) of the tiles sorted in chunks
   float spt_scale;        // LoD noise factor on the distances to SPT roots (lodgs_frame_set_lod_noise)
   lodgs::ViewConst* d_view_sel;  // view constants of the last lod_select (device)
   lodgs::ViewConst* d_view_ren;  // view constants of the last render (device)
@@ -176,10 +177,6 @@ struct lodgs_frame {
   const float* r_rgb;
   float bg[3];
   lodgs::ViewConst view;
-  const uint32_t* sorted_ival;  // the buffer holding the final instance order
-  const uint32_t* sorted_ikey;
-  const uint2* sorted_info;     // the (splat, block mask) words in tile order (inst_info or info_k)
-  const uint32_t* sorted_order;  // selection positions of the drawn splats in depth order
   // timing mode: one (stage, start, end) event pair per stage and call
   bool timing;
   struct TimedStage {
@@ -237,14 +234,48 @@ constexpr int kPartial = 11;
 // Floats of the colour backward's per-splat record (written by the forward).
 constexpr int kColorRec = 16;
 
+// The tile order's chunks (k_tile_scan): as many as keep a chunk to
+// kOrderChunk tiles, of equal size but for the last; the order has a place for
+// every tile of whole chunks (kNoTile where the last is shorter).
+constexpr int32_t kOrderChunk = 2048;
+constexpr uint32_t kNoTile = 0xFFFFFFFFu;
+__host__ __device__ inline int32_t tile_chunks(int32_t ntiles) { return (ntiles + kOrderChunk - 1) / kOrderChunk; }
+__host__ __device__ inline int32_t tile_chunk(int32_t ntiles) {
+  const int32_t c = tile_chunks(ntiles);
+  return (ntiles + c - 1) / c;
+}
+// Place of the l-th tile of chunk b of c: the chunks take turns, starting with
+// another one each time, so that a chunk of heavy tiles does not always fall
+// to the same XCDs (workgroups go to the XCDs in turn: with a fixed order the
+// heavy chunk of a 4K view kept half of them busy, 513 against 313 us).
+__host__ __device__ inline uint32_t order_place(uint32_t l, uint32_t b, uint32_t c) { return c * l + (b + l) % c; }
+inline int32_t tile_places(int32_t ntiles) { return tile_chunks(ntiles) * tile_chunk(ntiles); }
+
+// Half the instances of a sort chunk: a tile sorted in chunks holds more than
+// one chunk, so it lists at most one chunk per this many instances.
+constexpr int kSortChunkHalf = 1024;
+
+// Selection positions per tile of the drawn-splat scan.
+constexpr int kDrawnTile = 2048;
+inline size_t drawn_scan_tiles(int64_t n) { return (size_t)((n + kDrawnTile - 1) / kDrawnTile); }
+
+// What the render's first kernel clears besides the counters: the tiles'
+// instance counts and the look-back words of the drawn-splat scan (those that
+// n_render positions use).
+struct ViewClear {
+  uint32_t* tile_count;
+  unsigned long long* scan_words;
+};
+
 // Writes the per-view constants to the frame's device slot (one thread): the
 // kernels of a stage read them from there, so a captured graph is replayed
 // for another camera by updating this one node's argument.  The same thread
 // starts the stage's counters: kViewSelect clears the select counters,
-// kViewRender sets n_render = clamp(*d_count, 0, cap) and clears n_drawn.
+// kViewRender sets n_render = clamp(*d_count, 0, cap) and clears the render's
+// counters; the other threads clear the arrays of `clear` (kViewRender).
 constexpr int kViewOnly = 0, kViewSelect = 1, kViewRender = 2;
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, hipStream_t st);
+                     int64_t cap, const ViewClear& clear, hipStream_t st);
 
 int hip_fail(hipError_t e, const char* what);
 
@@ -287,6 +318,8 @@ int graph_launch(lodgs_graph* g, const lodgs_camera* cam, float tau, float* d_rg
 // *n_args, or -1 when func is not one: a captured view is pointed at another
 // image by updating that one argument.
 int blend_output_arg(const void* func, int* n_args);
+// Once per frame creation: launch limits of the render's kernels.
+int render_kernel_limits();
 void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count, const ViewConst& v,
                    const float bg[3], float* d_rgb, hipStream_t st);
 void launch_backward(lodgs_frame* f, const float* d_dL, const lodgs_grads* sel, const lodgs_grads* nodes,
@@ -316,28 +349,29 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->chunk_owner, (size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
   fn(f->splats, ns);
   fn(f->depth_key, ns);
-  fn(f->depth_key2, ns);
-  fn(f->order, ns);
-  fn(f->order2, ns);
   fn(f->tiles, ns);
+  fn(f->scan_words, 2 * drawn_scan_tiles((int64_t)ns));
   fn(f->inst_off, ns);
+  fn(f->chunk_first, ni / 64 + 1);
   fn(f->drawn_list, ns);
   fn(f->rect, ns);
-  fn(f->ikey, ni);
-  fn(f->ival, ni);
-  fn(f->ikey2, ni);
-  fn(f->ival2, ni);
+  fn(f->inst_key, ni);
   fn(f->inst_info, ni);
+  fn(f->bucket_key, ni);
+  fn(f->ival, ni);
+  fn(f->info_k, ni);
   fn(f->inst_grad, (size_t)kPartial * ni);
   fn(f->inst_event, ni);
-  fn(f->info_k, ni);
-  fn(f->rank_info, 2 * ns);
   fn(f->grad2d, 9 * ns);
   fn(f->contrib, ns);
   fn(f->dcol, (size_t)kColorRec * ns);
   fn(f->long_list, ns);
   fn(f->ranges, nt);
-  fn(f->tile_order, nt);
+  fn(f->tile_order, nt + (size_t)tile_chunks((int32_t)nt));
+  fn(f->tile_count, nt);
+  fn(f->tile_cursor, nt);
+  fn(f->tile_mid, (size_t)tile_chunks((int32_t)nt));
+  fn(f->big_list, ni / kSortChunkHalf + 1);
   fn(f->work, 2);
   fn(f->d_view_sel, 1);
   fn(f->d_view_ren, 1);

@@ -6,13 +6,21 @@
 //             covariance + 0.3 px^2, conic, square footprint, tile rectangle,
 //             opacity, SH colour.  Writes a 64-byte Splat record, the depth key
 //             and the tile count (0 for a splat that is not drawn).
-//  sort       order-preserving compaction of the drawn splats, stable radix
-//             sort of their FP32 depth bits, then (k_dup) one (tile, splat)
-//             instance per covered tile emitted in depth order, then a stable
-//             radix sort of the instances by tile: the result is the order of
-//             the 64-bit key (tile << 32 | depth), ties by selection order, with
-//             far less key traffic.
-//  k_ranges   first/last instance of every tile.
+//  k_drawn_scan  ranks of the drawn splats (selection order) and their first
+//             instance, one look-back scan.
+//  k_dup      one (tile, splat) instance per covered tile, with its block mask,
+//             and the tiles' instance counts.
+//  k_tile_scan  the tiles' ranges of the instance list, and the tiles by
+//             descending count.
+//  k_bucket   the instances' (depth, index) keys into their tile's range.
+//  k_tile_sort, k_tile_merge  each tile's keys in LDS: by FP32 depth bits, ties
+//             by selection order.  The list is then in the order of the
+//             64-bit key (tile << 32 | depth), ties by selection order.
+//             No splat or instance passes through a global radix sort: a sort
+//             by depth of the splats and one by tile of the instances took 18
+//             launches (82 of a 512 x 512 view's 164 us; 288 us of a street
+//             view with 0.95M drawn splats and 2.1M instances), the five
+//             kernels above take 24 and 160 us there.
 //  k_blend    one workgroup per tile, PX pixels per lane; splat records are
 //             staged in LDS one batch per workgroup size; each 16-lane row
 //             (4x4 pixel blocks) replays only the splats whose alpha >= 1/255
@@ -184,62 +192,210 @@ __global__ void __launch_bounds__(kBlock) k_project(SceneDev S, const ViewConst*
   }
 }
 
-struct LoadDrawn {
-  const uint32_t* tiles;
-  __device__ uint32_t operator()(int64_t i) const { return tiles[i] != 0u ? 1u : 0u; }
-};
+// Ranks of the drawn splats and their first instances in one launch: the scan
+// of (drawn, tile count) over the selection, in order, written for each drawn
+// position as its place in the list of drawn positions and the index of its
+// first instance, and for each 64-instance chunk the rank of the splat that
+// holds its first instance (k_dup's chunks).  A small selection (kDrawnDirect)
+// is cut into tiles of 2 positions per thread, and a tile adds up all
+// positions before it itself: no workgroup waits for another.  A larger one is
+// cut into tiles of 2, above kDrawnWide 8, per thread, taken by ticket (a tile only waits for tiles that running or
+// finished workgroups hold); a tile publishes its two sums and looks back over
+// the tiles before it (lookback_prefix).
+constexpr int kDrawnThreads = 1024;
+constexpr int64_t kDrawnDirect = 65536, kDrawnWide = 524288;
+static_assert(kDrawnTile == 2 * kDrawnThreads, "the look-back words cover the smaller tiles");
 
-// Order-preserving compaction of the drawn splats, done by the scan of their
-// flags: the drawn splat at selection position i has rank = its prefix among
-// the drawn ones; (depth key, i) go to that rank (the sort's input), and so
-// does i in the list of drawn selection positions (kept for the backward).
-struct StoreDrawn {
-  const uint32_t* depth_key;
-  uint32_t* key_out;
-  uint32_t* val_out;
-  uint32_t* list;
-  __device__ void operator()(int64_t i, uint32_t prefix, uint32_t drawn) const {
-    if (!drawn) return;
-    key_out[prefix] = depth_key[i];
-    val_out[prefix] = (uint32_t)i;
-    list[prefix] = (uint32_t)i;
+template <int ITEMS>
+__device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, int64_t n, int64_t tile, bool direct,
+                                           bool last, FrameCounters* ctr, unsigned long long* words, uint32_t* list,
+                                           uint32_t* off, uint32_t* chunk_first, int64_t chunks, uint32_t (*wt)[kDrawnThreads / 64], uint32_t* pre) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t i0 = (tile * kDrawnThreads + t) * ITEMS;
+  uint32_t v[ITEMS];
+  if (i0 + ITEMS <= n) {
+    if (ITEMS == 8) {
+      const uint4 a = *reinterpret_cast<const uint4*>(tiles + i0), b = *reinterpret_cast<const uint4*>(tiles + i0 + 4);
+      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+      v[4 % ITEMS] = b.x; v[5 % ITEMS] = b.y; v[6 % ITEMS] = b.z; v[7 % ITEMS] = b.w;
+    } else {
+      const uint2 a = *reinterpret_cast<const uint2*>(tiles + i0);
+      v[0] = a.x; v[1] = a.y;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) v[k] = i0 + k < n ? tiles[i0 + k] : 0u;
   }
-};
+  uint32_t bc = 0, bd = 0;  // this thread's part of the positions before the tile
+  if (direct) {
+#pragma unroll 4
+    for (int64_t i = 4 * t; i < tile * kDrawnThreads * ITEMS; i += 4 * kDrawnThreads) {
+      const uint4 a = *reinterpret_cast<const uint4*>(tiles + i);
+      bc = add_sat(bc, (a.x + a.y) + (a.z + a.w));  // (a splat has at most 2^20 tiles)
+      bd += (a.x != 0u) + (a.y != 0u) + (a.z != 0u) + (a.w != 0u);
+    }
+  }
+  uint32_t c = 0, d = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    c += v[k];
+    d += v[k] != 0u ? 1u : 0u;
+  }
+  uint32_t xc = c, xd = d;
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) {
+    const uint32_t yc = __shfl_up(xc, s, 64), yd = __shfl_up(xd, s, 64);
+    if (lane >= s) {
+      xc = add_sat(xc, yc);
+      xd += yd;
+    }
+  }
+  uint32_t oc = __shfl_up(xc, 1, 64), od = xd - d;  // of the wave's lanes before
+  oc = lane == 0 ? 0u : oc;
+  if (direct) {
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+      bc = add_sat(bc, __shfl_xor(bc, s, 64));
+      bd += __shfl_xor(bd, s, 64);
+    }
+  }
+  if (lane == 63) {
+    wt[0][wv] = xd;
+    wt[1][wv] = xc;
+    wt[2][wv] = bd;
+    wt[3][wv] = bc;
+  }
+  __syncthreads();
+  uint32_t td = 0, tc = 0, pd = 0, pc = 0;
+#pragma unroll
+  for (int w = 0; w < kDrawnThreads / 64; ++w) {
+    const uint32_t wd = wt[0][w], wc = wt[1][w];
+    od += w < wv ? wd : 0u;
+    oc = add_sat(oc, w < wv ? wc : 0u);
+    td += wd;
+    tc = add_sat(tc, wc);
+    pd += wt[2][w];
+    pc = add_sat(pc, wt[3][w]);
+  }
+  if (!direct) {
+    if (wv < 2) {  // wave 0: the drawn splats, wave 1: the instances
+      const uint32_t x = lookback_prefix(words + wv, 2, tile, wv == 0 ? td : tc);
+      if (lane == 0) pre[wv] = x;
+    }
+    __syncthreads();
+    pd = pre[0];
+    pc = pre[1];
+  }
+  if (last && t == 0) {
+    ctr->n_drawn = (int32_t)(pd + td);
+    ctr->n_instances = (int32_t)add_sat(pc, tc);
+  }
+  od += pd;
+  oc = add_sat(oc, pc);
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t end = add_sat(oc, v[k]);
+    uint32_t ch = 0, ch_end = 0;  // the chunks that start in [oc, end)
+    if (v[k] != 0u) {
+      list[od] = (uint32_t)(i0 + k);
+      off[od] = oc;
+      if ((int64_t)oc < 64 * chunks) {
+        ch = (oc + 63u) / 64u;
+        ch_end = (uint32_t)min((int64_t)((end - 1u) / 64u) + 1, chunks);
+        if (ch < ch_end) chunk_first[ch++] = od;
+      }
+    }
+    // a splat of many chunks is noted by its whole wave
+    for (uint64_t more = __ballot(ch < ch_end); more; more &= more - 1) {  // wave-uniform
+      const int l = __builtin_ctzll(more);
+      const uint32_t b = __shfl(ch, l, 64), e = __shfl(ch_end, l, 64), r = __shfl(od, l, 64);
+      for (uint32_t q = b + lane; q < e; q += 64) chunk_first[q] = r;
+    }
+    od += v[k] != 0u ? 1u : 0u;
+    oc = end;
+  }
+}
 
-struct LoadTilesInOrder {
-  const uint32_t* tiles;
-  const uint32_t* order;
-  __device__ uint32_t operator()(int64_t r) const { return tiles[order[r]]; }
-};
+__global__ void __launch_bounds__(kDrawnThreads) k_drawn_scan(const uint32_t* __restrict__ tiles, FrameCounters* ctr,
+                                                              unsigned long long* words, uint32_t* list,
+                                                              uint32_t* off, uint32_t* chunk_first, int64_t icap) {
+  __shared__ uint32_t wt[4][kDrawnThreads / 64];
+  __shared__ uint32_t pre[2];
+  __shared__ uint32_t s_tile;
+  const int64_t n = ctr->n_render;
+  const int64_t chunks = (icap + 63) / 64;
+  if (n <= kDrawnDirect) {
+    const int64_t ntiles = (n + kDrawnTile - 1) / kDrawnTile;  // at most 32
+    const int64_t tile = blockIdx.x;
+    if (tile < ntiles)
+      drawn_tile<2>(tiles, n, tile, true, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
+    return;
+  }
+  const bool wide = n > kDrawnWide;
+  const int64_t per = wide ? 8 * kDrawnThreads : 2 * kDrawnThreads;
+  const int64_t ntiles = (n + per - 1) / per;
+  if ((int64_t)blockIdx.x >= ntiles) return;  // block-uniform
+  for (;;) {
+    if (threadIdx.x == 0) s_tile = (uint32_t)atomicAdd(&ctr->drawn_ticket, 1);
+    __syncthreads();
+    const int64_t tile = s_tile;
+    if (tile >= ntiles) return;  // block-uniform
+    if (wide) drawn_tile<8>(tiles, n, tile, false, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
+    else drawn_tile<2>(tiles, n, tile, false, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
+    if (ntiles <= (int64_t)gridDim.x) return;  // every tile has a workgroup
+    __syncthreads();
+  }
+}
 
 // Instance emission, load-balanced over the instances: the instances (splat,
-// tile) in depth order of their splats are cut into chunks of 64 and each
+// tile) in selection order of their splats are cut into chunks of 64 and each
 // wave takes a contiguous run of chunks.  The drawn splats whose instances
-// meet a chunk (at most 64, as every drawn splat has one) are found from the
-// instance offsets (the scan of the tile counts in depth order): a 64-ary
-// search for the wave's first chunk, then one comparison per chunk.  Lane l
-// loads the l-th of them (splat, rectangle, 64-byte record and the per-splat
-// part of the block mask) into LDS; lane l then emits instance k0 + l, whose
-// splat is the last one starting at or before it (a binary search over the
-// chunk's splats in LDS).  An instance is its tile key (tile row-major in the
-// rectangle), its emission index (the tile sort carries it) and the (splat,
-// block mask) word: the 4x4 blocks of the tile that the splat's alpha >=
-// 1/255 ellipse can reach (splat_block_mask).  The chunk holding a splat's
-// first instance also writes the splat's record for the projection backward
-// (rank_info) and lists it when it has more than kLongSegment instances.  The
-// instance count is clamped to the capacity here (block 0 publishes the
-// clamped count and flags an overflow); only instances below it are emitted,
-// so only splats whose first instance is emitted get a record or a place on
-// the list.
-constexpr int kDupWaves = kBlock / 64;
+// meet a chunk (at most 64, as every drawn splat has one) start at the one
+// k_drawn_scan noted for the wave's first chunk; one comparison per chunk
+// gives the next.  Lane l loads the l-th of them (splat,
+// rectangle, 64-byte record, depth key and the per-splat part of the block
+// mask) into LDS; lane l then emits instance k0 + l, whose splat is the last
+// one starting at or before it (a binary search over the chunk's splats in
+// LDS).  An instance is its tile (row-major in the rectangle) and depth key,
+// and the (splat, block mask) word: the 4x4 blocks of the tile that the
+// splat's alpha >= 1/255 ellipse can reach (splat_block_mask).  The chunk
+// holding a splat's first instance also lists the splat when it has more than
+// kLongSegment instances.  The instance count is clamped to the capacity here
+// (block 0 publishes the clamped count and flags an overflow); only instances
+// below it are emitted.
+//
+// The tiles' counts: a workgroup counts its own instances per tile in LDS (16
+// bits each) and adds its non-zero counts to tile_count; where the image has
+// more than kLdsTiles tiles, or a workgroup more instances than 16 bits hold,
+// every instance adds to tile_count itself.
+//
+// One workgroup of 16 waves per CU, so the counters are cleared and added up
+// 256 times a launch, not once for every few hundred instances (a 4K view's
+// 64 KB of counters: 37 us against 160 with 2048 workgroups of four waves);
+// four times as many workgroups where a workgroup's instances would outgrow 16
+// bits.  Bound by the block masks' arithmetic: 48 us for 2.1M instances.
+constexpr int kDupThreads = 1024;
+constexpr int kDupWaves = kDupThreads / 64;
+constexpr int kDupFew = 256, kDupGrid = 1024;
+constexpr int kLdsTiles = 32768;
+constexpr int64_t kDupMost = 0xFFFF / (64 * kDupWaves);  // chunks per wave that 16-bit counts hold
 
-__global__ void __launch_bounds__(kBlock) k_dup(FrameCounters* ctr, const uint32_t* order, const uint32_t* inst_off,
-                                                int32_t tiles_x, int64_t cap, uint32_t* ikey, uint32_t* ival,
-                                                uint2* inst_info, uint32_t* long_list,
-                                                const Splat* __restrict__ splats, uint4* rank_info) {
-  __shared__ Splat rec[kDupWaves][64];
-  __shared__ MaskSetup msk[kDupWaves][64];
+// What block_mask needs of a splat, staged per chunk.
+struct alignas(16) DupSplat {
+  float4 mean;    // x hi, lo, y hi, lo
+  float4 shape;   // ce, se, h1, h2
+  float4 bound;   // K, hx, hy, depth bits (K < 0: alpha < 1/255 everywhere)
+};
+
+__global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const uint32_t* __restrict__ list,
+                                                const uint32_t* __restrict__ inst_off,
+                                                const uint32_t* __restrict__ chunk_first, int32_t tiles_x,
+                                                int32_t lds_tiles, int64_t cap, const uint32_t* __restrict__ depth_key,
+                                                uint2* inst_key, uint2* inst_info, uint32_t* long_list,
+                                                const Splat* __restrict__ splats, uint32_t* tile_count) {
+  __shared__ DupSplat rec[kDupWaves][64];
   __shared__ uint4 own[kDupWaves][64];  // (splat, instance offset, rectangle width, x0 | y0 << 16)
+  extern __shared__ uint32_t hist[];    // two 16-bit counts per word (lds_tiles > 0)
   const uint32_t total = (uint32_t)ctr->n_instances;  // the scan's 32-bit sum
   const int64_t n = (int64_t)total > cap ? cap : (int64_t)total;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -248,27 +404,22 @@ __global__ void __launch_bounds__(kBlock) k_dup(FrameCounters* ctr, const uint32
   }
   const int64_t nd = ctr->n_drawn;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t nchunks = (n + 63) / 64, nw = (int64_t)gridDim.x * kDupWaves;
+  const int64_t nchunks = (n + 63) / 64, few = (int64_t)kDupFew * kDupWaves;
+  const int64_t nw = nchunks <= few * kDupMost ? few : (int64_t)gridDim.x * kDupWaves;  // waves, at most
   const int64_t per = (nchunks + nw - 1) / nw;
-  const int64_t c0 = ((int64_t)blockIdx.x * kDupWaves + wv) * per;
-  const int64_t c1 = c0 + per < nchunks ? c0 + per : nchunks;
-  if (c0 >= c1) return;  // wave-uniform; no block barrier below
-  // rf = the last drawn splat with inst_off[rf] <= 64 c0 (inst_off[0] = 0,
-  // offsets strictly increase): 64 samples of [lo, hi) per step, the answer
-  // stays in [lo, hi)
-  int64_t lo = 0, hi = nd;
-  {
-    const uint32_t k0 = (uint32_t)(64 * c0);
-    while (hi - lo > 1) {  // wave-uniform
-      const int64_t span = hi - lo;
-      const bool le = inst_off[lo + span * lane / 64] <= k0;  // a prefix of the lanes (lane 0 always)
-      const int m = 63 - __builtin_clzll(__ballot(le));
-      const int64_t nlo = lo + span * m / 64;
-      hi = m == 63 ? hi : lo + span * (m + 1) / 64;
-      lo = nlo;
-    }
+  // few chunks: as many waves of each workgroup as spread them over 256 (the
+  // waves of a workgroup take neighbouring runs, whose tiles overlap)
+  const int64_t spread = (nchunks + kDupFew - 1) / kDupFew;
+  const int waves = spread < kDupWaves ? (int)spread : kDupWaves;
+  if ((int64_t)blockIdx.x * waves * per >= nchunks) return;  // block-uniform
+  const bool in_lds = lds_tiles > 0 && per <= kDupMost;
+  if (in_lds) {
+    for (int w = threadIdx.x; w < (lds_tiles + 1) / 2; w += kDupThreads) hist[w] = 0u;
+    __syncthreads();
   }
-  int64_t rf = lo;
+  const int64_t c0 = wv < waves ? ((int64_t)blockIdx.x * waves + wv) * per : nchunks;
+  const int64_t c1 = c0 + per < nchunks ? c0 + per : nchunks;
+  int64_t rf = c0 < c1 ? chunk_first[c0] : 0;  // the splat that holds the chunk's first instance
   for (int64_t c = c0; c < c1; ++c) {  // wave-uniform
     const int64_t k0 = 64 * c, k1 = k0 + 64 < n ? k0 + 64 : n;
     // the splats rf .. rf + cnt - 1 start before k1
@@ -277,19 +428,18 @@ __global__ void __launch_bounds__(kBlock) k_dup(FrameCounters* ctr, const uint32
     const bool in = r < nd && (int64_t)off < k1;  // a prefix of the lanes (lane 0 always)
     const int cnt = __popcll(__ballot(in));
     if (in) {
-      const uint32_t i = order[r];
-      const Splat sp = splats[i];  // the one random read per splat (the record holds the rectangle)
+      const uint32_t i = list[r];
+      const Splat sp = splats[i];  // the record holds the rectangle
       const uint32_t x0 = sp.rect_x & 0xFFFFu, y0 = sp.rect_y & 0xFFFFu;
       const uint32_t w = (sp.rect_x >> 16) - x0, h = (sp.rect_y >> 16) - y0;
-      rec[wv][lane] = sp;
-      msk[wv][lane] = block_mask_setup(sp);
+      const MaskSetup ms = block_mask_setup(sp);
+      DupSplat& ds = rec[wv][lane];
+      ds.mean = make_float4(sp.mxh, sp.mxl, sp.myh, sp.myl);
+      ds.shape = make_float4(sp.ce, sp.se, sp.h1, sp.h2);
+      ds.bound = make_float4(ms.ok ? ms.K : -1.0f, ms.hx, ms.hy, __uint_as_float(depth_key[i]));
       own[wv][lane] = make_uint4(i, off, w, x0 | (y0 << 16));
-      if ((int64_t)off >= k0) {  // the splat's first instance is in this chunk
-        rank_info[2 * r] = make_uint4(i, 0u, sp.rect_x, sp.rect_y);
-        rank_info[2 * r + 1] = make_uint4(__float_as_uint(sp.mxh), __float_as_uint(sp.mxl), __float_as_uint(sp.myh),
-                                          __float_as_uint(sp.myl));
-        if (w * h > kLongSegment) long_list[atomicAdd(&ctr->n_long, 1)] = (uint32_t)r;
-      }
+      // the splat's first instance is in this chunk
+      if ((int64_t)off >= k0 && w * h > kLongSegment) long_list[atomicAdd(&ctr->n_long, 1)] = (uint32_t)r;
     }
     __builtin_amdgcn_wave_barrier();
     const int64_t k = k0 + lane;
@@ -301,83 +451,131 @@ __global__ void __launch_bounds__(kBlock) k_dup(FrameCounters* ctr, const uint32
       const uint4 ow = own[wv][o];
       const uint32_t l = (uint32_t)(k - ow.y);
       const uint32_t ty = (ow.w >> 16) + l / ow.z, tx = (ow.w & 0xFFFFu) + l % ow.z;
-      ikey[k] = ty * (uint32_t)tiles_x + tx;
-      ival[k] = (uint32_t)k;  // the tile sort carries the emission index
-      inst_info[k] = make_uint2(ow.x, splat_block_mask(rec[wv][o], msk[wv][o], (int)tx, (int)ty));
+      const uint32_t tile = ty * (uint32_t)tiles_x + tx;
+      const float4 a = rec[wv][o].mean, b = rec[wv][o].shape, q = rec[wv][o].bound;
+      Splat sp;
+      sp.mxh = a.x; sp.mxl = a.y; sp.myh = a.z; sp.myl = a.w;
+      sp.ce = b.x; sp.se = b.y; sp.h1 = b.z; sp.h2 = b.w;
+      MaskSetup ms;
+      ms.K = q.x; ms.hx = q.y; ms.hy = q.z;
+      ms.mx = a.x + a.y; ms.my = a.z + a.w;
+      ms.ok = q.x >= 0.0f;
+      inst_key[k] = make_uint2(tile, __float_as_uint(q.w));
+      inst_info[k] = make_uint2(ow.x, splat_block_mask(sp, ms, (int)tx, (int)ty));
+      if (in_lds) atomicAdd(&hist[tile >> 1], (tile & 1u) ? 0x10000u : 1u);
+      else atomicAdd(&tile_count[tile], 1u);
     }
-    __builtin_amdgcn_wave_barrier();  // rec, msk and own are rewritten by the next chunk
+    __builtin_amdgcn_wave_barrier();  // rec and own are rewritten by the next chunk
     // the next chunk's first splat: the last one starting at or before k1
     const int64_t rn = rf + cnt;
     const uint32_t offn = rn < nd ? inst_off[rn] : 0xFFFFFFFFu;
     rf = (int64_t)offn == k1 ? rn : rn - 1;
   }
-}
-
-// Tile ranges from the tile-sorted keys, one thread per boundary k in
-// [0, n]: between the keys t0 = key[k - 1] and t1 = key[k] (-1 before the
-// first, ntiles after the last; keys >= ntiles, which only an instance
-// overflow produces, count as ntiles) tile t0 ends at k, tile t1 starts at k,
-// and every tile strictly between them is empty (k, k).
-__global__ void __launch_bounds__(kBlock) k_ranges(const FrameCounters* ctr, const uint32_t* key, uint2* ranges,
-                                                   uint32_t ntiles) {
-  const int64_t n = ctr->n_inst_clamped;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k <= n; k += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t0 = k > 0 ? (int64_t)min(key[k - 1], ntiles) : -1;
-    const int64_t t1 = k < n ? (int64_t)min(key[k], ntiles) : (int64_t)ntiles;
-    if (t0 == t1) continue;
-    if (t0 >= 0 && t0 < ntiles) ranges[t0].y = (uint32_t)k;
-    if (t1 < ntiles) ranges[t1].x = (uint32_t)k;
-    for (int64_t t = t0 + 1; t < t1; ++t) ranges[t] = make_uint2((uint32_t)k, (uint32_t)k);
+  if (in_lds) {
+    __syncthreads();
+    for (int w = threadIdx.x; w < (lds_tiles + 1) / 2; w += kDupThreads) {
+      const uint32_t x = hist[w];
+      if (x & 0xFFFFu) atomicAdd(&tile_count[2 * w], x & 0xFFFFu);
+      if (x >> 16) atomicAdd(&tile_count[2 * w + 1], x >> 16);
+    }
   }
 }
 
-// Workgroup order of the blend kernels: tiles by descending class of their
-// instance count n (the bit length of n and the two bits below its leading
-// one, so classes are a quarter octave wide), so the longest workgroups start
-// early; results do not depend on the order of the tiles.  Workgroup b orders
-// the chunk of kOrderChunk tiles starting at b * kOrderChunk (a 1080p frame
-// has one chunk): each tile takes its rank within its class from an LDS
-// counter, and a scan over the classes gives each class its start.  The
-// order within a class is whatever the LDS atomics give.
+// From the tiles' instance counts: the exclusive scan gives every tile its
+// range of the instance list (and the cursor k_bucket fills it from), the
+// chunks of tiles with more than kSortSmall instances are listed, and the
+// tiles are put in the blend kernels' workgroup order: by descending class of
+// the count n (its bit length and the two bits below its leading one, so
+// classes are a quarter octave wide), so the longest workgroups start early;
+// results do not depend on the order of the tiles.  Each of the C workgroups
+// takes one chunk of tile_chunk(ntiles) <= kOrderChunk tiles and sums the
+// counts before it (one workgroup for 8160 tiles was bound by its own
+// instructions: 10.6 us, four take 6): each tile takes its rank within its
+// class from an LDS counter, and a scan over the classes gives each class its
+// start (mid[b] is where the classes of less than 64 instances begin).  The
+// chunks' orders are interleaved (order_place: kNoTile past a shorter chunk's
+// end), so every chunk's longest come first.
+// The order within a class is whatever the LDS atomics give.  The lanes of a wave
+// whose tiles share the first lane's class (empty tiles, mostly) count with
+// one atomic: same-address LDS atomics run one after another.
 constexpr int kOrderThreads = 1024;
-constexpr int kOrderBatch = 8;  // tiles per thread
-constexpr int32_t kOrderChunk = kOrderThreads * kOrderBatch;
+constexpr int kOrderBatch = 2;  // consecutive tiles per thread
+static_assert(kOrderChunk == kOrderThreads * kOrderBatch, "two tiles per thread");
 static_assert(kTileClasses == 128, "one thread per class in waves 0 and 1");
 
-__device__ __forceinline__ int tile_class(uint2 r) {
-  const uint32_t n = r.y - r.x;
+__device__ __forceinline__ int tile_class(uint32_t n) {
   const int bl = min(31, 32 - __clz((int)n));  // 0 for an empty tile
   const int sub = bl >= 3 ? (int)((n >> (bl - 3)) & 3u) : 0;
   return bl * 4 + sub;  // < kTileClasses
 }
 
-__global__ void __launch_bounds__(kOrderThreads) k_tile_order(const uint2* ranges, int32_t ntiles, uint32_t* order) {
+// Instances that a workgroup of k_tile_sort sorts; a tile with more is sorted
+// in chunks of that many, which k_tile_merge puts together.
+constexpr int kSortSmall = 2048;
+static_assert(kSortSmall == 2 * kSortChunkHalf, "the chunk list's length");
+constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
+
+__global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __restrict__ count, int32_t ntiles,
+                                                             FrameCounters* ctr, uint2* ranges, uint32_t* cursor,
+                                                             uint32_t* order, uint32_t* mid, uint2* big_list) {
   __shared__ uint32_t cnt[kTileClasses];
   __shared__ uint32_t half[2];
-  const int32_t lo = blockIdx.x * kOrderChunk;
-  const int32_t n = min(kOrderChunk, ntiles - lo);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint2 r[kOrderBatch];
+  __shared__ uint32_t wt[kOrderThreads / 64], wb[kOrderThreads / 64];
+  __shared__ uint32_t big, big_base;  // this chunk's large tiles' sort chunks
+  const int32_t per = tile_chunk(ntiles), lo = blockIdx.x * per;
+  const int32_t n = min(per, ntiles - lo);
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int32_t k0 = t * kOrderBatch;
+  uint32_t m[kOrderBatch], sum = 0, before = 0;
 #pragma unroll
-  for (int k = 0; k < kOrderBatch; ++k) {
-    const int32_t t = k * kOrderThreads + (int32_t)threadIdx.x;
-    r[k] = t < n ? ranges[lo + t] : make_uint2(0u, 0u);
+  for (int k = 0; k < kOrderBatch; ++k) m[k] = k0 + k < n ? count[lo + k0 + k] : 0u;
+#pragma unroll 4
+  for (int32_t i = t; i < lo; i += kOrderThreads) before += count[i];
+  if (t < kTileClasses) cnt[t] = 0;
+  if (t == 0) big = 0;
+#pragma unroll
+  for (int k = 0; k < kOrderBatch; ++k) sum += m[k];
+  uint32_t x = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+    before += __shfl_xor(before, d, 64);
   }
-  if (threadIdx.x < kTileClasses) cnt[threadIdx.x] = 0;
+  if (lane == 63) {
+    wt[wv] = x;
+    wb[wv] = before;
+  }
   __syncthreads();
+  uint32_t start = x - sum;
+#pragma unroll
+  for (int w = 0; w < kOrderThreads / 64; ++w) start += wb[w] + (w < wv ? wt[w] : 0u);
   uint32_t key[kOrderBatch];  // class << 16 | rank within the class (rank < kOrderChunk)
+  uint32_t big_at[kOrderBatch];
+  const uint64_t lt = lanemask_lt();
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) {
-    const int32_t t = k * kOrderThreads + (int32_t)threadIdx.x;
     key[k] = 0;
-    if (t < n) {
-      const int c = tile_class(r[k]);
-      key[k] = ((uint32_t)c << 16) | atomicAdd(&cnt[c], 1u);
+    const bool in = k0 + k < n;
+    const int c = tile_class(m[k]);
+    const int c0 = __builtin_amdgcn_readfirstlane(c);
+    const uint64_t same = __ballot(in && c == c0);
+    uint32_t base = 0;
+    if (lane == 0 && same) base = atomicAdd(&cnt[c0], (uint32_t)__popcll(same));
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    if (in) {
+      const int32_t tile = lo + k0 + k;
+      ranges[tile] = make_uint2(start, start + m[k]);
+      cursor[tile] = start;
+      start += m[k];
+      key[k] = ((uint32_t)c << 16) | (c == c0 ? base + (uint32_t)__popcll(same & lt) : atomicAdd(&cnt[c], 1u));
+      if (m[k] > (uint32_t)kSortSmall) big_at[k] = atomicAdd(&big, (m[k] + kSortSmall - 1) / kSortSmall);
     }
   }
   __syncthreads();
+  if (t == kOrderThreads - 1 && big != 0u) big_base = (uint32_t)atomicAdd(&ctr->n_big, (int)big);
   // cnt[c] becomes the tiles of all classes above c (waves 0 and 1, whole waves)
-  const int c = threadIdx.x;
+  const int c = t;
   uint32_t incl = 0;
   if (c < kTileClasses) {
     incl = cnt[c];
@@ -391,10 +589,315 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_order(const uint2* range
   __syncthreads();
   if (c < kTileClasses) cnt[c] = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
   __syncthreads();
+  // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
+  if (t == 0) mid[blockIdx.x] = cnt[kWaveClass - 1];
 #pragma unroll
-  for (int k = 0; k < kOrderBatch; ++k) {
-    const int32_t t = k * kOrderThreads + (int32_t)threadIdx.x;
-    if (t < n) order[lo + cnt[key[k] >> 16] + (key[k] & 0xFFFFu)] = (uint32_t)(lo + t);
+  for (int k = 0; k < kOrderBatch; ++k)
+    if (k0 + k < n) {
+      order[order_place(cnt[key[k] >> 16] + (key[k] & 0xFFFFu), blockIdx.x, gridDim.x)] = (uint32_t)(lo + k0 + k);
+      if (m[k] > (uint32_t)kSortSmall)
+        for (uint32_t q = 0; q * kSortSmall < m[k]; ++q)
+          big_list[big_base + big_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
+    } else if (k0 + k < per) {
+      order[order_place((uint32_t)(k0 + k), blockIdx.x, gridDim.x)] = kNoTile;
+    }
+}
+
+// The instances' sort keys (depth bits, emission index) into their tile's
+// range, in any order (the keys are distinct, so the sort fixes it).  A
+// workgroup counts its instances per tile in LDS, the first
+// instance of each tile takes the tile's places with one atomic and hands
+// them to the others; only the counters of tiles it meets are touched.  Bound
+// by those atomics (27 G/s over the chip): 22 us for 2.1M instances.
+// Images of more than kBucketLdsTiles tiles take a place per instance.
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketItems = 8;   // at most, per thread
+constexpr int kBucketGrid = 512;  // a CU takes two where the counters leave room
+constexpr int kBucketLdsTiles = 32768;  // 128 KB of counters
+
+__global__ void __launch_bounds__(kBucketThreads) k_bucket(const FrameCounters* ctr, const uint2* __restrict__ inst_key,
+                                                           int32_t lds_tiles, uint32_t* cursor,
+                                                           unsigned long long* __restrict__ bkey) {
+  extern __shared__ uint32_t place[];
+  const int64_t n = ctr->n_inst_clamped;
+  // items per thread: enough to keep to one round of the grid, at most kBucketItems
+  const int64_t want = (n + (int64_t)gridDim.x * kBucketThreads - 1) / ((int64_t)gridDim.x * kBucketThreads);
+  const int items = (int)(want < 1 ? 1 : (want > kBucketItems ? kBucketItems : want));
+  const int64_t tile_n = (int64_t)items * kBucketThreads;
+  for (int64_t b0 = (int64_t)blockIdx.x * tile_n; b0 < n; b0 += (int64_t)gridDim.x * tile_n) {  // block-uniform
+    uint2 w[kBucketItems];
+    bool in[kBucketItems];
+    uint32_t pos[kBucketItems];
+#pragma unroll
+    for (int u = 0; u < kBucketItems; ++u) {
+      const int64_t k = b0 + u * kBucketThreads + threadIdx.x;
+      in[u] = u < items && k < n;
+      w[u] = in[u] ? inst_key[k] : make_uint2(0u, 0u);
+      pos[u] = 0u;
+    }
+    if (lds_tiles > 0) {
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u]) place[w[u].x] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u]) pos[u] = atomicAdd(&place[w[u].x], 1u);
+      __syncthreads();
+      // the first of a tile takes its places: alone to read the tile's count
+      uint32_t base[kBucketItems];
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u] && pos[u] == 0u) base[u] = atomicAdd(&cursor[w[u].x], place[w[u].x]);
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u] && pos[u] == 0u) place[w[u].x] = base[u];
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u]) pos[u] += place[w[u].x];
+      __syncthreads();
+    } else {
+#pragma unroll
+      for (int u = 0; u < kBucketItems; ++u)
+        if (in[u]) pos[u] = atomicAdd(&cursor[w[u].x], 1u);
+    }
+#pragma unroll
+    for (int u = 0; u < kBucketItems; ++u) {
+      const uint32_t k = (uint32_t)(b0 + u * kBucketThreads + threadIdx.x);
+      if (in[u]) bkey[pos[u]] = ((unsigned long long)w[u].y << 32) | k;
+    }
+  }
+}
+
+// Ascending order of one key per lane over the wave: a bitonic network whose
+// rounds start by comparing mirrored lanes (l ^ (2^k - 1)), so that every step
+// keeps the smaller key in the lower lane.  Partners inside a 16-lane row come
+// by DPP moves.
+#define LODGS_DPP64(v, ctrl)                                                                             \
+  (((unsigned long long)(uint32_t)__builtin_amdgcn_update_dpp(0, (int)((v) >> 32), ctrl, 0xf, 0xf, false) \
+    << 32) |                                                                                              \
+   (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, false))
+
+__device__ __forceinline__ unsigned long long keep(unsigned long long v, unsigned long long o, bool low) {
+  return (v < o) == low ? v : o;
+}
+
+__device__ __forceinline__ unsigned long long wave_sort(unsigned long long v) {
+  const int lane = threadIdx.x & 63;
+  const bool b0 = (lane & 1) == 0, b1 = (lane & 2) == 0, b2 = (lane & 4) == 0, b3 = (lane & 8) == 0;
+  const bool b4 = (lane & 16) == 0, b5 = (lane & 32) == 0;
+  const auto x1 = [](unsigned long long a) { return LODGS_DPP64(a, 0xB1); };    // l ^ 1: quad_perm [1,0,3,2]
+  const auto x2 = [](unsigned long long a) { return LODGS_DPP64(a, 0x4E); };    // l ^ 2: quad_perm [2,3,0,1]
+  const auto x3 = [](unsigned long long a) { return LODGS_DPP64(a, 0x1B); };    // l ^ 3: quad_perm [3,2,1,0]
+  const auto x7 = [](unsigned long long a) { return LODGS_DPP64(a, 0x141); };   // l ^ 7: row_half_mirror
+  const auto x8 = [](unsigned long long a) { return LODGS_DPP64(a, 0x128); };   // l ^ 8: row_ror 8
+  const auto x15 = [](unsigned long long a) { return LODGS_DPP64(a, 0x140); };  // l ^ 15: row_mirror
+  const auto x4 = [&](unsigned long long a) { return x3(x7(a)); };              // l ^ 4
+  v = keep(v, x1(v), b0);
+  v = keep(v, x3(v), b1);
+  v = keep(v, x1(v), b0);
+  v = keep(v, x7(v), b2);
+  v = keep(v, x2(v), b1);
+  v = keep(v, x1(v), b0);
+  v = keep(v, x15(v), b3);
+  v = keep(v, x4(v), b2);
+  v = keep(v, x2(v), b1);
+  v = keep(v, x1(v), b0);
+  v = keep(v, __shfl_xor(v, 31, 64), b4);
+  v = keep(v, x8(v), b3);
+  v = keep(v, x4(v), b2);
+  v = keep(v, x2(v), b1);
+  v = keep(v, x1(v), b0);
+  v = keep(v, __shfl_xor(v, 63, 64), b5);
+  v = keep(v, __shfl_xor(v, 16, 64), b4);
+  v = keep(v, x8(v), b3);
+  v = keep(v, x4(v), b2);
+  v = keep(v, x2(v), b1);
+  v = keep(v, x1(v), b0);
+  return v;
+}
+#undef LODGS_DPP64
+
+// Sorts in[0, m) into keys (LDS; 0 < m <= THREADS * ITEMS, itself a power of two;
+// distinct keys below ~0) with the whole workgroup: runs of 64 in registers,
+// then rounds that merge neighbouring runs, every key finding its place by a
+// binary search of the other run (the searches of a thread's keys run side by
+// side).  Places past m hold ~0, so that every run is whole.
+template <int THREADS, int ITEMS>
+__device__ __forceinline__ void block_sort(const unsigned long long* in, unsigned long long* keys, int m) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  int whole = 64;
+  while (whole < m) whole *= 2;
+  for (int r = wv; r * 64 < whole; r += THREADS / 64) {  // wave-uniform
+    const int j = r * 64 + lane;
+    keys[j] = r * 64 < m ? wave_sort(j < m ? in[j] : ~0ull) : ~0ull;
+  }
+  __syncthreads();
+  for (int w = 64; w < m; w *= 2) {  // block-uniform
+    unsigned long long v[ITEMS];
+    int sib[ITEMS], at[ITEMS];
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) {
+      const int j = e * THREADS + t;
+      v[e] = keys[j];
+      sib[e] = (j & ~(w - 1)) ^ w;
+      at[e] = 0;
+      if (j >= whole) sib[e] = 0;  // past the padded keys: searched for nothing
+    }
+    for (int s = w >> 1; s > 0; s >>= 1) {
+#pragma unroll
+      for (int e = 0; e < ITEMS; ++e) at[e] += keys[sib[e] + at[e] + s - 1] < v[e] ? s : 0;
+    }
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) at[e] += keys[sib[e] + at[e]] < v[e] ? 1 : 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) {
+      const int j = e * THREADS + t;
+      if (j < m) keys[(j & ~(2 * w - 1)) + (j & (w - 1)) + at[e]] = v[e];
+    }
+    __syncthreads();
+  }
+}
+
+// block_sort with as many keys per thread as m needs.
+template <int THREADS>
+__device__ __forceinline__ void block_sort_small(const unsigned long long* in, unsigned long long* keys, int m) {
+  static_assert(kSortSmall == 8 * THREADS, "eight keys per thread at most");
+  if (m <= THREADS) block_sort<THREADS, 1>(in, keys, m);
+  else if (m <= 2 * THREADS) block_sort<THREADS, 2>(in, keys, m);
+  else if (m <= 4 * THREADS) block_sort<THREADS, 4>(in, keys, m);
+  else block_sort<THREADS, 8>(in, keys, m);
+}
+
+// Sorts the tiles' keys: the listed chunks of large tiles (in place, for
+// k_tile_merge), then the tiles by descending class, those of at least 64
+// instances one workgroup each, the others four to a workgroup, each by one
+// wave in registers.  A tile's instance words and emission indices are written
+// in its sorted order.  A fixed grid takes the work in that order (largest
+// first), so no workgroup is launched for nothing.  Bound by the 64-bit
+// comparisons: 5.8 us for 40K instances in 1024 tiles, 41 us (and 27 us for
+// k_tile_merge) for 2.1M in 8160 tiles, 1.3M of them in tiles above 2048.
+constexpr int kSmallThreads = 256;
+constexpr int kSmallItems = kSortSmall / kSmallThreads;
+constexpr int kTileSortGrid = 1792;  // seven workgroups per CU: what the registers allow
+
+__global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters* ctr, const uint2* __restrict__ ranges,
+                                                             const uint32_t* __restrict__ tile_order,
+                                                             const uint32_t* __restrict__ mid, int32_t ntiles,
+                                                             const uint2* __restrict__ big_list,
+                                                             unsigned long long* bkey,
+                                                             const uint2* __restrict__ inst_info,
+                                                             uint2* __restrict__ info_k, uint32_t* __restrict__ ival) {
+  __shared__ unsigned long long keys[kSortSmall];
+  const int t = threadIdx.x, lane = t & 63;
+  const int nb = ctr->n_big;
+  for (int li = blockIdx.x; li < nb; li += gridDim.x) {  // block-uniform
+    const uint2 e = big_list[li];
+    const uint2 rg = ranges[e.x];
+    const uint32_t x = rg.x + e.y * kSortSmall;
+    const int m = (int)min(rg.y - x, (uint32_t)kSortSmall);
+    block_sort_small<kSmallThreads>(bkey + x, keys, m);
+    for (int j = t; j < m; j += kSmallThreads) bkey[x + j] = keys[j];
+    __syncthreads();
+  }
+  // the chunks of the tile order, one after the other; the first items go to
+  // the workgroups after those that took the last ones
+  const int32_t per = tile_chunk(ntiles), nch = tile_chunks(ntiles);
+  int32_t used = nb % (int32_t)gridDim.x;
+  for (int32_t ch = 0; ch < nch; ++ch) {
+    const int32_t n = min(per, ntiles - ch * per), nm = (int32_t)mid[ch];
+    const int32_t items = nm + (n - nm + 3) / 4;
+    int32_t it = (int32_t)blockIdx.x - used;
+    if (it < 0) it += (int32_t)gridDim.x;
+    used = (used + items) % (int32_t)gridDim.x;
+    for (; it < items; it += (int32_t)gridDim.x) {  // block-uniform
+      if (it >= nm) {  // four tiles of less than 64 instances
+        const int32_t at = nm + 4 * (it - nm) + (t >> 6);
+        if (at < n) {  // wave-uniform
+          const uint2 rg = ranges[tile_order[order_place((uint32_t)at, (uint32_t)ch, (uint32_t)nch)]];
+          const int m = (int)(rg.y - rg.x);
+          if (m > 0) {
+            const uint32_t k = (uint32_t)wave_sort(lane < m ? bkey[rg.x + lane] : ~0ull);
+            if (lane < m) {
+              ival[rg.x + lane] = k;
+              info_k[rg.x + lane] = inst_info[k];
+            }
+          }
+        }
+        continue;
+      }
+      const uint2 rg = ranges[tile_order[order_place((uint32_t)it, (uint32_t)ch, (uint32_t)nch)]];
+      if (rg.y - rg.x > (uint32_t)kSortSmall) continue;  // listed in chunks
+      const int m = (int)(rg.y - rg.x);
+      block_sort_small<kSmallThreads>(bkey + rg.x, keys, m);
+      for (int j = t; j < m; j += kSmallThreads) {
+        const uint32_t k = (uint32_t)keys[j];
+        ival[rg.x + j] = k;
+        info_k[rg.x + j] = inst_info[k];
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// Puts the sorted chunks of a large tile together, one workgroup per chunk: a
+// key's place in its tile is its index in its chunk and, for every other
+// chunk, the number of smaller keys there, found by a binary search of the
+// chunk staged in LDS.  All chunks of all large tiles work at once, which
+// counts more here than the extra comparisons of a tile of many chunks.
+__global__ void __launch_bounds__(kSmallThreads) k_tile_merge(const FrameCounters* ctr, const uint2* __restrict__ ranges,
+                                                              const uint2* __restrict__ big_list,
+                                                              const unsigned long long* __restrict__ bkey,
+                                                              const uint2* __restrict__ inst_info,
+                                                              uint2* __restrict__ info_k, uint32_t* __restrict__ ival) {
+  __shared__ unsigned long long keys[kSortSmall];
+  const int t = threadIdx.x;
+  const int nb = ctr->n_big;
+  for (int li = blockIdx.x; li < nb; li += gridDim.x) {  // block-uniform
+    const uint2 e = big_list[li];
+    const uint2 rg = ranges[e.x];
+    const uint32_t x = rg.x + e.y * kSortSmall, nc = (rg.y - rg.x + kSortSmall - 1) / kSortSmall;
+    const int m = (int)min(rg.y - x, (uint32_t)kSortSmall);
+    unsigned long long v[kSmallItems];
+    uint32_t at[kSmallItems];
+#pragma unroll
+    for (int q = 0; q < kSmallItems; ++q) {
+      const int j = q * kSmallThreads + t;
+      v[q] = j < m ? bkey[x + j] : 0ull;
+      at[q] = (uint32_t)j;
+    }
+    for (uint32_t c = 0; c < nc; ++c) {  // block-uniform
+      if (c == e.y) continue;
+      const uint32_t y = rg.x + c * kSortSmall;
+      const int len = (int)min(rg.y - y, (uint32_t)kSortSmall);
+#pragma unroll
+      for (int q = 0; q < kSmallItems; ++q) {
+        const int j = q * kSmallThreads + t;
+        keys[j] = j < len ? bkey[y + j] : ~0ull;
+      }
+      __syncthreads();
+      int less[kSmallItems];
+#pragma unroll
+      for (int q = 0; q < kSmallItems; ++q) less[q] = 0;
+#pragma unroll
+      for (int s = kSortSmall / 2; s > 0; s >>= 1) {
+#pragma unroll
+        for (int q = 0; q < kSmallItems; ++q) less[q] += keys[less[q] + s - 1] < v[q] ? s : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < kSmallItems; ++q) at[q] += (uint32_t)(less[q] + (keys[less[q]] < v[q] ? 1 : 0));
+      __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < kSmallItems; ++q) {
+      if (q * kSmallThreads + t < m) {
+        const uint32_t k = (uint32_t)v[q];
+        ival[rg.x + at[q]] = k;
+        info_k[rg.x + at[q]] = inst_info[k];
+      }
+    }
   }
 }
 
@@ -424,7 +927,9 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   __shared__ uint32_t ev[NT];
   __shared__ uint32_t bm[NT];
   __shared__ uint8_t hits[NW][4][NT];  // per row of each wave: the batch slots it replays, in order
-  const int tile = (int)tile_order[blockIdx.x];
+  const uint32_t place = tile_order[blockIdx.x];
+  if (place == kNoTile) return;  // block-uniform
+  const int tile = (int)place;
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
   int px, pys[PX];
@@ -570,7 +1075,9 @@ __global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp
   __shared__ float4 rec[3][64];     // the batch's records: (mx hi, lo, my hi, lo), (ce, se, h1, h2), (o, r, g, b)
   __shared__ uint8_t hits[4][64];   // per row: the batch slots it replays, in order
   __shared__ uint32_t evr[64];      // per slot: this quarter's event bits
-  const int tile = (int)tile_order[blockIdx.x >> 2], q = (int)(blockIdx.x & 3u);
+  const uint32_t place = tile_order[blockIdx.x >> 2];
+  if (place == kNoTile) return;  // block-uniform
+  const int tile = (int)place, q = (int)(blockIdx.x & 3u);
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x, g = lane >> 4;
   const uint64_t lt = lanemask_lt();
@@ -709,11 +1216,11 @@ __global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp
 
 template <bool COUNT>
 static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], float* d_rgb, hipStream_t st) {
-  const int ntiles = v.tiles_x * v.tiles_y;
+  const int ntiles = tile_places(v.tiles_x * v.tiles_y);
   unsigned long long* work = COUNT ? f->work : nullptr;
   uint32_t* event = COUNT ? nullptr : f->inst_event;
   if (!COUNT && f->blend_px_fwd == 1) {
-    hipLaunchKernelGGL(k_blend_q, dim3(4 * ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges, f->sorted_info,
+    hipLaunchKernelGGL(k_blend_q, dim3(4 * ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges, f->info_k,
                        f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2], d_rgb,
                        reinterpret_cast<uint8_t*>(event));
     return;
@@ -721,17 +1228,17 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
   switch (f->blend_px_fwd) {
     case 1:
       hipLaunchKernelGGL((k_blend<COUNT, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_info, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
+                         f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work);
       break;
     case 4:
       hipLaunchKernelGGL((k_blend<COUNT, 4>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_info, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
+                         f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work);
       break;
     default:
       hipLaunchKernelGGL((k_blend<COUNT, 2>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
-                         f->sorted_info, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
+                         f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work);
       break;
   }
@@ -752,12 +1259,22 @@ int blend_output_arg(const void* func, int* n_args) {
   return -1;
 }
 
+int render_kernel_limits() {
+  // the tile counters of k_dup and k_bucket take more than the default 64 KB on large images
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bucket),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kBucketLdsTiles);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dup), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            2 * kLdsTiles);
+  return e == hipSuccess ? LODGS_OK : hip_fail(e, "lodgs_frame_create: kernel LDS");
+}
+
 void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count, const ViewConst& v,
                    const float bg[3], float* d_rgb, hipStream_t st) {
   const SceneDev& S = render_params(f);
   const int64_t cap = f->caps.max_selected, icap = f->caps.max_instances;
   stage_begin(f, LODGS_STAGE_PROJECT, st);
-  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, st);
+  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, ViewClear{f->tile_count, f->scan_words}, st);
   const int pgrid = 2048;
   switch (S.sh_degree) {
 #define LODGS_PROJECT(D)                                                                                         \
@@ -770,40 +1287,29 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
 #undef LODGS_PROJECT
   }
   stage_end(f, st);
-  stage_begin(f, LODGS_STAGE_DEPTH_SORT, st);
-  // drawn splats only: ranks among them in selection order, then a stable
-  // sort of their depth keys, ties in selection order
-  scan_exclusive(LoadDrawn{f->tiles}, &f->ctr->n_render, cap, f->block_sums,
-                 StoreDrawn{f->depth_key, f->depth_key2, f->order, f->drawn_list}, &f->ctr->n_drawn,
-                 st);
-  SortScratch ws{f->sort_table, f->sort_below};
-  const bool sw = sort_pairs(f->depth_key2, f->order, f->depth_key, f->order2, &f->ctr->n_drawn, cap, 32, ws, st);
-  const uint32_t* order = sw ? f->order2 : f->order;
-  f->sorted_order = order;
-  stage_end(f, st);
-  stage_begin(f, LODGS_STAGE_DUPLICATE, st);
-  scan_exclusive(LoadTilesInOrder{f->tiles, order}, &f->ctr->n_drawn, cap, f->block_sums, f->inst_off,
-                 &f->ctr->n_instances, st);
-  hipLaunchKernelGGL(k_dup, dim3(pgrid), dim3(kBlock), 0, st, f->ctr, order, f->inst_off, v.tiles_x, icap, f->ikey,
-                     f->ival, f->inst_info, f->long_list, f->splats, f->rank_info);
-  stage_end(f, st);
   const int ntiles = v.tiles_x * v.tiles_y;
-  int tbits = 8;
-  while ((1 << tbits) < ntiles) tbits += 8;
-  stage_begin(f, LODGS_STAGE_TILE_SORT, st);
-  // the (splat, block mask) word of each instance moves with it (read in
-  // emission order, so coalesced)
-  const bool sw2 = sort_pairs(f->ikey, f->ival, f->ikey2, f->ival2, &f->ctr->n_inst_clamped, icap, tbits, ws, st,
-                              f->inst_info, f->info_k);
-  f->sorted_ikey = sw2 ? f->ikey2 : f->ikey;
-  f->sorted_ival = sw2 ? f->ival2 : f->ival;
-  f->sorted_info = sw2 ? f->info_k : f->inst_info;
+  stage_begin(f, LODGS_STAGE_DUPLICATE, st);
+  hipLaunchKernelGGL(k_drawn_scan, dim3(256), dim3(kDrawnThreads), 0, st, f->tiles, f->ctr, f->scan_words, f->drawn_list,
+                     f->inst_off, f->chunk_first, icap);
+  const int32_t dup_lds = ntiles <= kLdsTiles ? ntiles : 0;
+  hipLaunchKernelGGL(k_dup, dim3(kDupGrid), dim3(kDupThreads), 4 * ((dup_lds + 1) / 2), st, f->ctr, f->drawn_list,
+                     f->inst_off, f->chunk_first, v.tiles_x, dup_lds, icap, f->depth_key, f->inst_key, f->inst_info, f->long_list,
+                     f->splats, f->tile_count);
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_RANGES, st);
-  hipLaunchKernelGGL(k_ranges, dim3(2048), dim3(kBlock), 0, st, f->ctr, f->sorted_ikey, f->ranges, (uint32_t)ntiles);
-  if (ntiles > 0)
-    hipLaunchKernelGGL(k_tile_order, dim3((ntiles + kOrderChunk - 1) / kOrderChunk), dim3(kOrderThreads), 0, st,
-                       f->ranges, ntiles, f->tile_order);
+  hipLaunchKernelGGL(k_tile_scan, dim3(tile_chunks(ntiles)), dim3(kOrderThreads), 0, st,
+                     f->tile_count, ntiles, f->ctr, f->ranges, f->tile_cursor, f->tile_order, f->tile_mid, f->big_list);
+  stage_end(f, st);
+  stage_begin(f, LODGS_STAGE_TILE_SORT, st);
+  const int32_t bucket_lds = ntiles <= kBucketLdsTiles ? ntiles : 0;
+  hipLaunchKernelGGL(k_bucket, dim3(kBucketGrid), dim3(kBucketThreads), 4 * bucket_lds, st, f->ctr, f->inst_key, bucket_lds,
+                     f->tile_cursor, f->bucket_key);
+  stage_end(f, st);
+  stage_begin(f, LODGS_STAGE_DEPTH_SORT, st);
+  hipLaunchKernelGGL(k_tile_sort, dim3(kTileSortGrid), dim3(kSmallThreads), 0, st, f->ctr, f->ranges,
+                     f->tile_order, f->tile_mid, ntiles, f->big_list, f->bucket_key, f->inst_info, f->info_k, f->ival);
+  hipLaunchKernelGGL(k_tile_merge, dim3(1024), dim3(kSmallThreads), 0, st, f->ctr, f->ranges, f->big_list,
+                     f->bucket_key, f->inst_info, f->info_k, f->ival);
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_BLEND, st);
   launch_blend<false>(f, v, bg, d_rgb, st);
