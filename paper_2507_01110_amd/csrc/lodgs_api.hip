@@ -80,15 +80,14 @@ void stage_end(lodgs_frame* f, hipStream_t st) {
 
 namespace {
 __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                           int64_t cap, ViewClear clear) {
+                           int64_t cap, uint32_t* tile_count) {
   int64_t n = 0;
   if (mode == kViewRender) {
     n = *d_count;
     n = n < 0 ? 0 : (n > cap ? cap : n);
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t words = 2 * ((n + kDrawnTile - 1) / kDrawnTile), ntiles = (int64_t)v.tiles_x * v.tiles_y;
-    for (int64_t i = t0; i < words; i += stride) clear.scan_words[i] = 0ull;
-    for (int64_t i = t0; i < ntiles; i += stride) clear.tile_count[i] = 0u;
+    const int64_t ntiles = (int64_t)v.tiles_x * v.tiles_y;
+    for (int64_t i = t0; i < ntiles; i += stride) tile_count[i] = 0u;
     if (t0 != 0) return;
   }
   *dst = v;
@@ -102,16 +101,15 @@ __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int 
     ctr->n_instances = 0;
     ctr->n_long = 0;
     ctr->n_big = 0;
-    ctr->drawn_ticket = 0;
   }
 }
 }  // namespace
 
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, const ViewClear& clear, hipStream_t st) {
+                     int64_t cap, uint32_t* tile_count, hipStream_t st) {
   // a render's clearing: a few thousand words, spread over 32 workgroups
   const int grid = mode == kViewRender ? 32 : 1, block = mode == kViewRender ? kBlock : 1;
-  hipLaunchKernelGGL(k_set_view, dim3(grid), dim3(block), 0, st, v, dst, ctr, mode, d_count, cap, clear);
+  hipLaunchKernelGGL(k_set_view, dim3(grid), dim3(block), 0, st, v, dst, ctr, mode, d_count, cap, tile_count);
 }
 
 void launch_blend_count(lodgs_frame* f, hipStream_t st);
@@ -586,16 +584,6 @@ struct lodgs_graph {
   hipGraphExec_t exec;
   hipGraphNode_t node_sel, node_ren;
   hipKernelNodeParams p_sel, p_ren;
-  // the captured arguments of the two k_set_view nodes other than the view
-  lodgs::ViewConst* dst_sel;
-  lodgs::ViewConst* dst_ren;
-  FrameCounters* ctr_sel;
-  FrameCounters* ctr_ren;
-  int mode_sel, mode_ren;
-  const int32_t* count_sel;
-  const int32_t* count_ren;
-  int64_t cap_sel, cap_ren;
-  lodgs::ViewClear clear_sel, clear_ren;
   int32_t width, height;
   // the forward blend node: its output image argument is replaced when a
   // replay writes to another image
@@ -610,6 +598,9 @@ struct lodgs_graph {
 };
 
 namespace lodgs {
+
+// Arguments of the kernels that take a captured graph's views.
+constexpr int kSelectBeginArgs = 6, kSetViewArgs = 7;
 
 // Replaces argument `arg` of a captured kernel node (nargs arguments) by the
 // pointer value v.
@@ -631,8 +622,12 @@ int graph_launch(lodgs_graph* g, const lodgs_camera* cam, float tau, float* d_rg
   if (!std::isfinite(tau) || tau < 0.0f) return set_error(LODGS_E_INVALID, "lodgs_graph_launch: bad tau");
   ViewConst vs = make_view(*cam, tau), vr = make_view(*cam, 0.0f);
   vs.spt_scale = g->frame->spt_scale;  // the frame's LoD noise at this launch
-  void* args_s[7] = {&vs, &g->dst_sel, &g->ctr_sel, &g->mode_sel, &g->count_sel, &g->cap_sel, &g->clear_sel};
-  void* args_r[7] = {&vr, &g->dst_ren, &g->ctr_ren, &g->mode_ren, &g->count_ren, &g->cap_ren, &g->clear_ren};
+  // the captured arguments of the two view nodes, with another view (the first)
+  void *args_s[kSelectBeginArgs], *args_r[kSetViewArgs];
+  for (int k = 1; k < kSelectBeginArgs; ++k) args_s[k] = g->p_sel.kernelParams[k];
+  for (int k = 1; k < kSetViewArgs; ++k) args_r[k] = g->p_ren.kernelParams[k];
+  args_s[0] = &vs;
+  args_r[0] = &vr;
   hipKernelNodeParams ps = g->p_sel, pr = g->p_ren;
   ps.kernelParams = args_s;
   pr.kernelParams = args_r;
@@ -686,31 +681,12 @@ static int capture(lodgs_graph* g, hipStream_t st, const char* who, Launch launc
       g->l1_nargs = nargs;
       continue;
     }
-    if (p.func != reinterpret_cast<void*>(&k_set_view)) continue;
-    ViewConst* dst = *reinterpret_cast<ViewConst**>(p.kernelParams[1]);
-    FrameCounters* ctr = *reinterpret_cast<FrameCounters**>(p.kernelParams[2]);
-    const int mode = *reinterpret_cast<int*>(p.kernelParams[3]);
-    const int32_t* cnt = *reinterpret_cast<const int32_t**>(p.kernelParams[4]);
-    const int64_t cap = *reinterpret_cast<int64_t*>(p.kernelParams[5]);
-    const ViewClear clear = *reinterpret_cast<ViewClear*>(p.kernelParams[6]);
-    if (dst == f->d_view_sel) {
+    if (p.func == reinterpret_cast<void*>(&k_select_begin)) {
       g->node_sel = nodes[k];
       g->p_sel = p;
-      g->dst_sel = dst;
-      g->ctr_sel = ctr;
-      g->mode_sel = mode;
-      g->count_sel = cnt;
-      g->cap_sel = cap;
-      g->clear_sel = clear;
-    } else if (dst == f->d_view_ren) {
+    } else if (p.func == reinterpret_cast<void*>(&k_set_view)) {
       g->node_ren = nodes[k];
       g->p_ren = p;
-      g->dst_ren = dst;
-      g->ctr_ren = ctr;
-      g->mode_ren = mode;
-      g->count_ren = cnt;
-      g->cap_ren = cap;
-      g->clear_ren = clear;
     }
   }
   if (e != hipSuccess) return hip_fail(e, who);

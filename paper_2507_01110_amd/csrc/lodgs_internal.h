@@ -106,15 +106,13 @@ struct FrameCounters {
   int32_t n_drawn;
   int32_t n_instances;   // full count
   int32_t n_inst_clamped;
+  int32_t n_chunks;      // SPT candidate chunks of the last select
   int32_t n_bit_words;   // constant: words of the comparator cuts' node bitmask
   int32_t upper_plus_high;
   int32_t spt_count;     // constant n_spt
-  int32_t n_chunks;      // SPT candidate chunks of the last select
-  int32_t seg_total;     // compaction segments of the last select
   int32_t n_long;        // drawn splats with more than kLongSegment instances
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
-  int32_t drawn_ticket;  // next tile of the drawn-splat scan
-  int32_t pad[3];
+  int32_t pad;
 };
 
 struct lodgs_frame {
@@ -130,9 +128,11 @@ struct lodgs_frame {
   uint8_t* upper_test;    // [n_upper] bit 0 culled, bit 1 fine enough
   int32_t* spt_high;      // [n_spt]
   float* spt_X;           // [n_spt]
-  uint32_t* spt_off;      // [n_spt]
-  uint32_t* seg;          // [ceil(n_upper/64) + n_spt + n_nodes/512 + 1]
-  uint32_t* chunk_owner;  // [n_spt + n_nodes/512 + 1] SPT of each candidate chunk
+  uint32_t* cut_selected; // [cut_tiles] per tile of the cut: selected nodes
+  uint4* cut_sums;        // [cut_tiles] and selected upper nodes, visible SPTs, candidates, 0
+  uint32_t* cut_first;    // [cut_tiles] first chunk of each SPT tile
+  int2* cut_chunks;       // [cut_chunks] first node, SPT
+  uint16_t* chunk_count;  // [cut_chunks] selected nodes
   // comparator cuts (allocated when the scene has its hierarchy attached)
   uint32_t* cut_bits;     // [n_bit_words] one bit per node, selected
   int32_t* frontier[2];   // [max_selected] BFS frontiers (ping-pong)
@@ -142,7 +142,7 @@ struct lodgs_frame {
   lodgs::Splat* splats;   // [max_selected]
   uint32_t* depth_key;    // [max_selected]
   uint32_t* tiles;        // [max_selected]
-  unsigned long long* scan_words;  // [2 * drawn_scan_tiles(max_selected)] look-back words of the drawn-splat scan
+  uint2* wave_sums;       // [ceil(max_selected / 64)] per 64 selection positions: tile count, drawn splats
   uint32_t* inst_off;     // [max_selected] first instance of each drawn splat (selection order)
   uint32_t* chunk_first;  // [max_instances / 64 + 1] rank of the splat holding each 64-instance chunk's first
   uint32_t* drawn_list;   // [max_selected] selection positions of the drawn splats (selection order)
@@ -234,6 +234,13 @@ constexpr int kPartial = 11;
 // Floats of the colour backward's per-splat record (written by the forward).
 constexpr int kColorRec = 16;
 
+// Tiles of the cut: of upper nodes, then of SPTs; and the candidate chunks its
+// SPT prefixes make at most (a partial one each).
+constexpr int kCutTile = 256;
+inline int64_t upper_tiles(const SceneDev& S) { return ((int64_t)S.n_upper + kCutTile - 1) / kCutTile; }
+inline int64_t cut_tiles(const SceneDev& S) { return upper_tiles(S) + ((int64_t)S.n_spt + kCutTile - 1) / kCutTile; }
+inline int64_t cut_chunks(const SceneDev& S) { return (int64_t)S.n_spt + S.n_nodes / 512 + 1; }
+
 // The tile order's chunks (k_tile_scan): as many as keep a chunk to
 // kOrderChunk tiles, of equal size but for the last; the order has a place for
 // every tile of whole chunks (kNoTile where the last is shorter).
@@ -255,27 +262,17 @@ inline int32_t tile_places(int32_t ntiles) { return tile_chunks(ntiles) * tile_c
 // one chunk, so it lists at most one chunk per this many instances.
 constexpr int kSortChunkHalf = 1024;
 
-// Selection positions per tile of the drawn-splat scan.
-constexpr int kDrawnTile = 2048;
-inline size_t drawn_scan_tiles(int64_t n) { return (size_t)((n + kDrawnTile - 1) / kDrawnTile); }
-
-// What the render's first kernel clears besides the counters: the tiles'
-// instance counts and the look-back words of the drawn-splat scan (those that
-// n_render positions use).
-struct ViewClear {
-  uint32_t* tile_count;
-  unsigned long long* scan_words;
-};
-
 // Writes the per-view constants to the frame's device slot (one thread): the
 // kernels of a stage read them from there, so a captured graph is replayed
 // for another camera by updating this one node's argument.  The same thread
 // starts the stage's counters: kViewSelect clears the select counters,
 // kViewRender sets n_render = clamp(*d_count, 0, cap) and clears the render's
-// counters; the other threads clear the arrays of `clear` (kViewRender).
+// counters; the other threads clear the tiles' instance counts (kViewRender).
 constexpr int kViewOnly = 0, kViewSelect = 1, kViewRender = 2;
+__global__ void k_select_begin(ViewConst v, ViewConst* dst, FrameCounters* ctr, SceneDev S, uint32_t flags,
+                               uint8_t* utest);
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, const ViewClear& clear, hipStream_t st);
+                     int64_t cap, uint32_t* tile_count, hipStream_t st);
 
 int hip_fail(hipError_t e, const char* what);
 
@@ -344,13 +341,15 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->upper_test, (size_t)S.n_upper);
   fn(f->spt_high, (size_t)S.n_spt);
   fn(f->spt_X, (size_t)S.n_spt);
-  fn(f->spt_off, (size_t)S.n_spt);
-  fn(f->seg, (size_t)(S.n_upper + 63) / 64 + (size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
-  fn(f->chunk_owner, (size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
+  fn(f->cut_selected, (size_t)cut_tiles(S));
+  fn(f->cut_sums, (size_t)cut_tiles(S));
+  fn(f->cut_first, (size_t)cut_tiles(S));
+  fn(f->cut_chunks, (size_t)cut_chunks(S));
+  fn(f->chunk_count, (size_t)cut_chunks(S));
   fn(f->splats, ns);
   fn(f->depth_key, ns);
   fn(f->tiles, ns);
-  fn(f->scan_words, 2 * drawn_scan_tiles((int64_t)ns));
+  fn(f->wave_sums, (ns + 63) / 64);
   fn(f->inst_off, ns);
   fn(f->chunk_first, ni / 64 + 1);
   fn(f->drawn_list, ns);

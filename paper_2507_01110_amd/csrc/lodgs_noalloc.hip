@@ -1,7 +1,7 @@
 // lodgs_lod_select_noalloc: the HSPT cut of lodgs_lod_select for callers that
 // cannot allocate device memory.  The select stage's workspace (counters,
-// view constants, scan block sums, per-upper-node and per-SPT arrays, the
-// compaction segments) lives in one file-scope device array instead of a
+// view constants, per-upper-node, per-SPT and per-tile arrays, the candidate
+// chunks) lives in one file-scope device array instead of a
 // frame; the kernels are those of lodgs_lod_select.
 //
 // A __device__ array's name in host code is only a host-side handle, so the
@@ -16,7 +16,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = LODGS_NOALLOC_SCRATCH_BYTES;
+constexpr size_t kScratchBytes = LODGS_NOALLOC_SCRATCH_BYTES / 16 * 21;
 constexpr int kMaxDevices = 64;
 constexpr size_t kAlign = 256;
 
@@ -56,21 +56,38 @@ struct Carve {
   }
 };
 
+// The bytes that decide whether a scene is taken (LODGS_NOALLOC_SCRATCH_BYTES
+// at most): 2 per upper node, 12 per SPT and two words per compaction segment,
+// with the counters, the view and 512 scan words.  The workspace itself is at
+// most a quarter larger (10 bytes against 8 for every 512 nodes), which
+// kScratchBytes leaves room for.
+size_t scene_bytes(const SceneDev& S) {
+  Carve c{nullptr};
+  (void)c.take<FrameCounters>(1);
+  (void)c.take<lodgs::ViewConst>(1);
+  (void)c.take<uint32_t>(lodgs::kScanGrid + 1);
+  for (int k = 0; k < 2; ++k) (void)c.take<uint8_t>((size_t)S.n_upper);
+  for (int k = 0; k < 3; ++k) (void)c.take<uint32_t>((size_t)S.n_spt);
+  (void)c.take<uint32_t>((size_t)(S.n_upper + 63) / 64 + (size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
+  (void)c.take<uint32_t>((size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
+  return c.off;
+}
+
 size_t layout(const SceneDev& S, unsigned char* base, lodgs_frame* f) {
   Carve c{base};
   lodgs_frame tmp{};
   lodgs_frame& g = f ? *f : tmp;
   g.ctr = c.take<FrameCounters>(1);
   g.d_view_sel = c.take<lodgs::ViewConst>(1);
-  g.block_sums = c.take<uint32_t>(lodgs::kScanGrid + 1);
   g.upper_sel = c.take<uint8_t>((size_t)S.n_upper);
   g.upper_test = c.take<uint8_t>((size_t)S.n_upper);
   g.spt_high = c.take<int32_t>((size_t)S.n_spt);
   g.spt_X = c.take<float>((size_t)S.n_spt);
-  g.spt_off = c.take<uint32_t>((size_t)S.n_spt);
-  // the same lengths lodgs_frame_create gives these two
-  g.seg = c.take<uint32_t>((size_t)(S.n_upper + 63) / 64 + (size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
-  g.chunk_owner = c.take<uint32_t>((size_t)S.n_spt + (size_t)S.n_nodes / 512 + 1);
+  g.cut_selected = c.take<uint32_t>((size_t)lodgs::cut_tiles(S));
+  g.cut_sums = c.take<uint4>((size_t)lodgs::cut_tiles(S));
+  g.cut_first = c.take<uint32_t>((size_t)lodgs::cut_tiles(S));
+  g.cut_chunks = c.take<int2>((size_t)lodgs::cut_chunks(S));
+  g.chunk_count = c.take<uint16_t>((size_t)lodgs::cut_chunks(S));
   return c.off;
 }
 
@@ -95,8 +112,7 @@ extern "C" int lodgs_lod_select_noalloc(const lodgs_scene* scene, const lodgs_ca
     return lodgs::set_error(LODGS_E_INVALID, "lodgs_lod_select_noalloc: capacity");
   if (flags & ~(LODGS_CULL | LODGS_CONSERVATIVE))
     return lodgs::set_error(LODGS_E_INVALID, "lodgs_lod_select_noalloc: only LODGS_CULL and LODGS_CONSERVATIVE");
-  const size_t need = layout(scene->dev, nullptr, nullptr);
-  if (need > kScratchBytes)
+  if (scene_bytes(scene->dev) > LODGS_NOALLOC_SCRATCH_BYTES || layout(scene->dev, nullptr, nullptr) > kScratchBytes)
     return lodgs::set_error(LODGS_E_CAPACITY,
                             "lodgs_lod_select_noalloc: the scene's select workspace exceeds the static scratch "
                             "(LODGS_NOALLOC_SCRATCH_BYTES)");

@@ -58,47 +58,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* w
   return base + x - v;
 }
 
-// ---------------------------------------------------------------- look-back
-// One word per tile of a single-pass scan: 0 while the tile's sum is unknown,
-// then the flag kLookSum with its own sum, then kLookAll with the sum of it
-// and all tiles before.  A word carries all there is to read, so relaxed
-// accesses at agent scope (tiles run on different XCDs) are enough.  Sums
-// saturate at 2^32 - 1, so one past 32 bits still reads as past any capacity.
+// a + b, at most 2^32 - 1: a sum past 32 bits still reads as past any capacity.
 __device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
-
-constexpr unsigned long long kLookSum = 1ull << 32, kLookAll = 2ull << 32;
-
-// Publishes the tile's sum, adds up the tiles before it (64 words at a time,
-// newest first, up to one that holds the sum of all before) and publishes the
-// whole; returns the sum of the tiles before.  One full wave; the word of tile
-// j is words[j * stride].  Waits for tiles with smaller numbers only: number
-// them by ticket.
-__device__ __forceinline__ uint32_t lookback_prefix(unsigned long long* words, int stride, int64_t tile, uint32_t own) {
-  const int lane = threadIdx.x & 63;
-  uint32_t prefix = 0;
-  if (tile > 0) {
-    if (lane == 0) __hip_atomic_store(words + tile * stride, kLookSum | own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int64_t j = tile - 1; j >= 0;) {  // wave-uniform
-      const unsigned long long w =
-          j >= lane ? __hip_atomic_load(words + (j - lane) * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                    : kLookAll;  // before the first tile: a sum of 0
-      const uint64_t open = __ballot(w < kLookSum), all = __ballot(w >= kLookAll);
-      const int first_all = all ? __builtin_ctzll(all) : 64, first_open = open ? __builtin_ctzll(open) : 64;
-      const int use = first_all < first_open ? first_all + 1 : first_open;  // lanes that can be added
-      uint32_t x = lane < use ? (uint32_t)w : 0u;
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) x = add_sat(x, __shfl_xor(x, d, 64));
-      prefix = add_sat(prefix, x);
-      if (first_all < first_open) break;
-      j -= use;
-      if (use == 0) __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  if (lane == 0)
-    __hip_atomic_store(words + tile * stride, kLookAll | add_sat(prefix, own), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  return prefix;
-}
 
 // ---------------------------------------------------------------- scan
 template <class Load>

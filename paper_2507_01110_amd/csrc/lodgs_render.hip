@@ -7,7 +7,7 @@
 //             opacity, SH colour.  Writes a 64-byte Splat record, the depth key
 //             and the tile count (0 for a splat that is not drawn).
 //  k_drawn_scan  ranks of the drawn splats (selection order) and their first
-//             instance, one look-back scan.
+//             instance.
 //  k_dup      one (tile, splat) instance per covered tile, with its block mask,
 //             and the tiles' instance counts.
 //  k_tile_scan  the tiles' ranges of the instance list, and the tiles by
@@ -160,16 +160,21 @@ __device__ __forceinline__ void sh_color(const SceneDev& S, const ViewConst& v, 
 }
 
 template <int DEG>
-__global__ void __launch_bounds__(kBlock) k_project(SceneDev S, const ViewConst* __restrict__ vp, const int32_t* idx,
+__global__ void __launch_bounds__(kBlock, 3) k_project(SceneDev S, const ViewConst* __restrict__ vp, const int32_t* idx,
                                                     const int32_t* d_count, int64_t cap, Splat* splats,
                                                     uint32_t* depth_key, uint32_t* tiles, ushort4* rect,
-                                                    float* dcol) {
+                                                    float* dcol, uint2* wave_sums) {
   const ViewConst v = *vp;
   const int64_t n = clamp_count(d_count, cap);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t node = idx[i];
-    Proj P = project_node(S, v, node);
+  const int lane = threadIdx.x & 63;
+  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63); i0 < n;
+       i0 += (int64_t)gridDim.x * blockDim.x) {  // wave-uniform
+    const int64_t i = i0 + lane;
     uint32_t t = 0;
+    Proj P;
+    P.visible = false;
+    const int32_t node = i < n ? idx[i] : 0;
+    if (i < n) P = project_node(S, v, node);
     if (P.visible) {
       float raw[3], J[9], dir[3], il;
       sh_color<DEG>(S, v, node, raw, J, dir, il);
@@ -188,7 +193,11 @@ __global__ void __launch_bounds__(kBlock) k_project(SceneDev S, const ViewConst*
       depth_key[i] = __float_as_uint(P.depth);
       rect[i] = make_ushort4((unsigned short)P.x0, (unsigned short)P.x1, (unsigned short)P.y0, (unsigned short)P.y1);
     }
-    tiles[i] = t;  // 0: not drawn
+    if (i < n) tiles[i] = t;  // 0: not drawn
+    const uint32_t drawn = (uint32_t)__popcll(__ballot(t != 0u));
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d, 64);  // (a splat has at most 2^20 tiles)
+    if (lane == 0) wave_sums[i0 >> 6] = make_uint2(t, drawn);
   }
 }
 
@@ -196,27 +205,25 @@ __global__ void __launch_bounds__(kBlock) k_project(SceneDev S, const ViewConst*
 // of (drawn, tile count) over the selection, in order, written for each drawn
 // position as its place in the list of drawn positions and the index of its
 // first instance, and for each 64-instance chunk the rank of the splat that
-// holds its first instance (k_dup's chunks).  A small selection (kDrawnDirect)
-// is cut into tiles of 2 positions per thread, and a tile adds up all
-// positions before it itself: no workgroup waits for another.  A larger one is
-// cut into tiles of 2, above kDrawnWide 8, per thread, taken by ticket (a tile only waits for tiles that running or
-// finished workgroups hold); a tile publishes its two sums and looks back over
-// the tiles before it (lookback_prefix).
+// holds its first instance (k_dup's chunks).  A workgroup takes a tile of 2
+// positions per thread (8 above kDrawnWide) and adds up the projection's sums
+// of all positions before it itself, so none waits for another (look-back over
+// tiles numbered by ticket: 6.2 us at 170K positions, 16 at 1.5M).
 constexpr int kDrawnThreads = 1024;
-constexpr int64_t kDrawnDirect = 65536, kDrawnWide = 524288;
-static_assert(kDrawnTile == 2 * kDrawnThreads, "the look-back words cover the smaller tiles");
+constexpr int64_t kDrawnWide = 524288;
 
 template <int ITEMS>
-__device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, int64_t n, int64_t tile, bool direct,
-                                           bool last, FrameCounters* ctr, unsigned long long* words, uint32_t* list,
-                                           uint32_t* off, uint32_t* chunk_first, int64_t chunks, uint32_t (*wt)[kDrawnThreads / 64], uint32_t* pre) {
+__device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, const uint2* __restrict__ wave_sums,
+                                           int64_t n, int64_t tile, bool last, FrameCounters* ctr, uint32_t* list,
+                                           uint32_t* off, uint32_t* chunk_first, int64_t chunks,
+                                           uint32_t (*wt)[kDrawnThreads / 64]) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int64_t i0 = (tile * kDrawnThreads + t) * ITEMS;
   uint32_t v[ITEMS];
   if (i0 + ITEMS <= n) {
     if (ITEMS == 8) {
       const uint4 a = *reinterpret_cast<const uint4*>(tiles + i0), b = *reinterpret_cast<const uint4*>(tiles + i0 + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+      v[0] = a.x; v[1] = a.y; v[2 % ITEMS] = a.z; v[3 % ITEMS] = a.w;
       v[4 % ITEMS] = b.x; v[5 % ITEMS] = b.y; v[6 % ITEMS] = b.z; v[7 % ITEMS] = b.w;
     } else {
       const uint2 a = *reinterpret_cast<const uint2*>(tiles + i0);
@@ -227,13 +234,11 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, i
     for (int k = 0; k < ITEMS; ++k) v[k] = i0 + k < n ? tiles[i0 + k] : 0u;
   }
   uint32_t bc = 0, bd = 0;  // this thread's part of the positions before the tile
-  if (direct) {
 #pragma unroll 4
-    for (int64_t i = 4 * t; i < tile * kDrawnThreads * ITEMS; i += 4 * kDrawnThreads) {
-      const uint4 a = *reinterpret_cast<const uint4*>(tiles + i);
-      bc = add_sat(bc, (a.x + a.y) + (a.z + a.w));  // (a splat has at most 2^20 tiles)
-      bd += (a.x != 0u) + (a.y != 0u) + (a.z != 0u) + (a.w != 0u);
-    }
+  for (int64_t i = t; i < tile * (kDrawnThreads * ITEMS / 64); i += kDrawnThreads) {
+    const uint2 a = wave_sums[i];
+    bc = add_sat(bc, a.x);
+    bd += a.y;
   }
   uint32_t c = 0, d = 0;
 #pragma unroll
@@ -249,16 +254,11 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, i
       xc = add_sat(xc, yc);
       xd += yd;
     }
+    bc = add_sat(bc, __shfl_xor(bc, s, 64));
+    bd += __shfl_xor(bd, s, 64);
   }
   uint32_t oc = __shfl_up(xc, 1, 64), od = xd - d;  // of the wave's lanes before
   oc = lane == 0 ? 0u : oc;
-  if (direct) {
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
-      bc = add_sat(bc, __shfl_xor(bc, s, 64));
-      bd += __shfl_xor(bd, s, 64);
-    }
-  }
   if (lane == 63) {
     wt[0][wv] = xd;
     wt[1][wv] = xc;
@@ -276,15 +276,6 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, i
     tc = add_sat(tc, wc);
     pd += wt[2][w];
     pc = add_sat(pc, wt[3][w]);
-  }
-  if (!direct) {
-    if (wv < 2) {  // wave 0: the drawn splats, wave 1: the instances
-      const uint32_t x = lookback_prefix(words + wv, 2, tile, wv == 0 ? td : tc);
-      if (lane == 0) pre[wv] = x;
-    }
-    __syncthreads();
-    pd = pre[0];
-    pc = pre[1];
   }
   if (last && t == 0) {
     ctr->n_drawn = (int32_t)(pd + td);
@@ -316,33 +307,18 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, i
   }
 }
 
-__global__ void __launch_bounds__(kDrawnThreads) k_drawn_scan(const uint32_t* __restrict__ tiles, FrameCounters* ctr,
-                                                              unsigned long long* words, uint32_t* list,
-                                                              uint32_t* off, uint32_t* chunk_first, int64_t icap) {
+__global__ void __launch_bounds__(kDrawnThreads) k_drawn_scan(const uint32_t* __restrict__ tiles,
+                                                              const uint2* __restrict__ wave_sums, FrameCounters* ctr,
+                                                              uint32_t* list, uint32_t* off, uint32_t* chunk_first,
+                                                              int64_t icap) {
   __shared__ uint32_t wt[4][kDrawnThreads / 64];
-  __shared__ uint32_t pre[2];
-  __shared__ uint32_t s_tile;
-  const int64_t n = ctr->n_render;
-  const int64_t chunks = (icap + 63) / 64;
-  if (n <= kDrawnDirect) {
-    const int64_t ntiles = (n + kDrawnTile - 1) / kDrawnTile;  // at most 32
-    const int64_t tile = blockIdx.x;
-    if (tile < ntiles)
-      drawn_tile<2>(tiles, n, tile, true, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
-    return;
-  }
+  const int64_t n = ctr->n_render, chunks = (icap + 63) / 64;
   const bool wide = n > kDrawnWide;
-  const int64_t per = wide ? 8 * kDrawnThreads : 2 * kDrawnThreads;
-  const int64_t ntiles = (n + per - 1) / per;
-  if ((int64_t)blockIdx.x >= ntiles) return;  // block-uniform
-  for (;;) {
-    if (threadIdx.x == 0) s_tile = (uint32_t)atomicAdd(&ctr->drawn_ticket, 1);
-    __syncthreads();
-    const int64_t tile = s_tile;
-    if (tile >= ntiles) return;  // block-uniform
-    if (wide) drawn_tile<8>(tiles, n, tile, false, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
-    else drawn_tile<2>(tiles, n, tile, false, tile == ntiles - 1, ctr, words, list, off, chunk_first, chunks, wt, pre);
-    if (ntiles <= (int64_t)gridDim.x) return;  // every tile has a workgroup
+  const int64_t per = wide ? 8 * kDrawnThreads : 2 * kDrawnThreads, ntiles = (n + per - 1) / per;
+  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {  // block-uniform
+    const bool last = tile == ntiles - 1;
+    if (wide) drawn_tile<8>(tiles, wave_sums, n, tile, last, ctr, list, off, chunk_first, chunks, wt);
+    else drawn_tile<2>(tiles, wave_sums, n, tile, last, ctr, list, off, chunk_first, chunks, wt);
     __syncthreads();
   }
 }
@@ -427,6 +403,7 @@ __global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const u
     const uint32_t off = r < nd ? inst_off[r] : 0xFFFFFFFFu;
     const bool in = r < nd && (int64_t)off < k1;  // a prefix of the lanes (lane 0 always)
     const int cnt = __popcll(__ballot(in));
+    bool is_long = false;
     if (in) {
       const uint32_t i = list[r];
       const Splat sp = splats[i];  // the record holds the rectangle
@@ -438,8 +415,14 @@ __global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const u
       ds.shape = make_float4(sp.ce, sp.se, sp.h1, sp.h2);
       ds.bound = make_float4(ms.ok ? ms.K : -1.0f, ms.hx, ms.hy, __uint_as_float(depth_key[i]));
       own[wv][lane] = make_uint4(i, off, w, x0 | (y0 << 16));
-      // the splat's first instance is in this chunk
-      if ((int64_t)off >= k0 && w * h > kLongSegment) long_list[atomicAdd(&ctr->n_long, 1)] = (uint32_t)r;
+      is_long = (int64_t)off >= k0 && w * h > kLongSegment;  // and its first instance is in this chunk
+    }
+    const uint64_t longs = __ballot(is_long);
+    if (longs != 0ull) {  // wave-uniform: one atomic per chunk
+      uint32_t at = 0;
+      if (lane == 0) at = (uint32_t)atomicAdd(&ctr->n_long, __popcll(longs));
+      at = __shfl(at, 0, 64);
+      if (is_long) long_list[at + (uint32_t)__popcll(longs & lanemask_lt())] = (uint32_t)r;
     }
     __builtin_amdgcn_wave_barrier();
     const int64_t k = k0 + lane;
@@ -1274,12 +1257,12 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   const SceneDev& S = render_params(f);
   const int64_t cap = f->caps.max_selected, icap = f->caps.max_instances;
   stage_begin(f, LODGS_STAGE_PROJECT, st);
-  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, ViewClear{f->tile_count, f->scan_words}, st);
+  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, f->tile_count, st);
   const int pgrid = 2048;
   switch (S.sh_degree) {
 #define LODGS_PROJECT(D)                                                                                         \
   hipLaunchKernelGGL(k_project<D>, dim3(pgrid), dim3(kBlock), 0, st, S, f->d_view_ren, d_idx, d_count, cap,   \
-                     f->splats, f->depth_key, f->tiles, f->rect, f->dcol)
+                     f->splats, f->depth_key, f->tiles, f->rect, f->dcol, f->wave_sums)
     case 0: LODGS_PROJECT(0); break;
     case 1: LODGS_PROJECT(1); break;
     case 2: LODGS_PROJECT(2); break;
@@ -1289,7 +1272,7 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   stage_end(f, st);
   const int ntiles = v.tiles_x * v.tiles_y;
   stage_begin(f, LODGS_STAGE_DUPLICATE, st);
-  hipLaunchKernelGGL(k_drawn_scan, dim3(256), dim3(kDrawnThreads), 0, st, f->tiles, f->ctr, f->scan_words, f->drawn_list,
+  hipLaunchKernelGGL(k_drawn_scan, dim3(512), dim3(kDrawnThreads), 0, st, f->tiles, f->wave_sums, f->ctr, f->drawn_list,
                      f->inst_off, f->chunk_first, icap);
   const int32_t dup_lds = ntiles <= kLdsTiles ? ntiles : 0;
   hipLaunchKernelGGL(k_dup, dim3(kDupGrid), dim3(kDupThreads), 4 * ((dup_lds + 1) / 2), st, f->ctr, f->drawn_list,

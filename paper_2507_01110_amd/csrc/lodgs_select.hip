@@ -1,6 +1,7 @@
 // LoD cut over the flattened HSPT (Sec. 4.3 two-step cut; Sec. 4.1 Eq. 4 and
 // Alg. 2 for the SPTs) and order-preserving stream compaction of the result.
 //
+// Step 0 (k_select_begin): the view constants and the upper nodes' view tests.
 // Step 1 (k_cut_upper): one thread per upper node and per SPT root.  A node is
 // reached when no upper ancestor "stops" the descent (stops = culled, or fine
 // enough at its own distance); the ancestor chain of the balanced upper
@@ -10,32 +11,46 @@
 // visible, and a binary search over the SPT's r_max (descending) gives the
 // candidate prefix length high_j = #{r_max > X_j}.  X_j is taken at the root's
 // distance times the view's LoD noise factor (1 outside noisy training; the
-// upper nodes' own distances are never scaled).
-// Step 2: the candidates (upper nodes, then the prefixes of the visible SPTs)
-// are compacted in order with wave ballots, one wave per segment.
+// upper nodes' own distances are never scaled).  The visible prefixes are
+// listed in chunks of kChunk candidates.
+// Step 2 (k_cut_count): a wave per chunk counts its selected candidates (r_min
+// <= X_j).
+// Step 3 (k_cut_write): the selected nodes are written in layout order, a wave
+// per chunk, at the sum of the counts before it.
+// Four launches and no workgroup that waits for another.  A small view's cut is
+// bound by the launches' latency: 18 us on a 32,767-node scene and 38 on 12M
+// nodes, street level (nine launches, with two-kernel scans: 31 and 48).  Tiles numbered by ticket that look back over published
+// counts took longer than adding the counts up (a contended ticket costs 0.1
+// to 0.2 us a tile here), and a wave per SPT left the SPTs of tens of
+// thousands of candidates, which city scenes have, to one wave each.
 #include "lodgs_internal.h"
 
 namespace lodgs {
 
-namespace {
-
-// Per upper node, the two view tests of the cut, evaluated once per view:
-// bit 0 = culled (its sphere is outside the frustum, when culling), bit 1 =
-// fine enough (r_min <= X at its own distance).  The descent stops at a node
-// with either bit; an upper node is selected when it is reached, not culled
-// and fine enough.
-__global__ void __launch_bounds__(kBlock) k_upper_tests(SceneDev S, const ViewConst* __restrict__ vp, uint32_t flags,
-                                                        uint8_t* utest) {
-  const ViewConst v = *vp;
+// Writes the view constants for the kernels that follow, clears the cut's
+// counters, and evaluates per upper node the two view
+// tests of the cut: bit 0 = culled (its sphere is outside the frustum, when
+// culling), bit 1 = fine enough (r_min <= X at its own distance).  The descent
+// stops at a node with either bit; an upper node is selected when it is
+// reached, not culled and fine enough.  (A captured graph is replayed for
+// another camera by updating v in this node's arguments.)
+__global__ void __launch_bounds__(kBlock) k_select_begin(ViewConst v, ViewConst* dst, FrameCounters* ctr, SceneDev S,
+                                                         uint32_t flags, uint8_t* utest) {
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  if (t0 == 0) {
+    *dst = v;
+    ctr->n_chunks = 0;
+  }
   const bool cull = (flags & LODGS_CULL) != 0;
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < S.n_upper;
-       u += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t u = t0; u < S.n_upper; u += stride) {
     const float mx = S.means[3 * u], my = S.means[3 * u + 1], mz = S.means[3 * u + 2];
     const bool culled = cull && sphere_culled(v, mx, my, mz, S.rho[u]);
     const bool fine = S.r_min[u] <= view_distance(v, mx, my, mz) * v.k;
     utest[u] = (uint8_t)((culled ? 1u : 0u) | (fine ? 2u : 0u));
   }
 }
+
+namespace {
 
 // Longest ancestor chain a walk follows (a malformed parent array with a
 // cycle then reads as "not reached" instead of looping).
@@ -143,177 +158,252 @@ __global__ void __launch_bounds__(kBlock) k_anc_fill(SceneDev S, int32_t D, int3
   }
 }
 
+// A tile of the cut: kCutTile upper nodes, or kCutTile SPTs (tiles follow the
+// layout order: the upper nodes', then the SPTs').  The SPT prefixes' chunks
+// hold at most kChunk candidates.
+constexpr int32_t kChunk = 512;
+constexpr int kChunkGrid = 1024;  // workgroups over the chunks, four waves each
+static_assert(kCutTile == kBlock, "one upper node or SPT per thread");
+
+// Per tile: the upper nodes' decisions and their count, or the SPTs' candidate
+// prefixes and their chunks (first node, SPT), which a tile appends to the
+// list in order (the tiles in any order: first[tile] is where).
 __global__ void __launch_bounds__(kBlock) k_cut_upper(SceneDev S, const ViewConst* __restrict__ vp, uint32_t flags,
                                                       const uint8_t* utest, uint8_t* upper_sel, int32_t* spt_high,
-                                                      float* spt_X, FrameCounters* ctr, CacheDev C) {
-  const ViewConst v = *vp;
-  const bool cull = (flags & LODGS_CULL) != 0;
-  const bool conservative = (flags & LODGS_CONSERVATIVE) != 0 && S.spt_radius != nullptr;
+                                                      float* spt_X, FrameCounters* ctr, int32_t n_upper_tiles, uint32_t* selected,
+                                                      uint4* sums, uint32_t* first, int2* chunks, CacheDev C) {
+  __shared__ uint32_t wt[kBlock / 64];
+  __shared__ uint32_t w3[3][kBlock / 64];
+  __shared__ uint32_t s_base;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int64_t total = (int64_t)S.n_upper + S.n_spt;
-  int vis = 0, hsum = 0;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    if (e < S.n_upper) {
-      const int32_t u = (int32_t)e;
-      upper_sel[u] = (utest[u] == 2u && reached(S, utest, e, total, S.upper_parent[u])) ? 1 : 0;
-    } else {
-      const int32_t j = (int32_t)(e - S.n_upper);
-      const int32_t b = S.spt_begin[j], m = S.spt_begin[j + 1] - b;
-      int32_t high = 0;
-      float X = 0.0f;
-      uint8_t vst = 0;
-      if (reached(S, utest, e, total, S.spt_parent[j])) {
-        const float mx = S.means[3 * (int64_t)b], my = S.means[3 * (int64_t)b + 1], mz = S.means[3 * (int64_t)b + 2];
-        if (!(cull && sphere_culled(v, mx, my, mz, S.rho[b]))) {
-          const float d = view_distance(v, mx, my, mz) * v.spt_scale;  // the LoD noise (1: none)
-          X = conservative ? fmaxf(0.0f, d - S.spt_radius[j]) * v.k : d * v.k;
-          if (C.cached) {  // the cache's ratio test (squared, FP32)
-            vst = 2;
-            if (C.cached[j]) {
-              const float r = d / C.dc[j];
-              const float r2 = r * r;
-              if (C.d_min <= r2 && r2 <= C.d_max) {
-                X = C.Xc[j];
-                vst = 1;
-              }
-            }
-            C.dcur[j] = d;
+  const int tile = (int)blockIdx.x;
+  const bool upper = tile < n_upper_tiles;  // block-uniform
+  uint32_t up = 0, vis = 0, c = 0;
+  int32_t high = 0, b = 0;
+  float X = 0.0f;
+  const int64_t j = upper ? (int64_t)tile * kCutTile + t : (int64_t)(tile - n_upper_tiles) * kCutTile + t;
+  if (upper) {
+    const bool p = j < S.n_upper && utest[j] == 2u && reached(S, utest, j, total, S.upper_parent[j]);
+    if (j < S.n_upper) upper_sel[j] = p ? 1 : 0;
+    up = p ? 1u : 0u;
+  } else if (j < S.n_spt) {
+    const ViewConst v = *vp;
+    const bool cull = (flags & LODGS_CULL) != 0;
+    const bool conservative = (flags & LODGS_CONSERVATIVE) != 0 && S.spt_radius != nullptr;
+    uint8_t vst = 0;
+    b = S.spt_begin[j];
+    const int32_t m = S.spt_begin[j + 1] - b;
+    const float mx = S.means[3 * (int64_t)b], my = S.means[3 * (int64_t)b + 1], mz = S.means[3 * (int64_t)b + 2];
+    const float rho = S.rho[b];
+    if (reached(S, utest, S.n_upper + j, total, S.spt_parent[j]) && !(cull && sphere_culled(v, mx, my, mz, rho))) {
+      const float d = view_distance(v, mx, my, mz) * v.spt_scale;  // the LoD noise (1: none)
+      X = conservative ? fmaxf(0.0f, d - S.spt_radius[j]) * v.k : d * v.k;
+      if (C.cached) {  // the cache's ratio test (squared, FP32)
+        vst = 2;
+        if (C.cached[j]) {
+          const float r = d / C.dc[j];
+          const float r2 = r * r;
+          if (C.d_min <= r2 && r2 <= C.d_max) {
+            X = C.Xc[j];
+            vst = 1;
           }
-          high = count_above(S.r_max + b, m, X);
-          hsum += high;
-          ++vis;
         }
+        C.dcur[j] = d;
       }
-      if (C.cached) {
-        C.vstate[j] = vst;
-        C.spt_sel[j] = 0u;
-      }
-      spt_high[j] = high;
-      spt_X[j] = X;
+      high = count_above(S.r_max + b, m, X);
+      vis = 1;
+    }
+    if (C.cached) {
+      C.vstate[j] = vst;
+      C.spt_sel[j] = 0u;
+    }
+    spt_high[j] = high;
+    spt_X[j] = X;
+    c = (uint32_t)((high + kChunk - 1) / kChunk);
+  }
+  uint32_t tot;
+  const uint32_t at = block_exclusive_scan(c, wt, &tot);
+  uint32_t r[3] = {up, vis, (uint32_t)high};
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] += __shfl_xor(r[k], d, 64);
+  if (lane == 0)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w3[k][wv] = r[k];
+  if (t == 0 && tot) s_base = (uint32_t)atomicAdd(&ctr->n_chunks, (int)tot);
+  __syncthreads();
+  if (t == 0) {
+    uint32_t a[3] = {0u, 0u, 0u};
+    for (int w = 0; w < kBlock / 64; ++w)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) a[k] += w3[k][w];
+    selected[tile] = a[0];  // an SPT tile's count comes with its chunks
+    sums[tile] = make_uint4(a[0], a[1], a[2], 0u);
+    if (!upper) first[tile] = tot ? s_base : 0u;
+  }
+  if (tot) {
+    const uint32_t base = s_base + at;
+    for (uint32_t q = 0; q < c; ++q)
+      chunks[base + q] = make_int2(b + (int32_t)q * kChunk, (int32_t)j);
+  }
+}
+
+// A chunk's selected candidates: bit q of the result is set when this lane's
+// q-th one (node c.x + 64 q + lane) is.  The candidates are requested together.
+__device__ __forceinline__ uint32_t chunk_bits(const SceneDev& S, const int32_t* __restrict__ spt_high,
+                                               const float* __restrict__ spt_X, const int2& c) {
+  const int lane = threadIdx.x & 63;
+  const float X = spt_X[c.y];
+  const int32_t end = S.spt_begin[c.y] + spt_high[c.y];  // of the SPT's prefix
+  float rm[kChunk / 64];
+#pragma unroll
+  for (int q = 0; q < kChunk / 64; ++q) rm[q] = c.x + 64 * q + lane < end ? S.r_min[(int64_t)c.x + 64 * q + lane] : 0.0f;
+  uint32_t bits = 0u;
+#pragma unroll
+  for (int q = 0; q < kChunk / 64; ++q) bits |= c.x + 64 * q + lane < end && rm[q] <= X ? 1u << q : 0u;
+  return bits;
+}
+
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+  return x;
+}
+
+// The chunks' selected candidates, and their sums by tile (and, for the cut
+// cache, by SPT).  A workgroup takes a run of chunks, each wave a part of it,
+// and adds the run's sum over a tile with one atomic: one per chunk made the
+// few visible tiles' words the bound (54 us for a 12M-node street view).
+constexpr int kCountThreads = 1024, kCountWaves = kCountThreads / 64, kCountGrid = 256;
+
+__global__ void __launch_bounds__(kCountThreads) k_cut_count(SceneDev S, const FrameCounters* ctr,
+                                                             const int32_t* __restrict__ spt_high,
+                                                             const float* __restrict__ spt_X,
+                                                             const int2* __restrict__ chunks, int32_t n_upper_tiles,
+                                                             uint16_t* chunk_count, uint32_t* selected,
+                                                             uint32_t* spt_sel) {
+  __shared__ int32_t w_tile[kCountWaves];   // the wave's last tile (-1: none) ...
+  __shared__ uint32_t w_sum[kCountWaves];   // ... and what it has not yet added to it
+  const int n = ctr->n_chunks, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int per = (n + kCountGrid * kCountWaves - 1) / (kCountGrid * kCountWaves);  // chunks of a wave
+  const int c0 = ((int)blockIdx.x * kCountWaves + wv) * per, c1 = min(c0 + per, n);
+  if ((int)blockIdx.x * kCountWaves * per >= n) return;  // block-uniform
+  int32_t tile = -1;
+  uint32_t sum = 0;
+  for (int c = c0; c < c1; ++c) {  // wave-uniform
+    const int2 ch = chunks[c];
+    const uint32_t k = wave_total((uint32_t)__popc(chunk_bits(S, spt_high, spt_X, ch)));
+    const int32_t own = n_upper_tiles + ch.y / kCutTile;
+    if (own != tile && sum != 0u) {
+      if (lane == 0) atomicAdd(&selected[tile], sum);
+      sum = 0;
+    }
+    tile = own;
+    sum += k;
+    if (lane == 0) {
+      chunk_count[c] = (uint16_t)k;  // at most kChunk
+      if (spt_sel && k) atomicAdd(&spt_sel[ch.y], k);
     }
   }
-  // one pair of atomics per workgroup (same-address atomics serialise)
-  __shared__ int wsum[kBlock / 64][2];
-  for (int d = 32; d > 0; d >>= 1) {
-    vis += __shfl_xor(vis, d, 64);
-    hsum += __shfl_xor(hsum, d, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    wsum[threadIdx.x >> 6][0] = vis;
-    wsum[threadIdx.x >> 6][1] = hsum;
+  if (lane == 0) {
+    w_tile[wv] = tile;
+    w_sum[wv] = sum;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int a = 0, b = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
-      a += wsum[w][0];
-      b += wsum[w][1];
+  // the first wave of a tile adds the sums of all waves that ended in it
+  if (threadIdx.x < kCountWaves && w_tile[threadIdx.x] >= 0) {
+    const int32_t mine = w_tile[threadIdx.x];
+    uint32_t all = 0;
+    bool lead = true;
+    for (int w = 0; w < kCountWaves; ++w) {
+      if (w_tile[w] == mine) {
+        lead = lead && w >= (int)threadIdx.x;
+        all += w_sum[w];
+      }
     }
-    if (a) {
-      atomicAdd(&ctr->n_spt_visible, a);
-      atomicAdd(&ctr->sum_high, b);
-    }
+    if (lead && all) atomicAdd(&selected[mine], all);
   }
 }
 
-// Compaction by segments, one wave per segment: segments 0 .. n_up_chunks-1
-// are 64-node chunks of the upper hierarchy (predicate: selected), the rest
-// are chunks of at most kChunk candidates of the visible SPT prefixes
-// (predicate: r_min <= X_j); an SPT contributes ceil(high_j / kChunk)
-// chunks, located through the scan of those counts (which also writes the
-// SPT of every chunk).  Pass 1 counts each
-// segment with ballots, a scan turns the counts into output offsets, pass 2
-// writes each segment's selected nodes in order with ballot ranks.  Segments
-// follow the layout order, so the output is ascending.
-constexpr int32_t kChunk = 512;
-
-// The scan of the chunk counts stores each SPT's first chunk index and the
-// owner table: owner[t] = the SPT whose prefix holds candidate chunk t.
-struct StoreChunks {
-  uint32_t* ch_off;
-  uint32_t* owner;
-  __device__ void operator()(int64_t j, uint32_t first, uint32_t count) const {
-    ch_off[j] = first;
-    for (uint32_t t = 0; t < count; ++t) owner[first + t] = (uint32_t)j;
-  }
-};
-
-template <bool WRITE>
-__global__ void __launch_bounds__(kBlock) k_segments(SceneDev S, const uint8_t* upper_sel, const int32_t* spt_high,
-                                                     const float* spt_X, const uint32_t* ch_off,
-                                                     const uint32_t* owner, int32_t n_up_chunks,
-                                                     uint32_t* seg, int32_t* idx, int64_t capacity,
-                                                     FrameCounters* ctr, int32_t* d_count, uint32_t* spt_sel) {
-  const int lane = threadIdx.x & 63;
+// The first n_upper_tiles workgroups write their tile's selected upper nodes,
+// the others take the chunks, a wave each: a tile's place is the sum of the
+// counts of the tiles before it, a chunk's that of its tile and of the chunks
+// before it there.  The last workgroup publishes the totals.
+__global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t* __restrict__ upper_sel,
+                                                      int32_t n_upper_tiles, int32_t ntiles,
+                                                      const uint32_t* __restrict__ selected,
+                                                      const uint4* __restrict__ sums,
+                                                      const uint32_t* __restrict__ first,
+                                                      const int32_t* __restrict__ spt_high,
+                                                      const float* __restrict__ spt_X,
+                                                      const int2* __restrict__ chunks,
+                                                      const uint16_t* __restrict__ chunk_count, int32_t* idx,
+                                                      int64_t capacity, FrameCounters* ctr, int32_t* d_count) {
+  __shared__ uint32_t wt[kBlock / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const uint64_t lt = lanemask_lt();
-  const int64_t nseg = (int64_t)n_up_chunks + ctr->n_chunks;
-  const int64_t nw = (int64_t)gridDim.x * (kBlock / 64);
-  if (!WRITE && blockIdx.x == 0 && threadIdx.x == 0) ctr->seg_total = (int32_t)nseg;
-  uint32_t up_count = 0;
-  for (int64_t sg = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); sg < nseg; sg += nw) {
-    const uint32_t base = WRITE ? seg[sg] : 0u;
-    uint32_t c = 0;
-    if (sg < n_up_chunks) {
-      const int64_t u = sg * 64 + lane;
-      const bool p = u < S.n_upper && upper_sel[u] != 0;
-      const uint64_t b = __ballot(p);
-      if (WRITE && p) {
-        const uint32_t pos = base + (uint32_t)__popcll(b & lt);
-        if (pos < capacity) idx[pos] = (int32_t)u;
-      }
-      c = (uint32_t)__popcll(b);
-      up_count += c;
-    } else {
-      const uint32_t t = (uint32_t)(sg - n_up_chunks);
-      const int32_t j = (int32_t)owner[t];
-      const int32_t h = spt_high[j];
-      const int32_t e_begin = (int32_t)(t - ch_off[j]) * kChunk;
-      const int32_t e_end = min(h, e_begin + kChunk);
-      const float X = spt_X[j];
-      const int32_t b0 = S.spt_begin[j];
-      // the chunk's candidates (at most kChunk = 8 x 64) are requested together
-      static_assert(kChunk == 8 * 64, "eight wave-wide loads per chunk");
-      float rm[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int32_t e = e_begin + 64 * q + lane;
-        rm[q] = e < e_end ? S.r_min[b0 + e] : 0.0f;
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int32_t e = e_begin + 64 * q + lane;
-        const bool p = e < e_end && rm[q] <= X;
-        const uint64_t b = __ballot(p);
-        if (WRITE && p) {
-          const uint32_t pos = base + c + (uint32_t)__popcll(b & lt);
-          if (pos < capacity) idx[pos] = b0 + e;
-        }
-        c += (uint32_t)__popcll(b);
-      }
-      if (!WRITE && spt_sel && lane == 0 && c) atomicAdd(&spt_sel[j], c);
-    }
-    if (!WRITE && lane == 0) seg[sg] = c;
+  // selected nodes of the tiles [0, tile), the whole wave adding up
+  const auto before = [&](int tile) -> uint32_t {
+    uint32_t x = 0;
+#pragma unroll 4
+    for (int i = lane; i < tile; i += 64) x += selected[i];
+    return wave_total(x);
+  };
+  if ((int)blockIdx.x < n_upper_tiles) {  // block-uniform
+    const int tile = (int)blockIdx.x;
+    if (selected[tile] == 0u) return;
+    const int64_t u = (int64_t)tile * kCutTile + t;
+    const bool p = u < S.n_upper && upper_sel[u] != 0;
+    const uint32_t base = before(tile);
+    uint32_t tot;
+    const uint32_t pos = base + block_exclusive_scan(p ? 1u : 0u, wt, &tot);
+    if (p && pos < capacity) idx[pos] = (int32_t)u;
+    return;
   }
-  if (!WRITE) {  // one atomic per workgroup
-    __shared__ uint32_t wup[kBlock / 64];
-    if (lane == 0) wup[threadIdx.x >> 6] = up_count;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      uint32_t t = 0;
-      for (int w = 0; w < kBlock / 64; ++w) t += wup[w];
-      if (t) atomicAdd(&ctr->n_upper_selected, (int)t);
+  if (blockIdx.x == gridDim.x - 1) {  // block-uniform: the totals
+    if (wv == 0) {
+      const uint32_t n = before(ntiles);
+      uint32_t o[3] = {0u, 0u, 0u};
+      for (int i = lane; i < ntiles; i += 64) {
+        const uint4 x = sums[i];
+        o[0] += x.x;
+        o[1] += x.y;
+        o[2] += x.z;
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) o[k] = wave_total(o[k]);
+      if (lane == 0) {
+        ctr->n_selected = (int32_t)n;
+        ctr->n_upper_selected = (int32_t)o[0];
+        ctr->n_spt_visible = (int32_t)o[1];
+        ctr->sum_high = (int32_t)o[2];
+        *d_count = (int32_t)n;
+        if ((int64_t)n > capacity) ctr->status = LODGS_E_CAPACITY;
+      }
     }
-  } else if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int32_t n = ctr->n_selected;
-    *d_count = n;
-    if ((int64_t)n > capacity) ctr->status = LODGS_E_CAPACITY;
+    return;
+  }
+  const int n = ctr->n_chunks, nw = ((int)gridDim.x - n_upper_tiles - 1) * (kBlock / 64);
+  for (int c = ((int)blockIdx.x - n_upper_tiles) * (kBlock / 64) + wv; c < n; c += nw) {
+    if (chunk_count[c] == 0u) continue;  // wave-uniform
+    const int2 ch = chunks[c];
+    const int tile = n_upper_tiles + ch.y / kCutTile;
+    const uint32_t bits = chunk_bits(S, spt_high, spt_X, ch);
+    uint32_t x = 0;
+    for (int i = (int)first[tile] + lane; i < c; i += 64) x += chunk_count[i];
+    uint32_t pos0 = before(tile) + wave_total(x);
+#pragma unroll
+    for (int q = 0; q < kChunk / 64; ++q) {
+      const bool p = (bits >> q) & 1u;
+      const uint64_t m = __ballot(p);
+      const uint32_t pos = pos0 + (uint32_t)__popcll(m & lt);
+      if (p && pos < capacity) idx[pos] = ch.x + 64 * q + lane;
+      pos0 += (uint32_t)__popcll(m);
+    }
   }
 }
-
-struct LoadChunks {
-  const int32_t* high;
-  __device__ uint32_t operator()(int64_t j) const { return (uint32_t)((high[j] + kChunk - 1) / kChunk); }
-};
 
 }  // namespace
 
@@ -406,28 +496,19 @@ void launch_select(lodgs_frame* f, const ViewConst& v, uint32_t flags, int32_t* 
   if (cache) C = *cache;
   const SceneDev& S = f->scene->dev;
   stage_begin(f, LODGS_STAGE_SELECT, st);
-  launch_set_view(v, f->d_view_sel, f->ctr, kViewSelect, nullptr, 0, ViewClear{}, st);
-  const int64_t total = (int64_t)S.n_upper + S.n_spt;
-  int grid = (int)((total + kBlock - 1) / kBlock);
-  grid = grid < 1 ? 1 : (grid > 4096 ? 4096 : grid);
-  int ugrid = (int)((S.n_upper + kBlock - 1) / kBlock);
-  ugrid = ugrid < 1 ? 1 : (ugrid > 4096 ? 4096 : ugrid);
-  hipLaunchKernelGGL(k_upper_tests, dim3(ugrid), dim3(kBlock), 0, st, S, f->d_view_sel, flags, f->upper_test);
-  hipLaunchKernelGGL(k_cut_upper, dim3(grid), dim3(kBlock), 0, st, S, f->d_view_sel, flags, f->upper_test,
-                     f->upper_sel, f->spt_high, f->spt_X, f->ctr, C);
-  const int32_t n_up_chunks = (S.n_upper + 63) / 64;
-  // chunks per visible SPT prefix -> offsets, total -> n_chunks
-  scan_exclusive(LoadChunks{f->spt_high}, &f->ctr->spt_count, (int64_t)S.n_spt, f->block_sums,
-                 StoreChunks{f->spt_off, f->chunk_owner}, &f->ctr->n_chunks, st);
-  const int sgrid = 4096;
-  const int64_t seg_cap = (int64_t)n_up_chunks + S.n_spt + S.n_nodes / kChunk + 1;
-  hipLaunchKernelGGL(k_segments<false>, dim3(sgrid), dim3(kBlock), 0, st, S, f->upper_sel, f->spt_high, f->spt_X,
-                     f->spt_off, f->chunk_owner, n_up_chunks, f->seg, (int32_t*)nullptr, capacity, f->ctr, d_count,
-                     C.spt_sel);
-  scan_exclusive(LoadArray{f->seg}, &f->ctr->seg_total, seg_cap, f->block_sums, f->seg, &f->ctr->n_selected, st);
-  hipLaunchKernelGGL(k_segments<true>, dim3(sgrid), dim3(kBlock), 0, st, S, f->upper_sel, f->spt_high, f->spt_X,
-                     f->spt_off, f->chunk_owner, n_up_chunks, f->seg, d_idx, capacity, f->ctr, d_count,
-                     (uint32_t*)nullptr);
+  const int64_t g = ((int64_t)S.n_upper + kBlock - 1) / kBlock;
+  hipLaunchKernelGGL(k_select_begin, dim3((int)(g < 1 ? 1 : (g > 4096 ? 4096 : g))), dim3(kBlock), 0, st, v,
+                     f->d_view_sel, f->ctr, S, flags, f->upper_test);
+  const int32_t n_upper_tiles = (int32_t)upper_tiles(S);
+  const int32_t tiles = (int32_t)cut_tiles(S);
+  hipLaunchKernelGGL(k_cut_upper, dim3(tiles), dim3(kBlock), 0, st, S, f->d_view_sel, flags, f->upper_test,
+                     f->upper_sel, f->spt_high, f->spt_X, f->ctr, n_upper_tiles, f->cut_selected, f->cut_sums,
+                     f->cut_first, f->cut_chunks, C);
+  hipLaunchKernelGGL(k_cut_count, dim3(kCountGrid), dim3(kCountThreads), 0, st, S, f->ctr, f->spt_high, f->spt_X,
+                     f->cut_chunks, n_upper_tiles, f->chunk_count, f->cut_selected, C.spt_sel);
+  hipLaunchKernelGGL(k_cut_write, dim3(n_upper_tiles + kChunkGrid + 1), dim3(kBlock), 0, st, S, f->upper_sel,
+                     n_upper_tiles, tiles, f->cut_selected, f->cut_sums, f->cut_first, f->spt_high, f->spt_X,
+                     f->cut_chunks, f->chunk_count, d_idx, capacity, f->ctr, d_count);
   stage_end(f, st);
 }
 
@@ -574,7 +655,7 @@ void launch_select_full(lodgs_frame* f, const ViewConst& v, uint32_t flags, int3
   const bool bfs = (flags & LODGS_CUT_BFS) != 0;
   const int64_t n_words = cut_bit_words(S.n_nodes);
   stage_begin(f, LODGS_STAGE_SELECT, st);
-  launch_set_view(v, f->d_view_sel, f->ctr, kViewSelect, nullptr, 0, ViewClear{}, st);
+  launch_set_view(v, f->d_view_sel, f->ctr, kViewSelect, nullptr, 0, nullptr, st);
   int cgrid = (int)((n_words + kBlock - 1) / kBlock);
   cgrid = cgrid < 1 ? 1 : (cgrid > 2048 ? 2048 : cgrid);
   hipLaunchKernelGGL(k_cut_clear, dim3(cgrid), dim3(kBlock), 0, st, f->cut_bits, n_words,
