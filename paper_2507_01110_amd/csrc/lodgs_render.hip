@@ -993,10 +993,10 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
     if (__any(active) && nmax > 0) {  // wave-uniform
       // two register sets, each loaded one list entry ahead of its use
       const uint8_t* hl = hits[wv][g];
-      // (an entry is read unconditionally, within the row's 64 bytes, and
+      // (an entry is read unconditionally, within the row's NT bytes, and
       // replaced by 0 past the list's end, so every read is a plain LDS load)
       auto slot = [&](int t) -> int {
-        const int e = (int)hl[t & 63];
+        const int e = (int)hl[t & (NT - 1)];
         return t < n ? e : 0;
       };
       Splat sa = batch[slot(0)], sb;

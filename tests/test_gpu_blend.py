@@ -1,0 +1,58 @@
+"""The blend kernels against the oracle at the sizes where they change form:
+pixels with the path's 1e-4 bar, node gradients with its 1e-3 relative L2 per
+parameter group."""
+import numpy as np
+import pytest
+
+import oracle
+import scenegen
+from scenegen import configs
+
+pytestmark = pytest.mark.gpu
+
+GROUPS = {"means": slice(0, 3), "log_scales": slice(3, 6), "quats": slice(6, 10), "opacity_logits": slice(10, 11),
+          "sh": slice(11, None)}
+
+
+@pytest.fixture(scope="module")
+def scene():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2507_01110_amd.lodgs import Scene
+    tree = scenegen.build_tree(configs.tiny_spec(n=20000, seed=11, sh_degree=1))
+    return tree, Scene(tree)
+
+
+def check(tree, S, n, width, height, distance=300.0):
+    """Render and backward of n nodes spread over the layout."""
+    import torch
+    from paper_2507_01110_amd.lodgs import Frame, grads_like
+    cam = scenegen.camera_look_at((0.0, 0.0, distance), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), width, height)
+    positions = np.arange(n) * (S.n_nodes // n)
+    print("blend", n, width, height, distance, flush=True)
+    f = Frame(S, n, 1 << 20, width, height)
+    F = oracle.OracleFrame(tree, S.perm[positions].astype(np.int32), cam)
+    dL = np.random.default_rng(n).standard_normal((height, width, 3)).astype(np.float32)
+    _, g_o = F.backward(dL.astype(np.float64))
+    idx = torch.from_numpy(np.ascontiguousarray(positions, np.int32)).cuda()
+    cnt = torch.tensor([n], dtype=torch.int32, device="cuda")
+    sel = grads_like(S, n, zero=False)
+    for _ in range(2):  # the second pass starts from the first one's state
+        img = f.render(cam, idx=idx, count=cnt)
+        assert f.stats()["status"] == 0
+        assert float(np.abs(img.cpu().numpy().astype(np.float64) - F.image).max()) <= 1e-4
+        f.backward(torch.from_numpy(dL).cuda(), sel=sel)
+        got = np.concatenate([sel[k].reshape(n, -1).cpu().numpy().astype(np.float64) for k in GROUPS], axis=1)
+        for k, s in GROUPS.items():
+            err = np.linalg.norm(got[:, s] - g_o[:, s])
+            assert err <= 1e-3 * max(np.linalg.norm(g_o[:, s]), 1e-12), (k, err)
+
+
+@pytest.mark.parametrize("px", [1, 2, 4])
+@pytest.mark.parametrize("n", [60, 130, 300])
+def test_pixels_per_lane(scene, monkeypatch, px, n):
+    # rows that replay more than 64 of a batch's instances
+    monkeypatch.setenv("LODGS_BLEND_PX_FWD", str(px))
+    monkeypatch.setenv("LODGS_BLEND_PX_BWD", str(px))
+    check(*scene, n, 16, 16)
