@@ -194,7 +194,7 @@ def summarize_profiles(trace_csv, fetch_csv, write_csv, commands, dispatch_csv=N
         d = collections.defaultdict(list)
         for r in csv.DictReader(open(dispatch_csv)):
             k = short(r["Kernel_Name"]).replace("void ", "").replace(" ", "")
-            if k.startswith(("k_blend_bwd", "k_blend_q")):
+            if k.startswith(("k_blend_bwd", "k_blend_fwd")):
                 d[k].append((int(r["Start_Timestamp"]), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3))
         out.append("blend kernels per dispatch (us): stage pass = the last %d dispatches (one view at a time), "
                    "timed loop = the %d before them" % (stage_views, stage_views))
@@ -206,14 +206,14 @@ def summarize_profiles(trace_csv, fetch_csv, write_csv, commands, dispatch_csv=N
                            (k, sum(sp) / len(sp), sum(tl) / len(tl)))
         out.append("")
     h = kernel_source_hash()
-    for stage, pats in (("blend_bwd", ("k_blend_bwd",)), ("blend", ("k_blend_q", "k_blend<false"))):
+    for stage, pats in (("blend_bwd", ("k_blend_bwd",)), ("blend", ("k_blend_fwd", "k_blend<false"))):
         ks = [k for k in hbm if k.replace("void ", "").startswith(pats)]
         if ks:
             out.append("TRAFFIC %s %s %d %s" % (stage, ks[0].replace("void ", "").replace(" ", ""), round(hbm[ks[0]]), h))
     return "\n".join(out)
 
 
-def summarize_counters(csvs, commands, trace_stats=None, kernels=("k_blend_q", "k_blend_bwd")):
+def summarize_counters(csvs, commands, trace_stats=None, kernels=("k_blend_fwd", "k_blend_bwd")):
     """Text summary of rocprofv3 --pmc runs (SQ counters): per kernel whose
     name starts with one of `kernels`, the sum of each counter over its
     dispatches, and the derived shares (active / wait / VALU / LDS per wave
@@ -274,7 +274,7 @@ def summarize_counters(csvs, commands, trace_stats=None, kernels=("k_blend_q", "
             ex["lds_conflict_share"] = c["SQ_LDS_BANK_CONFLICT"] / c["SQ_LDS_IDX_ACTIVE"]
         out.append("  derived: " + "; ".join(d))
         out.append("")
-        stage = "blend_bwd" if k.startswith("k_blend_bwd") else ("blend" if k.startswith("k_blend_q") else None)
+        stage = "blend_bwd" if k.startswith("k_blend_bwd") else ("blend" if k.startswith("k_blend_fwd") else None)
         if stage and ex:
             executed.append("EXECUTED %s %s %s %s" % (stage, k.replace(" ", ""),
                                                       " ".join("%s=%.6g" % kv for kv in sorted(ex.items())),

@@ -56,6 +56,12 @@ __device__ __forceinline__ float row_reduce_scatter(const float* g, int lane, in
 #undef LODGS_RS_PAIR
 #undef LODGS_DPP
 
+// A wave-uniform 64-bit value, moved to scalar registers.
+__device__ __forceinline__ uint64_t uniform64(uint64_t x) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
+}
+
 // Backward of the blend: the forward's decisions, pixel layout blend_pixel<PX, true>
 // (each wave's rows spread over the block rows and columns).
 // Each 16-lane row replays only the splats whose forward event bits cover one
@@ -104,16 +110,15 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
   };
   __shared__ BatchRec batch[NB];
   __shared__ uint32_t bid[NB];
-  __shared__ uint32_t ev[NB];
+  __shared__ unsigned long long emask[NB / 64][16];      // the batch's event masks by block
+  __shared__ unsigned long long wave_ev[NW][NB / 64];    // and over each wave's blocks
   __shared__ uint8_t hits[NW][4][NB];  // per row of each wave: the batch slots it replays, in order
   // a row of acc per partial component; slot j's component c sits at column
   // j ^ c, so the ten lanes of a row adding one slot's components hit ten
   // banks (the rows are 128 words apart)
   __shared__ float acc[NW][NP][NB];
   __shared__ uint32_t wave_active[NW];  // per wave: some pixel still blends
-  const uint32_t place = tile_order[blockIdx.x];
-  if (place == kNoTile) return;  // block-uniform
-  const int tile = (int)place;
+  const int tile = (int)tile_order[blockIdx.x];
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, row = lane >> 4;
   int px = 0;
@@ -150,33 +155,56 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
   const float thr = 1.0f / 255.0f;
   for (int t = threadIdx.x; t < NW * NP * NB; t += NT) (&acc[0][0][0])[t] = 0.0f;
   // The last NB threads load: thread NT - NB + j holds batch slot j, the
-  // words (emission index, splat, event word) of this batch and the next, and
-  // the splat record of this batch (only for an instance with events: the
-  // others are never replayed), so the loads overlap the replay of the batch
-  // before.  The first threads write the partials out after a replay, so with
+  // words (emission index, splat, whether the instance has an event) of this
+  // batch and the next, and the splat record of this batch (only for an
+  // instance with events: the others are never replayed), so the loads overlap
+  // the replay of the batch before.  The first threads write the partials out after a replay, so with
   // four waves the staging of the next batch and the write-out of the last
   // run on different waves.
   const int ld = (int)threadIdx.x - (NT - NB);  // the loaded slot (loaders only)
   const bool loader = ld >= 0;
-  auto words = [&](uint32_t b, uint32_t& e, uint32_t& i, uint32_t& w) {
+  const unsigned long long* const ev64 = event_masks(event, rg.x, tile);
+  const uint32_t nbt = (rg.y - rg.x + 63) / 64;
+  // e, i of the loaded slot, and lane l % 16's event mask of the 64 slots that
+  // this wave loads (block l % 16's)
+  auto words = [&](uint32_t b, uint32_t& e, uint32_t& i, unsigned long long& mk) {
     const uint32_t k = b + (uint32_t)ld;
-    e = i = w = 0u;
-    if (loader && k < rg.y) {
+    e = i = 0u;
+    mk = 0ull;
+    if (!loader) return;
+    if (k < rg.y) {
       e = ival[k];
       i = info_k[k].x;
-      w = event[k];
     }
+    const uint32_t eb = (b - rg.x) / 64 + (uint32_t)(ld >> 6);  // wave-uniform
+    if (eb < nbt) mk = ev64[16 * eb + (lane & 15)];
   };
-  auto record = [&](uint32_t i, uint32_t w, float4& a, float4& b, float4& c) {
+  // whether the loaded slot has an event in any block
+  auto any_event = [&](unsigned long long mk) -> bool {
+    uint32_t lo = (uint32_t)mk, hi = (uint32_t)(mk >> 32);
+#define LODGS_OR16(x, ctrl) x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xf, 0xf, false)
+    LODGS_OR16(lo, 0xB1);   // quad_perm [1,0,3,2]
+    LODGS_OR16(hi, 0xB1);
+    LODGS_OR16(lo, 0x4E);   // quad_perm [2,3,0,1]
+    LODGS_OR16(hi, 0x4E);
+    LODGS_OR16(lo, 0x141);  // row_half_mirror
+    LODGS_OR16(hi, 0x141);
+    LODGS_OR16(lo, 0x140);  // row_mirror
+    LODGS_OR16(hi, 0x140);
+#undef LODGS_OR16
+    return (((lane < 32 ? lo : hi) >> (lane & 31)) & 1u) != 0u;
+  };
+  auto record = [&](uint32_t i, unsigned long long mk, float4& a, float4& b, float4& c) {
     a = b = c = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (w != 0u && i < nr) {  // i >= nr only follows an instance overflow (no events)
+    if (loader && any_event(mk) && i < nr) {  // i >= nr only follows an instance overflow (no events)
       const float4* r = reinterpret_cast<const float4*>(splats + i);
       a = r[0];
       b = r[1];
       c = r[2];
     }
   };
-  uint32_t e0, i0, w0, e1, i1, w1;
+  uint32_t e0, i0, e1, i1;
+  unsigned long long w0, w1;
   words(rg.x, e0, i0, w0);
   words(rg.x + NB, e1, i1, w1);
   float4 ra, rb, rc;
@@ -192,7 +220,7 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
     if (lane == 0) wave_active[wv] = wave_act ? 1u : 0u;
     if (loader) {
       bid[ld] = e0;
-      ev[ld] = event_blocks(w0);
+      if (lane < 16) emask[ld >> 6][lane] = w0;
       float4* dst = reinterpret_cast<float4*>(&batch[ld]);  // mean, axis, power, opacity, colour
       dst[0] = ra;
       dst[1] = rb;
@@ -203,37 +231,39 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
 #pragma unroll
     for (int w = 0; w < NW; ++w) block_act |= wave_active[w];
     if (block_act == 0u) break;  // every pixel of the tile has stopped (the same flags for all threads)
-    // the words of the slot this thread writes out after the replay, read
+    // the emission index this thread writes out to after the replay, read
     // now: a loader may stage the next batch while the write-out runs
-    const uint32_t out_bid = bid[threadIdx.x % NB], out_ev = ev[threadIdx.x % NB];
+    const uint32_t out_bid = bid[threadIdx.x % NB];
     record(i1, w1, ra, rb, rc);
-    uint32_t e2, i2, w2;
+    uint32_t e2, i2;
+    unsigned long long w2;
     words(b0 + 2 * NB, e2, i2, w2);
     const int m = (int)min((uint32_t)NB, rg.y - b0);
-    // every row's list of the batch slots whose events meet its blocks, in
-    // slot order (ballot ranks); each lane reads its slots' event words once
-    // for the four rows
-    static_assert(NB % 64 == 0, "whole waves of batch slots");
-    uint32_t evw[NB / 64];
-#pragma unroll
-    for (int c = 0; c < NB / 64; ++c) {
-      const int j = c * 64 + lane;
-      evw[c] = j < m ? ev[j] : 0u;
-    }
+    // every row's list of the batch slots with an event in one of its blocks,
+    // in slot order (ranks in the masks)
     const uint64_t lt = lanemask_lt();
     int nh[4];
+    uint64_t wave_any[NB / 64];
+#pragma unroll
+    for (int c = 0; c < NB / 64; ++c) wave_any[c] = 0ull;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const uint32_t want = blend_row_blocks<PX, true>(wv, r);
       int cnt = 0;
 #pragma unroll
       for (int c = 0; c < NB / 64; ++c) {
-        const bool h = (evw[c] & want) != 0u;
-        const uint64_t hb = __ballot(h);
-        if (h) hits[wv][r][cnt + __popcll(hb & lt)] = (uint8_t)(c * 64 + lane);
+        uint64_t hb = 0ull;
+#pragma unroll
+        for (int p = 0; p < PX; ++p) hb |= emask[c][31 - __builtin_clz(blend_pixel_block<PX, true>(wv, r, p))];
+        hb = uniform64(hb);
+        if ((hb >> lane) & 1ull) hits[wv][r][cnt + __popcll(hb & lt)] = (uint8_t)(c * 64 + lane);
         cnt += __popcll(hb);
+        wave_any[c] |= hb;
       }
       nh[r] = cnt;
+    }
+    if (lane == 0) {
+#pragma unroll
+      for (int c = 0; c < NB / 64; ++c) wave_ev[wv][c] = wave_any[c];
     }
     // the hit lists are the wave's own (its LDS operations run in order): a
     // wave-level fence and barrier order their writes before the reads
@@ -373,16 +403,12 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
       // value is never -0: rows start at +0 and x + y is -0 only when both
       // are), and an instance without events is written as zeros.
       float* dst = partial + NP * (int64_t)out_bid;
-      const uint32_t evb = out_ev;
       float r[NP];
 #pragma unroll
       for (int c = 0; c < NP; ++c) r[c] = 0.0f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
-        uint32_t wb = 0u;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) wb |= blend_row_blocks<PX, true>(w, g);
-        if ((evb & wb) == 0u) continue;
+        if (((wave_ev[w][threadIdx.x >> 6] >> lane) & 1ull) == 0ull) continue;
 #pragma unroll
         for (int c = 0; c < NP; ++c) {
           const int col = (int)threadIdx.x ^ c;
@@ -820,7 +846,7 @@ static void launch_scatter_deg(const SceneDev& S, lodgs_frame* f, const lodgs_gr
 template <int NP>
 static void launch_blend_bwd_np(lodgs_frame* f, const float* d_dL, hipStream_t st) {
   const ViewConst& v = f->view;
-  const int ntiles = tile_places(v.tiles_x * v.tiles_y);
+  const int ntiles = v.tiles_x * v.tiles_y;
   switch (f->blend_px_bwd) {
     case 1:
       hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,

@@ -335,15 +335,6 @@ __device__ __forceinline__ uint32_t blend_pixel_block(int wv, int g, int p) {
   return block_bit(bx, by);
 }
 
-// Forward events of one instance: byte q holds the (4-bit) events of quarter
-// q, written by that quarter's wave; as a 16-bit block mask and back.
-__device__ __forceinline__ uint32_t event_blocks(uint32_t w) {
-  return (w & 0xFu) | ((w >> 4) & 0xF0u) | ((w >> 8) & 0xF00u) | ((w >> 12) & 0xF000u);
-}
-__device__ __forceinline__ uint32_t event_word(uint32_t m) {
-  return (m & 0xFu) | ((m & 0xF0u) << 4) | ((m & 0xF00u) << 8) | ((m & 0xF000u) << 12);
-}
-
 // The blocks that row g of wave w covers.
 template <int PX, bool SPREAD = false>
 __device__ __forceinline__ uint32_t blend_row_blocks(int wv, int g) {

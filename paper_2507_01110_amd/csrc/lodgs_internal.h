@@ -89,7 +89,6 @@ struct lodgs_scene {
 
 namespace lodgs {
 constexpr int32_t kMaxAncDepth = 64;
-constexpr int kTileClasses = 128;  // blend tile-order classes (quarter octaves of the instance count)
 // Builds the ancestor table (synchronous; scene creation only).
 int build_ancestor_table(lodgs_scene* s);
 int build_spt_radius(lodgs_scene* s);
@@ -112,7 +111,8 @@ struct FrameCounters {
   int32_t spt_count;     // constant n_spt
   int32_t n_long;        // drawn splats with more than kLongSegment instances
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
-  int32_t pad;
+  int32_t n_heavy;       // tiles of at least kHeavyTile instances: the first of the tile order
+  int32_t n_mid;         // tiles of at least 64 instances: likewise
 };
 
 struct lodgs_frame {
@@ -153,17 +153,16 @@ struct lodgs_frame {
   uint32_t* ival;         // [max_instances] emission index of each instance, in (tile, depth) order
   uint2* info_k;          // [max_instances] the instances' words in that order
   float* inst_grad;       // [max_instances][kPartial] per-instance partials (emission order)
-  uint32_t* inst_event;   // [max_instances] forward events, byte q for quarter q's 4x4 blocks (tile order)
+  uint32_t* inst_event;   // [event_words] forward events: per tile, batch of 64 instances and 4x4 block a 64-bit mask
   double* grad2d;         // [max_selected][9] per-drawn-splat 2D sums (by rank among the drawn ones)
   float* dcol;            // [max_selected][kColorRec] colour backward record of each drawn splat (selection
                           // position): d colour / d view direction (9), unit view direction (3), 1 / distance,
                           // clamp bits, 2 unused
   uint32_t* long_list;    // [max_selected] ranks (among the drawn ones) of the splats with many instances
   uint2* ranges;          // [max tiles]
-  uint32_t* tile_order;   // [tile_places(max tiles)] tiles, heaviest of each chunk first, chunks interleaved
+  uint32_t* tile_order;   // [max tiles] tiles, heaviest class first
   uint32_t* tile_count;   // [max tiles] instances of each tile
   uint32_t* tile_cursor;  // [max tiles] next place in each tile's range
-  uint32_t* tile_mid;     // [chunks of the tile order] tiles of more than 64 instances
   uint2* big_list;        // [max_instances / kSortChunkHalf + 1] (tile, chunk) of the tiles sorted in chunks
   float spt_scale;        // LoD noise factor on the distances to SPT roots (lodgs_frame_set_lod_noise)
   lodgs::ViewConst* d_view_sel;  // view constants of the last lod_select (device)
@@ -242,21 +241,30 @@ inline int64_t cut_tiles(const SceneDev& S) { return upper_tiles(S) + ((int64_t)
 inline int64_t cut_chunks(const SceneDev& S) { return (int64_t)S.n_spt + S.n_nodes / 512 + 1; }
 
 // The tile order's chunks (k_tile_scan): as many as keep a chunk to
-// kOrderChunk tiles, of equal size but for the last; the order has a place for
-// every tile of whole chunks (kNoTile where the last is shorter).
+// kOrderChunk tiles, of equal size but for the last.
 constexpr int32_t kOrderChunk = 2048;
-constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 __host__ __device__ inline int32_t tile_chunks(int32_t ntiles) { return (ntiles + kOrderChunk - 1) / kOrderChunk; }
 __host__ __device__ inline int32_t tile_chunk(int32_t ntiles) {
   const int32_t c = tile_chunks(ntiles);
   return (ntiles + c - 1) / c;
 }
-// Place of the l-th tile of chunk b of c: the chunks take turns, starting with
-// another one each time, so that a chunk of heavy tiles does not always fall
-// to the same XCDs (workgroups go to the XCDs in turn: with a fixed order the
-// heavy chunk of a 4K view kept half of them busy, 513 against 313 us).
-__host__ __device__ inline uint32_t order_place(uint32_t l, uint32_t b, uint32_t c) { return c * l + (b + l) % c; }
-inline int32_t tile_places(int32_t ntiles) { return tile_chunks(ntiles) * tile_chunk(ntiles); }
+
+// Tiles of at least this many instances are blended by a wave per 4x4 block.
+constexpr int kHeavyBits = 9;  // bit length of kHeavyTile
+constexpr int kHeavyTile = 1 << (kHeavyBits - 1);
+
+// Forward events: per tile, for each batch of 64 of its instances (in order)
+// and each 4x4 block (the bits of block_bit), the mask of the batch's
+// instances that blended or stopped at a pixel of the block.  The tile whose
+// range starts at `begin` has its masks from word begin + 64 tile on (rounded up to a
+// mask): 32 words for every 64 instances or part of them.
+__host__ __device__ inline size_t event_words(size_t instances, size_t tiles) { return instances + 64 * tiles + 2; }
+__device__ __forceinline__ unsigned long long* event_masks(uint32_t* event, uint32_t begin, int tile) {
+  return reinterpret_cast<unsigned long long*>(event) + (((int64_t)begin + 64 * (int64_t)tile + 1) >> 1);
+}
+__device__ __forceinline__ const unsigned long long* event_masks(const uint32_t* event, uint32_t begin, int tile) {
+  return reinterpret_cast<const unsigned long long*>(event) + (((int64_t)begin + 64 * (int64_t)tile + 1) >> 1);
+}
 
 // Half the instances of a sort chunk: a tile sorted in chunks holds more than
 // one chunk, so it lists at most one chunk per this many instances.
@@ -360,16 +368,15 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->ival, ni);
   fn(f->info_k, ni);
   fn(f->inst_grad, (size_t)kPartial * ni);
-  fn(f->inst_event, ni);
+  fn(f->inst_event, event_words(ni, nt));
   fn(f->grad2d, 9 * ns);
   fn(f->contrib, ns);
   fn(f->dcol, (size_t)kColorRec * ns);
   fn(f->long_list, ns);
   fn(f->ranges, nt);
-  fn(f->tile_order, nt + (size_t)tile_chunks((int32_t)nt));
+  fn(f->tile_order, nt);
   fn(f->tile_count, nt);
   fn(f->tile_cursor, nt);
-  fn(f->tile_mid, (size_t)tile_chunks((int32_t)nt));
   fn(f->big_list, ni / kSortChunkHalf + 1);
   fn(f->work, 2);
   fn(f->d_view_sel, 1);

@@ -467,41 +467,58 @@ __global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const u
 // From the tiles' instance counts: the exclusive scan gives every tile its
 // range of the instance list (and the cursor k_bucket fills it from), the
 // chunks of tiles with more than kSortSmall instances are listed, and the
-// tiles are put in the blend kernels' workgroup order: by descending class of
+// tiles are put in the blend kernels' workgroup order, by descending class of
 // the count n (its bit length and the two bits below its leading one, so
 // classes are a quarter octave wide), so the longest workgroups start early;
-// results do not depend on the order of the tiles.  Each of the C workgroups
-// takes one chunk of tile_chunk(ntiles) <= kOrderChunk tiles and sums the
-// counts before it (one workgroup for 8160 tiles was bound by its own
-// instructions: 10.6 us, four take 6): each tile takes its rank within its
-// class from an LDS counter, and a scan over the classes gives each class its
-// start (mid[b] is where the classes of less than 64 instances begin).  The
-// chunks' orders are interleaved (order_place: kNoTile past a shorter chunk's
-// end), so every chunk's longest come first.
-// The order within a class is whatever the LDS atomics give.  The lanes of a wave
-// whose tiles share the first lane's class (empty tiles, mostly) count with
-// one atomic: same-address LDS atomics run one after another.
+// results do not depend on the order of the tiles.
+// Each of the C workgroups takes one chunk of at most kOrderChunk tiles (one
+// workgroup for 8160 tiles was bound by its own instructions: 10.6 us) and
+// reads the counts of all others too: their sum before it, and how many tiles
+// of each class lie before and after it (kept by lane, so that no two lanes of
+// an LDS operation meet).  An order of each chunk by itself, interleaved,
+// was shorter to make (6 against 8 us), but where one part of the image is
+// heavier its tiles started late: 132 against 101 us for the blend backward of
+// an aerial 1080p view.  Within its chunk a tile takes its rank in its class
+// from an LDS counter; the order within a chunk and class is whatever the LDS
+// atomics give.  The lanes of a wave whose tiles share the first lane's class
+// (empty tiles, mostly) count with one atomic: same-address LDS atomics run
+// one after another.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderBatch = 2;  // consecutive tiles per thread
 static_assert(kOrderChunk == kOrderThreads * kOrderBatch, "two tiles per thread");
-static_assert(kTileClasses == 128, "one thread per class in waves 0 and 1");
 
+constexpr int kTileClasses = 128;
 __device__ __forceinline__ int tile_class(uint32_t n) {
   const int bl = min(31, 32 - __clz((int)n));  // 0 for an empty tile
   const int sub = bl >= 3 ? (int)((n >> (bl - 3)) & 3u) : 0;
   return bl * 4 + sub;  // < kTileClasses
+}
+constexpr int kHeavyClass = 4 * kHeavyBits;  // class of kHeavyTile instances
+constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
+constexpr int kClassLanes = 32;  // copies of a class's counter
+
+// The sum of x over the wave's lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_add(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);   // quad_perm [1,0,3,2]
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false);   // quad_perm [2,3,0,1]
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false);  // row_half_mirror
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xf, 0xf, false);  // row_mirror
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = a[0] + a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return b[0] + b[1];
 }
 
 // Instances that a workgroup of k_tile_sort sorts; a tile with more is sorted
 // in chunks of that many, which k_tile_merge puts together.
 constexpr int kSortSmall = 2048;
 static_assert(kSortSmall == 2 * kSortChunkHalf, "the chunk list's length");
-constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
 
 __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __restrict__ count, int32_t ntiles,
                                                              FrameCounters* ctr, uint2* ranges, uint32_t* cursor,
-                                                             uint32_t* order, uint32_t* mid, uint2* big_list) {
-  __shared__ uint32_t cnt[kTileClasses];
+                                                             uint32_t* order, uint2* big_list) {
+  __shared__ uint32_t cnt[kTileClasses], pre[kTileClasses], post[kTileClasses];
+  __shared__ uint32_t others[kTileClasses][kClassLanes];  // the other chunks' tiles: low half before, high half after
   __shared__ uint32_t half[2];
   __shared__ uint32_t wt[kOrderThreads / 64], wb[kOrderThreads / 64];
   __shared__ uint32_t big, big_base;  // this chunk's large tiles' sort chunks
@@ -512,10 +529,36 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   uint32_t m[kOrderBatch], sum = 0, before = 0;
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) m[k] = k0 + k < n ? count[lo + k0 + k] : 0u;
-#pragma unroll 4
-  for (int32_t i = t; i < lo; i += kOrderThreads) before += count[i];
-  if (t < kTileClasses) cnt[t] = 0;
+  if (t < kTileClasses) cnt[t] = pre[t] = post[t] = 0;
   if (t == 0) big = 0;
+  if (gridDim.x > 1) {  // block-uniform
+    static_assert(kTileClasses * kClassLanes == 4 * kOrderThreads, "one 16-byte store per thread");
+    reinterpret_cast<uint4*>(&others[0][0])[t] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    // (a counter's half stays below 2^16: an image has at most 2^20 tiles, and
+    // a counter takes a 32nd of them)
+#pragma unroll 8
+    for (int32_t i = t; i < ntiles - n; i += kOrderThreads) {
+      const bool first = i < lo;
+      const uint32_t x = count[first ? i : i + n];
+      before += first ? x : 0u;
+      atomicAdd(&others[tile_class(x)][lane & (kClassLanes - 1)], first ? 1u : 0x10000u);
+    }
+    before = wave_add(before);
+    __syncthreads();
+    const uint4 q = reinterpret_cast<const uint4*>(&others[0][0])[t];  // a class: eight threads
+    uint32_t p = (q.x & 0xFFFFu) + (q.y & 0xFFFFu) + (q.z & 0xFFFFu) + (q.w & 0xFFFFu);
+    uint32_t r = (q.x >> 16) + (q.y >> 16) + (q.z >> 16) + (q.w >> 16);
+#pragma unroll
+    for (int d = 1; d < 8; d <<= 1) {
+      p += __shfl_xor(p, d, 64);
+      r += __shfl_xor(r, d, 64);
+    }
+    if ((t & 7) == 0) {
+      pre[t >> 3] = p;
+      post[t >> 3] = r;
+    }
+  }
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) sum += m[k];
   uint32_t x = sum;
@@ -523,7 +566,6 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t y = __shfl_up(x, d, 64);
     if (lane >= d) x += y;
-    before += __shfl_xor(before, d, 64);
   }
   if (lane == 63) {
     wt[wv] = x;
@@ -533,7 +575,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   uint32_t start = x - sum;
 #pragma unroll
   for (int w = 0; w < kOrderThreads / 64; ++w) start += wb[w] + (w < wv ? wt[w] : 0u);
-  uint32_t key[kOrderBatch];  // class << 16 | rank within the class (rank < kOrderChunk)
+  uint32_t key[kOrderBatch];  // class << 16 | rank within the chunk's class (rank < kOrderChunk)
   uint32_t big_at[kOrderBatch];
   const uint64_t lt = lanemask_lt();
 #pragma unroll
@@ -557,11 +599,13 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   }
   __syncthreads();
   if (t == kOrderThreads - 1 && big != 0u) big_base = (uint32_t)atomicAdd(&ctr->n_big, (int)big);
-  // cnt[c] becomes the tiles of all classes above c (waves 0 and 1, whole waves)
+  // pre[c] becomes the place of the chunk's first tile of class c: all tiles of
+  // the classes above c and the ones of class c before the chunk (waves 0 and
+  // 1, whole waves)
   const int c = t;
   uint32_t incl = 0;
   if (c < kTileClasses) {
-    incl = cnt[c];
+    incl = cnt[c] + pre[c] + post[c];
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const uint32_t y = __shfl_up(incl, d, 64);
@@ -570,19 +614,21 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
     if (lane == 63) half[wv] = incl;
   }
   __syncthreads();
-  if (c < kTileClasses) cnt[c] = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
+  if (c < kTileClasses) {
+    const uint32_t above = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
+    pre[c] += above;
+    if (blockIdx.x == 0 && c == kHeavyClass - 1) ctr->n_heavy = (int32_t)above;
+    // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
+    if (blockIdx.x == 0 && c == kWaveClass - 1) ctr->n_mid = (int32_t)above;
+  }
   __syncthreads();
-  // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
-  if (t == 0) mid[blockIdx.x] = cnt[kWaveClass - 1];
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k)
     if (k0 + k < n) {
-      order[order_place(cnt[key[k] >> 16] + (key[k] & 0xFFFFu), blockIdx.x, gridDim.x)] = (uint32_t)(lo + k0 + k);
+      order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = (uint32_t)(lo + k0 + k);
       if (m[k] > (uint32_t)kSortSmall)
         for (uint32_t q = 0; q * kSortSmall < m[k]; ++q)
           big_list[big_base + big_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
-    } else if (k0 + k < per) {
-      order[order_place((uint32_t)(k0 + k), blockIdx.x, gridDim.x)] = kNoTile;
     }
 }
 
@@ -768,8 +814,7 @@ constexpr int kTileSortGrid = 1792;  // seven workgroups per CU: what the regist
 
 __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters* ctr, const uint2* __restrict__ ranges,
                                                              const uint32_t* __restrict__ tile_order,
-                                                             const uint32_t* __restrict__ mid, int32_t ntiles,
-                                                             const uint2* __restrict__ big_list,
+                                                             int32_t ntiles, const uint2* __restrict__ big_list,
                                                              unsigned long long* bkey,
                                                              const uint2* __restrict__ inst_info,
                                                              uint2* __restrict__ info_k, uint32_t* __restrict__ ival) {
@@ -785,43 +830,38 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters
     for (int j = t; j < m; j += kSmallThreads) bkey[x + j] = keys[j];
     __syncthreads();
   }
-  // the chunks of the tile order, one after the other; the first items go to
-  // the workgroups after those that took the last ones
-  const int32_t per = tile_chunk(ntiles), nch = tile_chunks(ntiles);
-  int32_t used = nb % (int32_t)gridDim.x;
-  for (int32_t ch = 0; ch < nch; ++ch) {
-    const int32_t n = min(per, ntiles - ch * per), nm = (int32_t)mid[ch];
-    const int32_t items = nm + (n - nm + 3) / 4;
-    int32_t it = (int32_t)blockIdx.x - used;
-    if (it < 0) it += (int32_t)gridDim.x;
-    used = (used + items) % (int32_t)gridDim.x;
-    for (; it < items; it += (int32_t)gridDim.x) {  // block-uniform
-      if (it >= nm) {  // four tiles of less than 64 instances
-        const int32_t at = nm + 4 * (it - nm) + (t >> 6);
-        if (at < n) {  // wave-uniform
-          const uint2 rg = ranges[tile_order[order_place((uint32_t)at, (uint32_t)ch, (uint32_t)nch)]];
-          const int m = (int)(rg.y - rg.x);
-          if (m > 0) {
-            const uint32_t k = (uint32_t)wave_sort(lane < m ? bkey[rg.x + lane] : ~0ull);
-            if (lane < m) {
-              ival[rg.x + lane] = k;
-              info_k[rg.x + lane] = inst_info[k];
-            }
+  // the tile order: a workgroup for each tile of more than 64 instances, then
+  // a wave for each other one; the first items go to the workgroups after
+  // those that took the last chunks
+  const int32_t nm = ctr->n_mid, items = nm + (ntiles - nm + 3) / 4;
+  int32_t it = (int32_t)blockIdx.x - nb % (int32_t)gridDim.x;
+  if (it < 0) it += (int32_t)gridDim.x;
+  for (; it < items; it += (int32_t)gridDim.x) {  // block-uniform
+    if (it >= nm) {  // four tiles of at most 64 instances
+      const int32_t at = nm + 4 * (it - nm) + (t >> 6);
+      if (at < ntiles) {  // wave-uniform
+        const uint2 rg = ranges[tile_order[at]];
+        const int m = (int)(rg.y - rg.x);
+        if (m > 0) {
+          const uint32_t k = (uint32_t)wave_sort(lane < m ? bkey[rg.x + lane] : ~0ull);
+          if (lane < m) {
+            ival[rg.x + lane] = k;
+            info_k[rg.x + lane] = inst_info[k];
           }
         }
-        continue;
       }
-      const uint2 rg = ranges[tile_order[order_place((uint32_t)it, (uint32_t)ch, (uint32_t)nch)]];
-      if (rg.y - rg.x > (uint32_t)kSortSmall) continue;  // listed in chunks
-      const int m = (int)(rg.y - rg.x);
-      block_sort_small<kSmallThreads>(bkey + rg.x, keys, m);
-      for (int j = t; j < m; j += kSmallThreads) {
-        const uint32_t k = (uint32_t)keys[j];
-        ival[rg.x + j] = k;
-        info_k[rg.x + j] = inst_info[k];
-      }
-      __syncthreads();
+      continue;
     }
+    const uint2 rg = ranges[tile_order[it]];
+    if (rg.y - rg.x > (uint32_t)kSortSmall) continue;  // listed in chunks
+    const int m = (int)(rg.y - rg.x);
+    block_sort_small<kSmallThreads>(bkey + rg.x, keys, m);
+    for (int j = t; j < m; j += kSmallThreads) {
+      const uint32_t k = (uint32_t)keys[j];
+      ival[rg.x + j] = k;
+      info_k[rg.x + j] = inst_info[k];
+    }
+    __syncthreads();
   }
 }
 
@@ -910,9 +950,7 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   __shared__ uint32_t ev[NT];
   __shared__ uint32_t bm[NT];
   __shared__ uint8_t hits[NW][4][NT];  // per row of each wave: the batch slots it replays, in order
-  const uint32_t place = tile_order[blockIdx.x];
-  if (place == kNoTile) return;  // block-uniform
-  const int tile = (int)place;
+  const int tile = (int)tile_order[blockIdx.x];
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
   int px, pys[PX];
@@ -1013,7 +1051,15 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
     }
     if (!COUNT) {
       __syncthreads();
-      if ((int)threadIdx.x < m) event[b0 + threadIdx.x] = event_word(ev[threadIdx.x]);
+      // wave w's 64 slots are one event batch: a mask per block
+      const uint32_t e = (int)threadIdx.x < m ? ev[threadIdx.x] : 0u;
+      unsigned long long mine = 0ull;
+#pragma unroll
+      for (int b = 0; b < 16; ++b) {
+        const unsigned long long x = __ballot((e >> b) & 1u);
+        mine = lane == b ? x : mine;
+      }
+      if (lane < 16 && wv * 64 < m) event_masks(event, rg.x, tile)[16 * ((b0 - rg.x) / 64 + wv) + lane] = mine;
     }
   }
   if (COUNT) {
@@ -1037,30 +1083,35 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   }
 }
 
-// Forward blend with one wave per 8x8 quarter of a tile (four single-wave
-// workgroups per tile, tiles in the blend order): the wave's rows are the
+// A tile of at least kHeavyTile instances is blended by 16 waves, one per 4x4
+// block (blend_block_wave), others by four, one per 8x8 quarter
+// (blend_quarter).  The waves of a tile run on one XCD (workgroups go to the
+// XCDs in turn), so its words and records are read into one L2.
+constexpr int kHeavyWgs = 4096;  // single-wave workgroups that take the heavy tiles' blocks in turn
+
+// One wave on an 8x8 quarter of a tile: the wave's rows are the
 // quarter's four 4x4 blocks (blend_pixel<1>), lane l its pixel.  The wave
 // streams the tile's instances in batches of 64 and replays, row by row, the
 // ones whose block mask meets the row's block, as k_blend does.  Instance
-// words (owning splat, block mask, gathered in tile order) are loaded two
+// words (owning splat, block mask, in tile order) are loaded two
 // batches ahead and the splat records of the instances that reach the quarter
 // one batch ahead, into registers, so the loads overlap the blending; the
 // waves of a tile never wait for each other, and each stops when its own
-// pixels have.  Events: byte q of each instance's event word holds quarter q's
-// (4-bit) events, written by quarter q's wave, zero for instances it never
-// reached.
-__global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp, const uint2* __restrict__ ranges,
-                                                const uint2* __restrict__ info_k,
-                                                const Splat* __restrict__ splats, const FrameCounters* ctr,
-                                                const uint32_t* __restrict__ tile_order, float bg0, float bg1,
-                                                float bg2, float* rgb, uint8_t* event8) {
-  const ViewConst v = *vp;
-  __shared__ float4 rec[3][64];     // the batch's records: (mx hi, lo, my hi, lo), (ce, se, h1, h2), (o, r, g, b)
-  __shared__ uint8_t hits[4][64];   // per row: the batch slots it replays, in order
-  __shared__ uint32_t evr[64];      // per slot: this quarter's event bits
-  const uint32_t place = tile_order[blockIdx.x >> 2];
-  if (place == kNoTile) return;  // block-uniform
-  const int tile = (int)place, q = (int)(blockIdx.x & 3u);
+// pixels have.  Events: one mask per batch and block (event_masks), zero for
+// batches the wave never reached.
+struct QuarterLds {
+  float4 rec[3][64];    // the batch's records: (mx hi, lo, my hi, lo), (ce, se, h1, h2), (o, r, g, b)
+  uint8_t hits[4][64];  // per row: the batch slots it replays, in order
+  uint32_t evr[64];     // per slot: this quarter's event bits
+};
+
+__device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int q, uint2 rg,
+                                              const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
+                                              uint32_t nr, float bg0, float bg1, float bg2, float* rgb,
+                                              uint32_t* event, QuarterLds& lds) {
+  float4 (&rec)[3][64] = lds.rec;
+  uint8_t (&hits)[4][64] = lds.hits;
+  uint32_t (&evr)[64] = lds.evr;
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x, g = lane >> 4;
   const uint64_t lt = lanemask_lt();
@@ -1072,8 +1123,7 @@ __global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp
   const bool inside = px < v.width && py < v.height;
   bool live = inside;
   float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
-  const uint2 rg = ranges[tile];
-  const uint32_t nr = (uint32_t)ctr->n_render;
+  unsigned long long* const ev64 = event_masks(event, rg.x, tile);
   const float thr = 1.0f / 255.0f;
   // pipeline: words of batches b and b + 64, the record of batch b (this lane's slot)
   uint32_t sk0 = 0u, bk0 = 0u, sk1 = 0u, bk1 = 0u;
@@ -1180,15 +1230,24 @@ __global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp
       }
     }
     __syncthreads();
-    if (lane < m) event8[4 * (int64_t)(b0 + lane) + q] = (uint8_t)((evr[lane] >> (4 * q)) & 0xFu);
+    // the batch's event masks of the quarter's blocks
+    const uint32_t e = lane < m ? evr[lane] >> (4 * q) : 0u;
+    unsigned long long own = 0ull;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const unsigned long long x = __ballot((e >> b) & 1u);
+      own = lane == b ? x : own;
+    }
+    if (lane < 4) ev64[16 * ((b0 - rg.x) / 64) + 4 * q + lane] = own;
     __syncthreads();
     sk0 = sk1;
     bk0 = bk1;
     sk1 = sk2;
     bk1 = bk2;
   }
-  // instances of the tile that this quarter never reached
-  for (uint32_t k = b0 + lane; k < rg.y; k += 64) event8[4 * (int64_t)k + q] = 0;
+  // batches of the tile that this quarter never reached
+  const uint32_t nb = (rg.y - rg.x + 63) / 64;
+  for (uint32_t k = (b0 - rg.x) / 64 + (lane >> 2); k < nb; k += 16) ev64[16 * k + 4 * q + (lane & 3)] = 0ull;
   if (inside) {
     float* o = rgb + 3 * ((int64_t)py * v.width + px);
     o[0] = __builtin_fmaf(T, bg0, cr);
@@ -1197,15 +1256,188 @@ __global__ void __launch_bounds__(64) k_blend_q(const ViewConst* __restrict__ vp
   }
 }
 
+// The values of x in the four 16-lane rows' lanes of the same index, by row.
+__device__ __forceinline__ void rows_of(float x, float* y) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);  // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+  const auto even = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const auto odd = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  y[0] = __uint_as_float(even[0]);
+  y[1] = __uint_as_float(odd[0]);
+  y[2] = __uint_as_float(even[1]);
+  y[3] = __uint_as_float(odd[1]);
+}
+
+// One wave on a 4x4 block of a tile, four of the block's splats at a time: row
+// r evaluates the (4 s + r)-th one's alpha at the 16 pixels, the rows exchange
+// the factors 1 - alpha (1 where the splat is skipped), and every row forms the
+// pixel's transmittances in order, so each decision and product is the
+// sequential one.  A pixel stops where the transmittance would fall below
+// 1e-4: it and everything behind it then stays below, so no stop flag is kept.
+// Row c adds up channel c of the four in order.  A step costs about a third
+// more instructions than a quarter's (one splat for each of four blocks) and
+// retires four of the block's list, which is what bounds a heavy tile: its
+// wave is a serial chain of steps.  Records are stored compacted, in list
+// order, and read one step ahead.
+struct BlockLds {
+  float4 a[64], b[64];  // (mx hi, lo, my hi, lo), (ce, se, h1, h2)
+  float o[64];
+  float col[3][64];     // a step's four colours of a channel are one 16-byte read
+};
+
+__device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, int blk, uint2 rg,
+                                                 const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
+                                                 uint32_t nr, float bg0, float bg1, float bg2, float* rgb,
+                                                 uint32_t* event, BlockLds& lds) {
+  const int lane = threadIdx.x, r = lane >> 4, ch = r < 3 ? r : 2;
+  const int px = (tile % v.tiles_x) * kTile + 8 * ((blk >> 2) & 1) + 4 * (blk & 1) + (lane & 3);
+  const int py = (tile / v.tiles_x) * kTile + 8 * (blk >> 3) + 4 * ((blk >> 1) & 1) + ((lane >> 2) & 3);
+  const uint64_t lt = lanemask_lt();
+  const uint32_t bit = 1u << blk;
+  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f, thr = 1.0f / 255.0f;
+  const bool inside = px < v.width && py < v.height;
+  unsigned long long* const ev64 = event_masks(event, rg.x, tile) + blk;
+  float T = inside ? 1.0f : 0.0f;  // 0 once the pixel has stopped
+  float Tout = 1.0f, c = 0.0f;     // the transmittance at the end, this row's channel
+  // pipeline: words of batches b0 and b0 + 64, the record of batch b0 (this lane's slot)
+  const auto word = [&](uint32_t k) { return k < rg.y ? info_k[k] : make_uint2(0u, 0u); };
+  const auto mine = [&](const uint2& w) { return w.x < nr && (w.y & bit) != 0u; };  // (a word past the end has no bit)
+  uint2 w0 = word(rg.x + lane), w1 = word(rg.x + 64 + lane);
+  float4 ra = make_float4(0.f, 0.f, 0.f, 0.f), rb = ra, rc = ra;
+  const auto record = [&](const uint2& w) {
+    if (mine(w)) {
+      const float4* p = reinterpret_cast<const float4*>(splats + w.x);
+      ra = p[0];
+      rb = p[1];
+      rc = p[2];
+    }
+  };
+  record(w0);
+  uint32_t b0 = rg.x;
+  for (; b0 < rg.y; b0 += 64) {
+    if (!__any(T > 0.0f)) break;  // wave-uniform
+    const bool hit0 = mine(w0);
+    const uint64_t hb = __ballot(hit0);
+    const int h = __popcll(hb), at = __popcll(hb & lt);
+    if (hit0) {
+      lds.a[at] = ra;
+      lds.b[at] = rb;
+      lds.o[at] = rc.x;
+      lds.col[0][at] = rc.y;
+      lds.col[1][at] = rc.z;
+      lds.col[2][at] = rc.w;
+    }
+    // prefetch: the records of the next batch, the words of the one after
+    record(w1);
+    const uint2 w2 = word(b0 + 128 + lane);
+    __syncthreads();
+    uint64_t evm = 0ull;  // bit e: the e-th listed splat blended or stopped at a pixel of the block
+    float4 a = lds.a[r], b = lds.b[r];
+    float o = lds.o[r];
+#pragma unroll 1
+    for (int s = 0; s < h; s += 4) {  // wave-uniform
+      const int e = s + r, nx = (e + 4) & 63;
+      const float4 na = lds.a[nx], nb = lds.b[nx], col = *reinterpret_cast<const float4*>(&lds.col[ch][s]);
+      const float no = lds.o[nx];
+      Splat sp;
+      sp.mxh = a.x; sp.mxl = a.y; sp.myh = a.z; sp.myl = a.w;
+      sp.ce = b.x; sp.se = b.y; sp.h1 = b.z; sp.h2 = b.w;
+      float dx, dy, u1, u2;
+      const float power = splat_power(sp, fx, fy, dx, dy, u1, u2);
+      const float alpha = fminf(0.99f, o * fexp(power));
+      const bool hit = (e < h) & (alpha >= thr);
+      float f[4], w[4];
+      const float own = hit ? 1.0f - alpha : 1.0f;
+      rows_of(own, f);
+      const float t1 = T * f[0], t2 = t1 * f[1], t3 = t2 * f[2], t4 = t3 * f[3];
+      float Tb = r == 0 ? T : t1;  // before this row's splat
+      Tb = r >= 2 ? t2 : Tb;
+      Tb = r == 3 ? t3 : Tb;
+      const bool con = hit & (Tb * own >= 0.0001f);
+      const uint64_t hits = __ballot(hit & (Tb >= 0.0001f));  // (a pixel that had not stopped)
+      rows_of(con ? alpha * Tb : 0.0f, w);
+      c = w[0] > 0.0f ? __builtin_fmaf(col.x, w[0], c) : c;
+      c = w[1] > 0.0f ? __builtin_fmaf(col.y, w[1], c) : c;
+      c = w[2] > 0.0f ? __builtin_fmaf(col.z, w[2], c) : c;
+      c = w[3] > 0.0f ? __builtin_fmaf(col.w, w[3], c) : c;
+      const uint64_t four = ((hits & 0xFFFFull) ? 1ull : 0ull) | ((hits & 0xFFFF0000ull) ? 2ull : 0ull) |
+                            ((hits & 0xFFFF00000000ull) ? 4ull : 0ull) | ((hits >> 48) ? 8ull : 0ull);
+      evm |= four << s;
+      if (__any((T > 0.0f) & (t4 < 0.0001f))) {  // wave-uniform: a pixel stops at one of the four
+        float Tl = t1 >= 0.0001f ? t1 : T;
+        Tl = t2 >= 0.0001f ? t2 : Tl;
+        Tl = t3 >= 0.0001f ? t3 : Tl;
+        Tout = ((T > 0.0f) & (t4 < 0.0001f)) ? Tl : Tout;
+        T = t4 >= 0.0001f ? t4 : 0.0f;
+        if (!__any(T > 0.0f)) break;
+      } else {
+        T = t4;
+      }
+      a = na;
+      b = nb;
+      o = no;
+    }
+    const uint64_t slots = __ballot(hit0 && ((evm >> at) & 1ull) != 0ull);
+    if (lane == 0) ev64[16 * ((b0 - rg.x) / 64)] = slots;
+    __syncthreads();
+    w0 = w1;
+    w1 = w2;
+  }
+  // batches of the tile that this block never reached
+  const uint32_t nbt = (rg.y - rg.x + 63) / 64;
+  for (uint32_t k = (b0 - rg.x) / 64 + lane; k < nbt; k += 64) ev64[16 * k] = 0ull;
+  if (inside && r < 3) {
+    const float bg = r == 0 ? bg0 : (r == 1 ? bg1 : bg2);
+    rgb[3 * ((int64_t)py * v.width + px) + r] = __builtin_fmaf(T > 0.0f ? T : Tout, bg, c);
+  }
+}
+
+// Forward blend.  The first kHeavyWgs single-wave workgroups take the heavy
+// tiles' blocks in turn, the others the quarters of the other tiles, in the
+// tile order.  What bounds it is the longest tile's chain of steps, then the
+// instructions.  Quarters alone against blocks for tiles of 128, 256 and 512
+// instances on, us: 256-instance tiles of a 333 x 171 iteration 67 / 31 / 31 /
+// 38, an aerial 1080p view 63 / 42 / 36 / 48, a street view at 1080p (tiles of
+// up to 9035) 675 / 287 / 256 / 267 and at 4K 313 / 210 / 200 / 198.
+__global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ vp, const uint2* __restrict__ ranges,
+                                                  const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
+                                                  const FrameCounters* ctr, const uint32_t* __restrict__ tile_order,
+                                                  int32_t ntiles, float bg0, float bg1, float bg2, float* rgb,
+                                                  uint32_t* event) {
+  __shared__ union {
+    QuarterLds quarter;
+    BlockLds block;
+  } lds;
+  const uint32_t nr = (uint32_t)ctr->n_render;
+  const int xcd = blockIdx.x & 7;
+  if (blockIdx.x < kHeavyWgs) {
+    const int items = (ctr->n_heavy + 7) / 8 * 128;  // eight tiles' blocks for each 16 workgroups of an XCD
+    for (int i = blockIdx.x; i < items; i += kHeavyWgs) {
+      const int at = (i >> 7) * 8 + xcd, blk = (i >> 3) & 15;
+      if (at >= ctr->n_heavy) continue;
+      const int tile = (int)tile_order[at];
+      blend_block_wave(*vp, tile, blk, ranges[tile], info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.block);
+      __syncthreads();
+    }
+    return;
+  }
+  const int i = (int)blockIdx.x - kHeavyWgs, at = (i >> 5) * 8 + xcd, q = (i >> 3) & 3;
+  if (at >= ntiles) return;
+  const int tile = (int)tile_order[at];
+  const uint2 rg = ranges[tile];
+  if (rg.y - rg.x >= (uint32_t)kHeavyTile) return;
+  blend_quarter(*vp, tile, q, rg, info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.quarter);
+}
+
 template <bool COUNT>
 static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], float* d_rgb, hipStream_t st) {
-  const int ntiles = tile_places(v.tiles_x * v.tiles_y);
+  const int ntiles = v.tiles_x * v.tiles_y;
   unsigned long long* work = COUNT ? f->work : nullptr;
   uint32_t* event = COUNT ? nullptr : f->inst_event;
   if (!COUNT && f->blend_px_fwd == 1) {
-    hipLaunchKernelGGL(k_blend_q, dim3(4 * ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges, f->info_k,
-                       f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2], d_rgb,
-                       reinterpret_cast<uint8_t*>(event));
+    hipLaunchKernelGGL(k_blend_fwd, dim3(kHeavyWgs + 32 * ((ntiles + 7) / 8)), dim3(64), 0, st, f->d_view_ren,
+                       f->ranges, f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1],
+                       bg[2], d_rgb, event);
     return;
   }
   switch (f->blend_px_fwd) {
@@ -1228,10 +1460,10 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
 }
 
 int blend_output_arg(const void* func, int* n_args) {
-  // k_blend_q (..., bg2, rgb, event8) and k_blend<false, PX> (..., bg2, rgb, event, work)
-  if (func == reinterpret_cast<const void*>(&k_blend_q)) {
-    *n_args = 11;
-    return 9;
+  // k_blend_fwd (..., bg2, rgb, event) and k_blend<false, PX> (..., bg2, rgb, event, work)
+  if (func == reinterpret_cast<const void*>(&k_blend_fwd)) {
+    *n_args = 12;
+    return 10;
   }
   if (func == reinterpret_cast<const void*>(&k_blend<false, 1>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 2>) ||
@@ -1281,7 +1513,8 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_RANGES, st);
   hipLaunchKernelGGL(k_tile_scan, dim3(tile_chunks(ntiles)), dim3(kOrderThreads), 0, st,
-                     f->tile_count, ntiles, f->ctr, f->ranges, f->tile_cursor, f->tile_order, f->tile_mid, f->big_list);
+                     f->tile_count, ntiles, f->ctr, f->ranges, f->tile_cursor, f->tile_order,
+                     f->big_list);
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_TILE_SORT, st);
   const int32_t bucket_lds = ntiles <= kBucketLdsTiles ? ntiles : 0;
@@ -1290,7 +1523,7 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_DEPTH_SORT, st);
   hipLaunchKernelGGL(k_tile_sort, dim3(kTileSortGrid), dim3(kSmallThreads), 0, st, f->ctr, f->ranges,
-                     f->tile_order, f->tile_mid, ntiles, f->big_list, f->bucket_key, f->inst_info, f->info_k, f->ival);
+                     f->tile_order, ntiles, f->big_list, f->bucket_key, f->inst_info, f->info_k, f->ival);
   hipLaunchKernelGGL(k_tile_merge, dim3(1024), dim3(kSmallThreads), 0, st, f->ctr, f->ranges, f->big_list,
                      f->bucket_key, f->inst_info, f->info_k, f->ival);
   stage_end(f, st);

@@ -56,3 +56,16 @@ def test_pixels_per_lane(scene, monkeypatch, px, n):
     monkeypatch.setenv("LODGS_BLEND_PX_FWD", str(px))
     monkeypatch.setenv("LODGS_BLEND_PX_BWD", str(px))
     check(*scene, n, 16, 16)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 320, 1025])
+@pytest.mark.parametrize("size", [(16, 16), (13, 11)])
+def test_one_tile(scene, n, size):
+    # partial batches, and the tiles' forms on both sides of 256 instances
+    check(*scene, n, *size)
+
+
+@pytest.mark.parametrize("n,distance", [(255, 60.0), (600, 60.0), (2500, 90.0), (6000, 300.0)])
+def test_pixels_that_stop(scene, n, distance):
+    # pixels that stop early, in tiles of both forms; images of partial tiles
+    check(*scene, n, 40, 23, distance)
