@@ -101,6 +101,7 @@ __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int 
     ctr->n_instances = 0;
     ctr->n_long = 0;
     ctr->n_big = 0;
+    ctr->n_seg = 0;
   }
 }
 }  // namespace

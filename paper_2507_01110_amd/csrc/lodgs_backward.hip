@@ -88,37 +88,48 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // rows in order and writes one NP-float partial per (splat, tile) instance at
 // the instance's emission index, with zeros for instances that no pixel
 // reached.  No order depends on timing: the result is deterministic.
+// LDS of a workgroup of the blend backward.
 template <int PX, int NP>
-__global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restrict__ vp,
-                                                        const uint2* __restrict__ ranges,
-                                                        const uint32_t* __restrict__ ival,
-                                                        const uint2* __restrict__ info_k,
-                                                        const Splat* __restrict__ splats, const FrameCounters* ctr,
-                                                        const float* __restrict__ rgb, const float* __restrict__ dL,
-                                                        const uint32_t* __restrict__ event,
-                                                        const uint32_t* __restrict__ tile_order,
-                                                        float* __restrict__ partial) {
+struct BlendBwdLds {
   // NB instances per batch: at most one per thread, and at most 128, which
   // keeps the per-wave LDS rows small enough for several workgroups per CU
-  constexpr int NT = 256 / PX, NW = 4 / PX, NB = NT < 128 ? NT : 128;
-  const ViewConst v = *vp;
+  static constexpr int NT = 256 / PX, NW = 4 / PX, NB = NT < 128 ? NT : 128;
   // the first 12 floats of each splat record (mean, axis, power, opacity,
   // colour): all a replay reads, at a 12-word stride that spreads the rows'
   // reads of different slots over the banks
   struct BatchRec {
     float4 a, b, c;
   };
-  __shared__ BatchRec batch[NB];
-  __shared__ uint32_t bid[NB];
-  __shared__ unsigned long long emask[NB / 64][16];      // the batch's event masks by block
-  __shared__ unsigned long long wave_ev[NW][NB / 64];    // and over each wave's blocks
-  __shared__ uint8_t hits[NW][4][NB];  // per row of each wave: the batch slots it replays, in order
+  BatchRec batch[NB];
   // a row of acc per partial component; slot j's component c sits at column
   // j ^ c, so the ten lanes of a row adding one slot's components hit ten
   // banks (the rows are 128 words apart)
-  __shared__ float acc[NW][NP][NB];
-  __shared__ uint32_t wave_active[NW];  // per wave: some pixel still blends
-  const int tile = (int)tile_order[blockIdx.x];
+  float acc[NW][NP][NB];
+  unsigned long long emask[NB / 64][16];    // the batch's event masks by block
+  unsigned long long wave_ev[NW][NB / 64];  // and over each wave's blocks
+  uint32_t bid[NB];
+  uint32_t wave_active[NW];  // per wave: some pixel still blends
+  uint8_t hits[NW][4][NB];   // per row of each wave: the batch slots it replays, in order
+};
+
+// Instances [rg.x, rg.y) of the tile whose list begins at `first`: the whole
+// list, or a segment of it.
+template <int PX, int NP>
+__device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, uint32_t first, uint2 rg,
+                                                const uint32_t* __restrict__ ival, const uint2* __restrict__ info_k,
+                                                const Splat* __restrict__ splats, uint32_t nr,
+                                                const float* __restrict__ rgb, const float* __restrict__ dL,
+                                                const uint32_t* __restrict__ event, const float4* __restrict__ ckpt,
+                                                float* __restrict__ partial, BlendBwdLds<PX, NP>& lds) {
+  constexpr int NT = 256 / PX, NW = 4 / PX, NB = BlendBwdLds<PX, NP>::NB;
+  using BatchRec = typename BlendBwdLds<PX, NP>::BatchRec;
+  auto& batch = lds.batch;
+  auto& bid = lds.bid;
+  auto& emask = lds.emask;
+  auto& wave_ev = lds.wave_ev;
+  auto& hits = lds.hits;
+  auto& acc = lds.acc;
+  auto& wave_active = lds.wave_active;
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, row = lane >> 4;
   int px = 0;
@@ -139,6 +150,12 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
       G1[p] = dL[o + 1];
       G2[p] = dL[o + 2];
       GC[p] = __builtin_fmaf(G2[p], rgb[o + 2], __builtin_fmaf(G1[p], rgb[o + 1], G0[p] * rgb[o]));
+      if (rg.x > first) {  // the pixel's state before the segment
+        const float4 s = ckpt[256 * (int64_t)(rg.x / kSegment) + 16 * (py & 15) + (px & 15)];
+        T[p] = s.x;
+        GQ[p] = __builtin_fmaf(G2[p], s.w, __builtin_fmaf(G1[p], s.z, G0[p] * s.y));
+        live[p] = s.x > 0.0f;
+      }
     }
   }
   const float fx = (float)px + 0.5f;
@@ -150,8 +167,6 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
     exy[p] = ex * ey[p];
     eyy[p] = ey[p] * ey[p];
   }
-  const uint2 rg = ranges[tile];
-  const uint32_t nr = (uint32_t)ctr->n_render;
   const float thr = 1.0f / 255.0f;
   for (int t = threadIdx.x; t < NW * NP * NB; t += NT) (&acc[0][0][0])[t] = 0.0f;
   // The last NB threads load: thread NT - NB + j holds batch slot j, the
@@ -163,7 +178,7 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
   // run on different waves.
   const int ld = (int)threadIdx.x - (NT - NB);  // the loaded slot (loaders only)
   const bool loader = ld >= 0;
-  const unsigned long long* const ev64 = event_masks(event, rg.x, tile);
+  const unsigned long long* const ev64 = event_masks(event, first, tile) + 16 * ((rg.x - first) / 64);
   const uint32_t nbt = (rg.y - rg.x + 63) / 64;
   // e, i of the loaded slot, and lane l % 16's event mask of the 64 slots that
   // this wave loads (block l % 16's)
@@ -431,6 +446,49 @@ __global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restr
     float* dst = partial + NP * (int64_t)ival[k];
 #pragma unroll
     for (int c = 0; c < NP; ++c) dst[c] = 0.0f;
+  }
+}
+
+// The first kSegmentWgs workgroups take the segments of the long tiles in
+// turn (their number is known on the device only), the others a tile each, in
+// the tile order.
+constexpr int kSegmentWgs = 4096;
+template <int PX, int NP>
+__global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restrict__ vp,
+                                                        const uint2* __restrict__ ranges,
+                                                        const uint32_t* __restrict__ ival,
+                                                        const uint2* __restrict__ info_k,
+                                                        const Splat* __restrict__ splats, const FrameCounters* ctr,
+                                                        const float* __restrict__ rgb, const float* __restrict__ dL,
+                                                        const uint32_t* __restrict__ event,
+                                                        const uint32_t* __restrict__ tile_order,
+                                                        const uint2* __restrict__ seg_list,
+                                                        const float4* __restrict__ ckpt, float* __restrict__ partial) {
+  __shared__ BlendBwdLds<PX, NP> lds;
+  const bool segments = blockIdx.x < kSegmentWgs;
+  const int end = segments ? ctr->n_seg : (int)gridDim.x - kSegmentWgs;
+  const uint32_t nr = (uint32_t)ctr->n_render;
+  for (int i = segments ? (int)blockIdx.x : (int)blockIdx.x - kSegmentWgs; i < end; i += kSegmentWgs) {
+    int tile;
+    uint32_t q = 0;
+    if (segments) {
+      const uint2 e = seg_list[i];
+      tile = (int)e.x;
+      q = e.y;
+    } else {
+      tile = (int)tile_order[i];
+    }
+    const uint2 all = ranges[tile];
+    uint2 rg = all;
+    if (segments) {
+      rg.x = all.x + q * kSegment;
+      rg.y = min(all.y, rg.x + kSegment);
+    } else if (all.y - all.x > (uint32_t)kSegment) {
+      return;
+    }
+    blend_bwd_range<PX, NP>(*vp, tile, all.x, rg, ival, info_k, splats, nr, rgb, dL, event, ckpt, partial, lds);
+    if (!segments) return;
+    __syncthreads();
   }
 }
 
@@ -849,19 +907,19 @@ static void launch_blend_bwd_np(lodgs_frame* f, const float* d_dL, hipStream_t s
   const int ntiles = v.tiles_x * v.tiles_y;
   switch (f->blend_px_bwd) {
     case 1:
-      hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(kSegmentWgs + ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
-                         f->tile_order, f->inst_grad);
+                         f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;
     case 4:
-      hipLaunchKernelGGL((k_blend_bwd<4, NP>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<4, NP>), dim3(kSegmentWgs + ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
-                         f->tile_order, f->inst_grad);
+                         f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;
     default:
-      hipLaunchKernelGGL((k_blend_bwd<2, NP>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<2, NP>), dim3(kSegmentWgs + ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
-                         f->tile_order, f->inst_grad);
+                         f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;
   }
 }

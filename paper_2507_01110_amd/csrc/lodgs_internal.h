@@ -112,6 +112,7 @@ struct FrameCounters {
   int32_t n_long;        // drawn splats with more than kLongSegment instances
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
   int32_t n_heavy;       // tiles of at least kHeavyTile instances: the first of the tile order
+  int32_t n_seg;         // segments of the tiles of more than kSegment instances
   int32_t n_mid;         // tiles of at least 64 instances: likewise
 };
 
@@ -163,6 +164,10 @@ struct lodgs_frame {
   uint32_t* tile_order;   // [max tiles] tiles, heaviest class first
   uint32_t* tile_count;   // [max tiles] instances of each tile
   uint32_t* tile_cursor;  // [max tiles] next place in each tile's range
+  float4* ckpt;           // [max_instances / kSegment + 1][256] (transmittance, 0 if stopped; colour) of the tile's
+                          // pixels before the instances from the first place in a segmented tile's list on that
+                          // is a multiple of kSegment behind the list's start, by that place / kSegment
+  uint2* seg_list;        // [max_instances / kSegmentHalf + 1] (tile, segment) of the segmented tiles
   uint2* big_list;        // [max_instances / kSortChunkHalf + 1] (tile, chunk) of the tiles sorted in chunks
   float spt_scale;        // LoD noise factor on the distances to SPT roots (lodgs_frame_set_lod_noise)
   lodgs::ViewConst* d_view_sel;  // view constants of the last lod_select (device)
@@ -265,6 +270,15 @@ __device__ __forceinline__ unsigned long long* event_masks(uint32_t* event, uint
 __device__ __forceinline__ const unsigned long long* event_masks(const uint32_t* event, uint32_t begin, int tile) {
   return reinterpret_cast<const unsigned long long*>(event) + (((int64_t)begin + 64 * (int64_t)tile + 1) >> 1);
 }
+
+// A tile of more than kSegment instances is taken by the blend backward in
+// segments of that many, each from the pixels' state that the forward left in
+// `ckpt` before it, so no workgroup replays a longer list: the longest lists
+// had bounded the kernel.  Whole lists against segments of 512 and of 256, us:
+// a street view at 1080p (tiles of up to 9035) 619 / 307 / 318, a 333 x 171
+// iteration (1116) 98 / 61 / 39, an aerial 1080p view (407) 139 / 139 / 141.
+constexpr int kSegment = 256, kSegmentHalf = kSegment / 2;
+static_assert(kSegment >= kHeavyTile && kSegment % 256 == 0, "whole batches of every blend kernel");
 
 // Half the instances of a sort chunk: a tile sorted in chunks holds more than
 // one chunk, so it lists at most one chunk per this many instances.
@@ -377,6 +391,8 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->tile_order, nt);
   fn(f->tile_count, nt);
   fn(f->tile_cursor, nt);
+  fn(f->ckpt, 256 * (ni / kSegment + 1));
+  fn(f->seg_list, ni / kSegmentHalf + 1);
   fn(f->big_list, ni / kSortChunkHalf + 1);
   fn(f->work, 2);
   fn(f->d_view_sel, 1);

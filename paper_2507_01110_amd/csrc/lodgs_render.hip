@@ -516,12 +516,13 @@ static_assert(kSortSmall == 2 * kSortChunkHalf, "the chunk list's length");
 
 __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __restrict__ count, int32_t ntiles,
                                                              FrameCounters* ctr, uint2* ranges, uint32_t* cursor,
-                                                             uint32_t* order, uint2* big_list) {
+                                                             uint32_t* order, uint2* seg_list, uint2* big_list) {
   __shared__ uint32_t cnt[kTileClasses], pre[kTileClasses], post[kTileClasses];
   __shared__ uint32_t others[kTileClasses][kClassLanes];  // the other chunks' tiles: low half before, high half after
   __shared__ uint32_t half[2];
   __shared__ uint32_t wt[kOrderThreads / 64], wb[kOrderThreads / 64];
   __shared__ uint32_t big, big_base;  // this chunk's large tiles' sort chunks
+  __shared__ uint32_t seg, seg_base;  // and blend segments
   const int32_t per = tile_chunk(ntiles), lo = blockIdx.x * per;
   const int32_t n = min(per, ntiles - lo);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -530,7 +531,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) m[k] = k0 + k < n ? count[lo + k0 + k] : 0u;
   if (t < kTileClasses) cnt[t] = pre[t] = post[t] = 0;
-  if (t == 0) big = 0;
+  if (t == 0) big = seg = 0;
   if (gridDim.x > 1) {  // block-uniform
     static_assert(kTileClasses * kClassLanes == 4 * kOrderThreads, "one 16-byte store per thread");
     reinterpret_cast<uint4*>(&others[0][0])[t] = make_uint4(0u, 0u, 0u, 0u);
@@ -576,7 +577,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 #pragma unroll
   for (int w = 0; w < kOrderThreads / 64; ++w) start += wb[w] + (w < wv ? wt[w] : 0u);
   uint32_t key[kOrderBatch];  // class << 16 | rank within the chunk's class (rank < kOrderChunk)
-  uint32_t big_at[kOrderBatch];
+  uint32_t big_at[kOrderBatch], seg_at[kOrderBatch];
   const uint64_t lt = lanemask_lt();
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) {
@@ -594,10 +595,12 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
       cursor[tile] = start;
       start += m[k];
       key[k] = ((uint32_t)c << 16) | (c == c0 ? base + (uint32_t)__popcll(same & lt) : atomicAdd(&cnt[c], 1u));
+      if (m[k] > (uint32_t)kSegment) seg_at[k] = atomicAdd(&seg, (m[k] + kSegment - 1) / kSegment);
       if (m[k] > (uint32_t)kSortSmall) big_at[k] = atomicAdd(&big, (m[k] + kSortSmall - 1) / kSortSmall);
     }
   }
   __syncthreads();
+  if (t == kOrderThreads - 2 && seg != 0u) seg_base = (uint32_t)atomicAdd(&ctr->n_seg, (int)seg);
   if (t == kOrderThreads - 1 && big != 0u) big_base = (uint32_t)atomicAdd(&ctr->n_big, (int)big);
   // pre[c] becomes the place of the chunk's first tile of class c: all tiles of
   // the classes above c and the ones of class c before the chunk (waves 0 and
@@ -626,6 +629,9 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   for (int k = 0; k < kOrderBatch; ++k)
     if (k0 + k < n) {
       order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = (uint32_t)(lo + k0 + k);
+      if (m[k] > (uint32_t)kSegment)
+        for (uint32_t q = 0; q * kSegment < m[k]; ++q)
+          seg_list[seg_base + seg_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
       if (m[k] > (uint32_t)kSortSmall)
         for (uint32_t q = 0; q * kSortSmall < m[k]; ++q)
           big_list[big_base + big_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
@@ -943,7 +949,8 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
                                                     const uint2* __restrict__ info_k,
                                                     const Splat* __restrict__ splats, const FrameCounters* ctr,
                                                     const uint32_t* __restrict__ tile_order, float bg0, float bg1,
-                                                    float bg2, float* rgb, uint32_t* event, unsigned long long* work) {
+                                                    float bg2, float* rgb, uint32_t* event, unsigned long long* work,
+                                                    float4* ckpt) {
   constexpr int NT = 256 / PX, NW = 4 / PX;
   const ViewConst v = *vp;
   __shared__ Splat batch[NT];
@@ -972,11 +979,20 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   const uint32_t nr = (uint32_t)ctr->n_render;
   const float thr = 1.0f / 255.0f;
   unsigned long long n_eval = 0, n_contrib = 0;
-  for (uint32_t b0 = rg.x; b0 < rg.y; b0 += NT) {
+  // the pixels' state before instance k of the list (a segment's first)
+  auto checkpoint = [&](uint32_t k) {
+    float4* c = ckpt + 256 * (int64_t)(k / kSegment);
+#pragma unroll
+    for (int p = 0; p < PX; ++p)
+      c[16 * (pys[p] & 15) + (px & 15)] = make_float4(live[p] ? T[p] : 0.0f, cr[p], cg[p], cb[p]);
+  };
+  uint32_t b0 = rg.x;
+  for (; b0 < rg.y; b0 += NT) {
     bool active = false;
 #pragma unroll
     for (int p = 0; p < PX; ++p) active = active || live[p];
     if (__syncthreads_count(active) == 0) break;
+    if (!COUNT && b0 > rg.x && (b0 - rg.x) % kSegment == 0) checkpoint(b0);
     const uint32_t k = b0 + threadIdx.x;
     ev[threadIdx.x] = 0u;
     if (k < rg.y) {
@@ -1062,6 +1078,10 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
       if (lane < 16 && wv * 64 < m) event_masks(event, rg.x, tile)[16 * ((b0 - rg.x) / 64 + wv) + lane] = mine;
     }
   }
+  if (!COUNT)  // segments that no pixel reached
+    for (uint32_t k = b0 > rg.x ? rg.x + (b0 - rg.x + kSegment - 1) / kSegment * kSegment : rg.x + kSegment; k < rg.y;
+         k += kSegment)
+      checkpoint(k);
   if (COUNT) {
     for (int d = 32; d > 0; d >>= 1) {
       n_eval += __shfl_xor(n_eval, d, 64);
@@ -1288,7 +1308,7 @@ struct BlockLds {
 __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, int blk, uint2 rg,
                                                  const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
                                                  uint32_t nr, float bg0, float bg1, float bg2, float* rgb,
-                                                 uint32_t* event, BlockLds& lds) {
+                                                 uint32_t* event, float4* ckpt, BlockLds& lds) {
   const int lane = threadIdx.x, r = lane >> 4, ch = r < 3 ? r : 2;
   const int px = (tile % v.tiles_x) * kTile + 8 * ((blk >> 2) & 1) + 4 * (blk & 1) + (lane & 3);
   const int py = (tile / v.tiles_x) * kTile + 8 * (blk >> 3) + 4 * ((blk >> 1) & 1) + ((lane >> 2) & 3);
@@ -1313,9 +1333,15 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
     }
   };
   record(w0);
+  // the pixels' state before instance k of the list (a segment's first)
+  const auto checkpoint = [&](uint32_t k) {
+    float* s = reinterpret_cast<float*>(ckpt + 256 * (int64_t)(k / kSegment) + 16 * (py & 15) + (px & 15));
+    s[r < 3 ? r + 1 : 0] = r < 3 ? c : T;
+  };
   uint32_t b0 = rg.x;
   for (; b0 < rg.y; b0 += 64) {
     if (!__any(T > 0.0f)) break;  // wave-uniform
+    if (b0 > rg.x && (b0 - rg.x) % kSegment == 0) checkpoint(b0);
     const bool hit0 = mine(w0);
     const uint64_t hb = __ballot(hit0);
     const int h = __popcll(hb), at = __popcll(hb & lt);
@@ -1383,7 +1409,10 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
     w0 = w1;
     w1 = w2;
   }
-  // batches of the tile that this block never reached
+  // segments and batches of the tile that this block never reached
+  for (uint32_t k = b0 > rg.x ? rg.x + (b0 - rg.x + kSegment - 1) / kSegment * kSegment : rg.x + kSegment; k < rg.y;
+       k += kSegment)
+    checkpoint(k);
   const uint32_t nbt = (rg.y - rg.x + 63) / 64;
   for (uint32_t k = (b0 - rg.x) / 64 + lane; k < nbt; k += 64) ev64[16 * k] = 0ull;
   if (inside && r < 3) {
@@ -1403,7 +1432,7 @@ __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ 
                                                   const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
                                                   const FrameCounters* ctr, const uint32_t* __restrict__ tile_order,
                                                   int32_t ntiles, float bg0, float bg1, float bg2, float* rgb,
-                                                  uint32_t* event) {
+                                                  uint32_t* event, float4* ckpt) {
   __shared__ union {
     QuarterLds quarter;
     BlockLds block;
@@ -1416,7 +1445,8 @@ __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ 
       const int at = (i >> 7) * 8 + xcd, blk = (i >> 3) & 15;
       if (at >= ctr->n_heavy) continue;
       const int tile = (int)tile_order[at];
-      blend_block_wave(*vp, tile, blk, ranges[tile], info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.block);
+      blend_block_wave(*vp, tile, blk, ranges[tile], info_k, splats, nr, bg0, bg1, bg2, rgb, event, ckpt,
+                       lds.block);
       __syncthreads();
     }
     return;
@@ -1437,38 +1467,38 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
   if (!COUNT && f->blend_px_fwd == 1) {
     hipLaunchKernelGGL(k_blend_fwd, dim3(kHeavyWgs + 32 * ((ntiles + 7) / 8)), dim3(64), 0, st, f->d_view_ren,
                        f->ranges, f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1],
-                       bg[2], d_rgb, event);
+                       bg[2], d_rgb, event, f->ckpt);
     return;
   }
   switch (f->blend_px_fwd) {
     case 1:
       hipLaunchKernelGGL((k_blend<COUNT, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
-                         d_rgb, event, work);
+                         d_rgb, event, work, f->ckpt);
       break;
     case 4:
       hipLaunchKernelGGL((k_blend<COUNT, 4>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
-                         d_rgb, event, work);
+                         d_rgb, event, work, f->ckpt);
       break;
     default:
       hipLaunchKernelGGL((k_blend<COUNT, 2>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
-                         d_rgb, event, work);
+                         d_rgb, event, work, f->ckpt);
       break;
   }
 }
 
 int blend_output_arg(const void* func, int* n_args) {
-  // k_blend_fwd (..., bg2, rgb, event) and k_blend<false, PX> (..., bg2, rgb, event, work)
+  // k_blend_fwd (..., bg2, rgb, event, ckpt) and k_blend<false, PX> (..., bg2, rgb, event, work, ckpt)
   if (func == reinterpret_cast<const void*>(&k_blend_fwd)) {
-    *n_args = 12;
+    *n_args = 13;
     return 10;
   }
   if (func == reinterpret_cast<const void*>(&k_blend<false, 1>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 2>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 4>)) {
-    *n_args = 12;
+    *n_args = 13;
     return 9;
   }
   return -1;
@@ -1513,7 +1543,7 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_RANGES, st);
   hipLaunchKernelGGL(k_tile_scan, dim3(tile_chunks(ntiles)), dim3(kOrderThreads), 0, st,
-                     f->tile_count, ntiles, f->ctr, f->ranges, f->tile_cursor, f->tile_order,
+                     f->tile_count, ntiles, f->ctr, f->ranges, f->tile_cursor, f->tile_order, f->seg_list,
                      f->big_list);
   stage_end(f, st);
   stage_begin(f, LODGS_STAGE_TILE_SORT, st);

@@ -69,3 +69,9 @@ def test_one_tile(scene, n, size):
 def test_pixels_that_stop(scene, n, distance):
     # pixels that stop early, in tiles of both forms; images of partial tiles
     check(*scene, n, 40, 23, distance)
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 769])
+def test_segments(scene, n):
+    # lists that end at, before and behind the backward's segments of 256
+    check(*scene, n, 16, 16)
