@@ -9,6 +9,8 @@
 // EWA Jacobian, the camera transform, the covariance factorisation, the
 // quaternion normalisation, the sigmoid and the SH basis to the raw
 // parameters.
+#include <type_traits>
+
 #include "lodgs_internal.h"
 #include "lodgs_proj.h"
 
@@ -62,8 +64,7 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
 }
 
-// Backward of the blend: the forward's decisions, pixel layout blend_pixel<PX, true>
-// (each wave's rows spread over the block rows and columns).
+// Backward of the blend: the forward's decisions, pixel layout blend_pixel.
 // Each 16-lane row replays only the splats whose forward event bits cover one
 // of its blocks: elsewhere no pixel of the row blended the splat or stopped on
 // it in the forward, so the replay would leave every value unchanged.  The
@@ -139,7 +140,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
 #pragma unroll
   for (int p = 0; p < PX; ++p) {
     int py;
-    blend_pixel<PX, true>(tx, ty, wv, lane, p, px, py);
+    blend_pixel<PX>(tx, ty, wv, lane, p, px, py);
     fy[p] = (float)py + 0.5f;
     live[p] = px < v.width && py < v.height;
     T[p] = 1.0f;
@@ -231,7 +232,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     for (int p = 0; p < PX; ++p) active = active || live[p];
     // each wave publishes whether a pixel of it still blends with the batch,
     // behind the batch's barrier (no block-wide count, which takes three)
-    const bool wave_act = __any(active);
+    const bool wave_act = any_lane(active);
     if (lane == 0) wave_active[wv] = wave_act ? 1u : 0u;
     if (loader) {
       bid[ld] = e0;
@@ -268,7 +269,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
       for (int c = 0; c < NB / 64; ++c) {
         uint64_t hb = 0ull;
 #pragma unroll
-        for (int p = 0; p < PX; ++p) hb |= emask[c][31 - __builtin_clz(blend_pixel_block<PX, true>(wv, r, p))];
+        for (int p = 0; p < PX; ++p) hb |= emask[c][31 - __builtin_clz(blend_pixel_block<PX>(wv, r, p))];
         hb = uniform64(hb);
         if ((hb >> lane) & 1ull) hits[wv][r][cnt + __popcll(hb & lt)] = (uint8_t)(c * 64 + lane);
         cnt += __popcll(hb);
@@ -287,7 +288,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     const int n = row == 0 ? nh[0] : (row == 1 ? nh[1] : (row == 2 ? nh[2] : nh[3]));  // this row's list
     const int nmax = max(max(nh[0], nh[1]), max(nh[2], nh[3]));
-    if (__any(active) && nmax > 0) {  // wave-uniform
+    if (any_lane(active) && nmax > 0) {  // wave-uniform
       // one splat (batch slot j of this row's list; has = false past its end)
       // against the row's pixels; true when every pixel of the wave has
       // stopped
@@ -309,7 +310,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
           any_con = any_con | cons[p];
           act = act | live[p];
         }
-        if (__any(any_con)) {  // wave-uniform
+        if (any_lane(any_con)) {  // wave-uniform
           // the first pixel's terms start the sums: only the sign of a zero
           // sum differs from adding them to +0, and the LDS rows (never -0)
           // absorb that
@@ -362,11 +363,11 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
           // the rows add into the wave's row of their splats with one LDS
           // add instruction (two rows may be on the same splat: the LDS
           // applies the lanes of one instruction in a fixed order)
-          const uint64_t cm = __ballot(any_con);
+          const uint64_t cm = ballot(any_con);
           if (slot < NP && ((cm >> (16 * row)) & 0xFFFFull) != 0ull)
             __hip_atomic_fetch_add(&acc[wv][slot][j ^ slot], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        return !__any(act);
+        return !any_lane(act);
       };
       // two register sets, each loaded one list entry ahead of its use
       static_assert((NB & (NB - 1)) == 0, "a power of two of list entries");
@@ -449,44 +450,413 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
   }
 }
 
+// Columns of the blend backward's matrix products, for a wave whose row r is
+// the block (r & 1, r >> 1) of a 2 x 2 group (PX = 1).  Columns 0..12 of the
+// first product hold the moment factors 1; x of the left and right blocks; y
+// of the upper and lower ones; x^2; y^2; x y of the four.  The second holds a
+// colour channel of dL/dC of one block in each of twelve columns, placed where
+// the first has nothing for that block, so that a row's nine sums lie in nine
+// different columns.
+constexpr int kMomentColumns = 13;
+struct BwdColumns {
+  // per column, by 4-bit field from bit 0: for rows 0..3 which sum it holds
+  // for the row's splats (0..5 the moments 1, x, y, x^2, x y, y^2; 6..8 the
+  // colours; 15 none); the moment's powers (x | y << 2); its block (column |
+  // row << 1); the colour's row; its channel (3: none)
+  uint32_t col[16];
+  // per row, the lanes whose columns hold one of its sums, and a colour
+  uint64_t takes[4], colour[4];
+};
+constexpr BwdColumns bwd_columns() {
+  constexpr int colours[4][3] = {{2, 4, 6}, {1, 5, 8}, {3, 7, 12}, {9, 10, 11}};
+  BwdColumns t{};
+  for (int c = 0; c < 16; ++c) {
+    int px = 0, py = 0, b = 0;
+    if (c == 1 || c == 2) px = 1, b = c - 1;
+    if (c == 3 || c == 4) py = 1, b = 2 * (c - 3);
+    if (c == 5 || c == 6) px = 2, b = c - 5;
+    if (c == 7 || c == 8) py = 2, b = 2 * (c - 7);
+    if (c >= 9 && c < kMomentColumns) px = py = 1, b = c - 9;
+    uint32_t crow = 0, ch = 3;
+    for (int r = 0; r < 4; ++r) {
+      const int m[6] = {0, 1 + (r & 1), 3 + (r >> 1), 5 + (r & 1), 9 + r, 7 + (r >> 1)};
+      uint32_t sum = 15;
+      for (int k = 0; k < 6; ++k)
+        if (m[k] == c) sum = (uint32_t)k;
+      for (int k = 0; k < 3; ++k)
+        if (colours[r][k] == c) sum = 6u + (uint32_t)k, crow = (uint32_t)r, ch = (uint32_t)k;
+      t.col[c] |= sum << (4 * r);
+      if (sum < 9) t.takes[r] |= 0x0001000100010001ull << c;
+      if (sum >= 6 && sum < 9) t.colour[r] |= 0x0001000100010001ull << c;
+    }
+    t.col[c] |= (uint32_t)(px | py << 2) << 16 | (uint32_t)b << 20 | crow << 24 | ch << 28;
+  }
+  return t;
+}
+constexpr BwdColumns kBwdColumns = bwd_columns();
+static_assert(kBwdColumns.takes[0] == 0x02FF02FF02FF02FFull && kBwdColumns.takes[3] == 0x1F551F551F551F55ull,
+              "nine columns a row");
+__constant__ uint32_t kBwdColumn[16] = {
+    kBwdColumns.col[0],  kBwdColumns.col[1],  kBwdColumns.col[2],  kBwdColumns.col[3],
+    kBwdColumns.col[4],  kBwdColumns.col[5],  kBwdColumns.col[6],  kBwdColumns.col[7],
+    kBwdColumns.col[8],  kBwdColumns.col[9],  kBwdColumns.col[10], kBwdColumns.col[11],
+    kBwdColumns.col[12], kBwdColumns.col[13], kBwdColumns.col[14], kBwdColumns.col[15]};
+typedef float float4_t __attribute__((ext_vector_type(4)));
+// Orders the wave's LDS writes before its later reads (its LDS operations run
+// in order: nothing to wait for).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same for PX = 1, the default, in fewer instructions: they and the LDS
+// had bounded the kernel.  A wave's rows are the 2 x 2 blocks of a quarter.  A
+// lane holds one component of its row's splat, read by the others with a row
+// broadcast that is part of the instruction that uses it (one 4-byte LDS read
+// a step and one register, instead of three of 16 bytes and twelve).  The sums
+// over a block's pixels are matrix products: after four steps the terms of 16
+// (step, row) splats at 16 pixels, 16 x 16, times the columns' factors at
+// those pixels, in FP32.  The moments are summed without the opacity, which
+// multiplies the totals, and about the quarter's centre, which keeps the sums
+// small: the gradients' errors against 64 bits are 0.92 (scales, rotations)
+// to 1.00 (colours) of those of the tree of adds about the tile's centre.  A
+// step takes 62 vector instructions where it took 110, and the float adds in
+// the LDS (3 cycles a lane each) are gone.  96 registers and 31 KB let five
+// workgroups run on a CU, which hides part of the batches' waits: with four, 5
+// to 10% slower.  What is left: the waits of a workgroup's waves for each
+// other at every batch (the vector units issue two thirds of the time).
+// Before and after, us: an aerial 1080p view 139 / 117, a 1080p iteration
+// 90 / 70, a view of a batch 145 / 96, a street view 318 / 269, a 333 x 171
+// iteration 39 / 36.
+template <int NP>
+struct BlocksBwdLds {
+  static constexpr int NW = 4, NB = 64, NA = NP - 1;
+  static constexpr int kRow = NB + 20;  // (sums of one slot, and the slots of a write-out, on different banks)
+  float rec[NB + 4][16];  // the records' first 12 floats; slots NB.. are splats that reach no pixel
+  // per wave, the dL/do terms and the weights of four steps' splats (step,
+  // row) at the 16 pixels of the row's block
+  float4 fac[NW][2][64];
+  float4 grad[NW][64];  // the second product's right operands
+  float acc[NW][NA + 1][kRow];  // a row per sum, and one for the columns without
+  unsigned long long emask[2][16];  // the event masks of a batch and the next by block
+  uint32_t wave_active[NW];      // per wave: some pixel still blends
+  uint8_t hits[NW][NB + 4][4];   // per wave and row: the batch slots it replays, in order, then slots NB..
+};
+
+template <int N>
+__device__ __forceinline__ float row_lane(float x) {  // lane N of the row
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + N, 0xf, 0xf, true));
+}
+
+template <int NP>
+__device__ __forceinline__ void blend_bwd_blocks(const ViewConst& v, int tile, uint32_t first, uint2 rg,
+                                                 const uint32_t* __restrict__ ival, const uint2* __restrict__ info_k,
+                                                 const Splat* __restrict__ splats, uint32_t nr,
+                                                 const float* __restrict__ rgb, const float* __restrict__ dL,
+                                                 const uint32_t* __restrict__ event, const float4* __restrict__ ckpt,
+                                                 float* __restrict__ partial, BlocksBwdLds<NP>& lds) {
+  constexpr int NW = BlocksBwdLds<NP>::NW, NB = BlocksBwdLds<NP>::NB, NA = BlocksBwdLds<NP>::NA;
+  constexpr int kRow = BlocksBwdLds<NP>::kRow;
+  const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, row = lane >> 4;
+  // a thread loads part `part` of batch slot `mine`'s record and writes a
+  // quarter of its sums
+  const int mine = threadIdx.x >> 2, part = threadIdx.x & 3;
+  const unsigned long long* const ev64 = event_masks(event, first, tile) + 16 * ((rg.x - first) / 64);
+  // the slot's splat, and block (lane % 16)'s event mask of the batch
+  const auto words = [&](uint32_t b, uint32_t& i, unsigned long long& mk) {
+    i = b + mine < rg.y ? info_k[b + mine].x : 0u;
+    mk = b < rg.y ? ev64[16 * ((b - rg.x) / 64) + (lane & 15)] : 0ull;
+  };
+  // the record's part, if the slot has an event in any block
+  const auto record = [&](uint32_t i, unsigned long long mk) -> float4 {
+    uint32_t x = wv < 2 ? (uint32_t)mk : (uint32_t)(mk >> 32);
+#define LODGS_OR16(ctrl) x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, 0xf, 0xf, true)
+    LODGS_OR16(0xB1);   // quad_perm [1,0,3,2]
+    LODGS_OR16(0x4E);   // quad_perm [2,3,0,1]
+    LODGS_OR16(0x141);  // row_half_mirror
+    LODGS_OR16(0x140);  // row_mirror
+#undef LODGS_OR16
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    // (i >= nr only follows an instance overflow, without events)
+    if (((x >> (mine & 31)) & 1u) != 0u && i < nr && part < 3) r = reinterpret_cast<const float4*>(splats + i)[part];
+    return r;
+  };
+  uint32_t i0, i1;
+  unsigned long long mk0, mk1;
+  words(rg.x, i0, mk0);
+  words(rg.x + NB, i1, mk1);
+  int px, py;
+  blend_pixel<1>(tx, ty, wv, lane, 0, px, py);
+  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f, thr = 1.0f / 255.0f;
+  // (a stopped pixel's transmittance is 0: whatever hits it stops it again)
+  float T = 0.0f, GQ = 0.0f, GC = 0.0f, G0 = 0.0f, G1 = 0.0f, G2 = 0.0f;
+  if (px < v.width && py < v.height) {
+    const int64_t o = 3 * ((int64_t)py * v.width + px);
+    G0 = dL[o];
+    G1 = dL[o + 1];
+    G2 = dL[o + 2];
+    GC = __builtin_fmaf(G2, rgb[o + 2], __builtin_fmaf(G1, rgb[o + 1], G0 * rgb[o]));
+    T = 1.0f;
+    if (rg.x > first) {  // the pixel's state before the segment
+      const float4 s = ckpt[256 * (int64_t)(rg.x / kSegment) + 16 * (py & 15) + (px & 15)];
+      T = s.x;
+      GQ = __builtin_fmaf(G2, s.w, __builtin_fmaf(G1, s.z, G0 * s.y));
+    }
+  }
+  for (int t = threadIdx.x; t < (int)(sizeof lds.acc / sizeof(float)); t += 256) (&lds.acc[0][0][0])[t] = 0.0f;
+  if (threadIdx.x < 64) lds.rec[NB + row][lane & 15] = 0.0f;
+  // the right operands (this lane: column lane & 15, pixels (m, row) of the
+  // blocks) and, by row, where the column's sums go
+  float bm[4];
+  uint32_t dest[2];
+  {
+    const uint32_t cw = kBwdColumn[lane & 15];
+    const uint32_t mx = (cw >> 16) & 3u, my = (cw >> 18) & 3u, ch = cw >> 28;
+    const float x0 = (float)(4 * (int)((cw >> 20) & 1u)) - 3.5f;
+    const float y = (float)(4 * (int)((cw >> 21) & 1u) + row) - 3.5f;
+    const float yy = (lane & 15) >= kMomentColumns ? 0.0f : (my == 0u ? 1.0f : (my == 1u ? y : y * y));
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const float x = x0 + (float)m;
+      bm[m] = yy * (mx == 0u ? 1.0f : (mx == 1u ? x : x * x));
+    }
+    float* const g = reinterpret_cast<float*>(&lds.fac[wv][0][0]);  // dL/dC by channel
+    g[lane] = G0;
+    g[64 + lane] = G1;
+    g[128 + lane] = G2;
+    g[192 + lane] = 0.0f;
+    wave_fence();
+    lds.grad[wv][lane] = lds.fac[wv][0][16 * ch + 4 * ((cw >> 24) & 3u) + row];
+    const auto to = [&](uint32_t c) { return min(c, (uint32_t)NA) * kRow; };
+    dest[0] = to(cw & 15u) | to((cw >> 4) & 15u) << 16;
+    dest[1] = to((cw >> 8) & 15u) | to((cw >> 12) & 15u) << 16;
+    wave_fence();
+  }
+  float4 rec = record(i0, mk0);
+  if (threadIdx.x < 16) lds.emask[0][threadIdx.x] = mk0;
+  uint32_t b0 = rg.x, turn = 0;
+  for (; b0 < rg.y; b0 += NB, turn ^= 1u) {
+    const bool wave_act = any_lane(T > 0.0f);
+    if (lane == 0) lds.wave_active[wv] = wave_act ? 1u : 0u;
+    reinterpret_cast<float4*>(&lds.rec[mine][0])[part] = rec;
+    __syncthreads();
+    uint32_t block_act = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) block_act |= lds.wave_active[w];
+    if (block_act == 0u) break;  // every pixel of the tile has stopped (the same flags for all threads)
+    const int m = (int)min((uint32_t)NB, rg.y - b0);
+    const uint32_t out = mine < m ? ival[b0 + mine] : 0u;
+    rec = record(i1, mk1);
+    if (threadIdx.x < 16) lds.emask[turn ^ 1u][threadIdx.x] = mk1;
+    words(b0 + 2 * NB, i1, mk1);
+    // every row's list of the batch slots with an event in its block, in slot
+    // order (ranks in the masks)
+    int nmax = 0, nh[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint64_t hb = uniform64(lds.emask[turn][31 - __builtin_clz(blend_pixel_block<1>(wv, r, 0))]);
+      if (__builtin_amdgcn_inverse_ballot_w64(hb))
+        lds.hits[wv][__builtin_amdgcn_mbcnt_hi((uint32_t)(hb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hb, 0u))][r] =
+            (uint8_t)lane;
+      nh[r] = __popcll(hb);
+      nmax = max(nmax, nh[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      for (int k = nh[r]; k < nmax + 3; k += 64)  // wave-uniform
+        if (k + lane < nmax + 3) lds.hits[wv][k + lane][r] = (uint8_t)(NB + (lane & 3));
+    wave_fence();
+    if (wave_act && nmax > 0) {  // wave-uniform
+      float* const fac = reinterpret_cast<float*>(&lds.fac[wv][0][0]) + lane;
+      // step st of four: one splat per row (a component a lane) against the
+      // row's pixels; false when every pixel of the wave has stopped
+      const auto step = [&](float s, int st, int j) -> bool {
+        Splat sp;
+        sp.mxh = row_lane<0>(s);
+        sp.mxl = row_lane<1>(s);
+        sp.myh = row_lane<2>(s);
+        sp.myl = row_lane<3>(s);
+        sp.ce = row_lane<4>(s);
+        sp.se = row_lane<5>(s);
+        sp.h1 = row_lane<6>(s);
+        sp.h2 = row_lane<7>(s);
+        float dx, dy, u1, u2;
+        const float e = fexp(splat_power(sp, fx, fy, dx, dy, u1, u2));
+        const float oe = row_lane<8>(s) * e, alpha = fminf(0.99f, oe), left = 1.0f - alpha, tt = T * left;
+        const bool hit = alpha >= thr, con = hit & (tt >= 0.0001f);
+        const float Gc = __builtin_fmaf(row_lane<11>(s), G2, __builtin_fmaf(row_lane<10>(s), G1, row_lane<9>(s) * G0));
+        const float w = alpha * T, gq = __builtin_fmaf(w, Gc, GQ), wc = con ? w : 0.0f;
+        const float ia = __builtin_amdgcn_rcpf(left);  // gradient values only
+        const float dA = T * Gc - (GC - gq) * ia;
+        GQ = con ? gq : GQ;
+        fac[64 * st] = (con & (oe <= 0.99f)) ? dA * e : 0.0f;
+        fac[256 + 64 * st] = wc;
+        T = con ? tt : (hit ? 0.0f : T);
+        if (NP == 11) {  // contributing pixels
+          const uint64_t cm = ballot(con);
+          if ((lane & 15) == 0 && j < NB)
+            __hip_atomic_fetch_add(&lds.acc[wv][NA - 1][j], (float)__popc((uint32_t)(cm >> lane) & 0xFFFFu),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        return any_lane(T > 0.0f);
+      };
+      // the sums of the four steps from list entry t on (entries past a row's
+      // list leave zeros): register r holds row r's, lane (column, step)
+      float4_t d1 = {0.f, 0.f, 0.f, 0.f}, d2 = {0.f, 0.f, 0.f, 0.f};
+      uint32_t slots = NB * 0x01010101u;  // of the four rows' splats, by byte
+      const auto sums = [&](int t) {
+        wave_fence();
+        const float4 ao = lds.fac[wv][0][4 * (lane & 15) + row], aw = lds.fac[wv][1][4 * (lane & 15) + row];
+        const float4 bg = lds.grad[wv][lane];
+        slots = *reinterpret_cast<const uint32_t*>(&lds.hits[wv][t + row][0]);
+        d1 = d2 = float4_t{0.f, 0.f, 0.f, 0.f};
+        float4_t d3 = d2;  // (two shorter chains round less)
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.x, bm[0], d1, 0, 0, 0);
+        d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.x, bg.x, d2, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.y, bm[1], d1, 0, 0, 0);
+        d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.y, bg.y, d2, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.z, bm[2], d1, 0, 0, 0);
+        d3 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.z, bg.z, d3, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.w, bm[3], d1, 0, 0, 0);
+        d3 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.w, bg.w, d3, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d2[r] += d3[r];
+      };
+      // row r's sums are added to the wave's rows of their splats: a read, an
+      // add and a write (a float add in the LDS takes 3 cycles a lane, 195 an
+      // instruction; a read and a write 8), the read a step ahead of the
+      // write.  The splats of one row's entries differ, and the wave's LDS
+      // operations run in order.
+      float* const accs = &lds.acc[wv][0][0];
+      const auto place = [&](int r) -> float* {
+        return accs + ((dest[r >> 1] >> (16 * (r & 1))) & 0xFFFFu) + ((slots >> (8 * r)) & 0xFFu);
+      };
+      const auto sum = [&](int r) -> float {
+        return __builtin_amdgcn_inverse_ballot_w64(kBwdColumns.colour[r]) ? d2[r] : d1[r];
+      };
+      // records one list entry ahead of their use, entries two ahead, so a
+      // record's read never waits for the read of its slot
+      const uint8_t* hl = &lds.hits[wv][0][row];
+      int ja = hl[0], jb = hl[4];
+      float sa = lds.rec[ja][lane & 15], sb;
+      bool go = true;
+      for (int t = 0; go; t += 4) {
+        int end = t;
+#pragma unroll
+        for (int st = 0; st < 4; st += 2) {
+          const int jc = hl[4 * (t + st + 2)];
+          sb = lds.rec[jb][lane & 15];
+          float* const pa = place(st);
+          const float xa = *pa;
+          go = step(sa, st, ja);
+          *pa = xa + sum(st);
+          wave_fence();
+          go = ++end < nmax && go;
+          if (!go) break;
+          const int jd = hl[4 * (t + st + 3)];
+          sa = lds.rec[jc][lane & 15];
+          float* const pb = place(st + 1);
+          const float xb = *pb;
+          go = step(sb, st + 1, jb);
+          *pb = xb + sum(st + 1);
+          wave_fence();
+          go = ++end < nmax && go;
+          if (!go) break;
+          ja = jc;
+          jb = jd;
+        }
+        // (after a last group that is not whole: the steps and rows left)
+#pragma unroll
+        for (int st = 1; st < 4; ++st)
+          if (end - t <= st) {
+            fac[64 * st] = fac[256 + 64 * st] = 0.0f;
+            *place(st) += sum(st);
+            wave_fence();
+          }
+        sums(t);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        *place(r) += sum(r);
+        wave_fence();
+      }
+    }
+    __syncthreads();
+    if (mine < m) {
+      // The waves' sums in order; the moments, which were summed without the
+      // opacity and about the quarters' centres, are moved to the tile's, at
+      // (-+4, -+4): with m0, mx, my the zeroth and first ones, x gains cx m0,
+      // x^2 2 cx mx + 16 m0, x y cx my + cy mx + cx cy m0.
+      float pair[2][3] = {};  // the waves' sums by pairs
+      int pt = part;
+      asm volatile("" : "+v"(pt));  // keeps the factors from being held in registers over the batches
+      const float ax = pt == 1 ? 4.0f : 0.0f, ay = pt == 2 ? 4.0f : 0.0f, aq = pt == 3 ? 16.0f : 0.0f;
+      const float bx = pt == 3 ? 8.0f : 0.0f;
+      const float cq = pt == 1 ? 16.0f : 0.0f, cxy = pt == 0 ? 16.0f : 0.0f;
+      const float c4 = pt == 0 ? 4.0f : 0.0f, cy = pt == 1 ? 8.0f : 0.0f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float sx = w & 1 ? 1.0f : -1.0f, sy = w >> 1 ? 1.0f : -1.0f;
+        const float m0 = lds.acc[w][0][mine], mx = lds.acc[w][1][mine], my = lds.acc[w][2][mine];
+        const float x0 = lds.acc[w][part][mine], x1 = lds.acc[w][part + 4][mine];
+        float* const v = pair[w >> 1];
+        v[0] += __builtin_fmaf(sx * bx, mx, __builtin_fmaf(sx * ax + sy * ay + aq, m0, x0));
+        const float x1c =
+            __builtin_fmaf(sx * c4 + sy * cy, my, __builtin_fmaf(sy * c4, mx, __builtin_fmaf(sx * sy * cxy + cq, m0, x1)));
+        v[1] += part < 2 ? x1c : x1;
+        if (part + 8 < NA) v[2] += lds.acc[w][part + 8][mine];
+      }
+      const float out_o = lds.rec[mine][8];  // (staged, and staged anew, by this wave)
+      wave_fence();  // (a slot's four threads are in one wave)
+      float* dst = partial + NP * (int64_t)out;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int c = part + 4 * k;
+        if (c >= NA) break;
+        const float v = pair[0][k] + pair[1][k];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) lds.acc[w][c][mine] = 0.0f;
+        dst[c < 6 ? c : c + 1] = c < 6 ? v * out_o : v;
+        if (c == 0) dst[6] = v;
+      }
+    }
+  }
+  // instances that no pixel of the tile reached
+  for (uint32_t k = b0 + threadIdx.x; k < rg.y; k += 256) {
+    float* dst = partial + NP * (int64_t)ival[k];
+#pragma unroll
+    for (int c = 0; c < NP; ++c) dst[c] = 0.0f;
+  }
+}
+
 // The first kSegmentWgs workgroups take the segments of the long tiles in
 // turn (their number is known on the device only), the others a tile each, in
 // the tile order.
 constexpr int kSegmentWgs = 4096;
 template <int PX, int NP>
-__global__ void __launch_bounds__(256 / PX) k_blend_bwd(const ViewConst* __restrict__ vp,
-                                                        const uint2* __restrict__ ranges,
+__global__ void __launch_bounds__(256 / PX, PX == 1 ? 5 : 1) k_blend_bwd(const ViewConst* __restrict__ vp,
                                                         const uint32_t* __restrict__ ival,
                                                         const uint2* __restrict__ info_k,
                                                         const Splat* __restrict__ splats, const FrameCounters* ctr,
                                                         const float* __restrict__ rgb, const float* __restrict__ dL,
                                                         const uint32_t* __restrict__ event,
-                                                        const uint32_t* __restrict__ tile_order,
-                                                        const uint2* __restrict__ seg_list,
+                                                        const uint4* __restrict__ tile_order,
+                                                        const uint4* __restrict__ seg_list,
                                                         const float4* __restrict__ ckpt, float* __restrict__ partial) {
-  __shared__ BlendBwdLds<PX, NP> lds;
+  __shared__ std::conditional_t<PX == 1, BlocksBwdLds<NP>, BlendBwdLds<PX, NP>> lds;
   const bool segments = blockIdx.x < kSegmentWgs;
   const int end = segments ? ctr->n_seg : (int)gridDim.x - kSegmentWgs;
   const uint32_t nr = (uint32_t)ctr->n_render;
   for (int i = segments ? (int)blockIdx.x : (int)blockIdx.x - kSegmentWgs; i < end; i += kSegmentWgs) {
-    int tile;
-    uint32_t q = 0;
-    if (segments) {
-      const uint2 e = seg_list[i];
-      tile = (int)e.x;
-      q = e.y;
-    } else {
-      tile = (int)tile_order[i];
-    }
-    const uint2 all = ranges[tile];
-    uint2 rg = all;
-    if (segments) {
-      rg.x = all.x + q * kSegment;
-      rg.y = min(all.y, rg.x + kSegment);
-    } else if (all.y - all.x > (uint32_t)kSegment) {
-      return;
-    }
-    blend_bwd_range<PX, NP>(*vp, tile, all.x, rg, ival, info_k, splats, nr, rgb, dL, event, ckpt, partial, lds);
+    const uint4 o = segments ? seg_list[i] : tile_order[i];
+    const uint2 rg = segments ? make_uint2(o.z, o.w) : make_uint2(o.y, o.z);
+    if (!segments && rg.y - rg.x > (uint32_t)kSegment) return;
+    if constexpr (PX == 1)
+      blend_bwd_blocks<NP>(*vp, (int)o.x, o.y, rg, ival, info_k, splats, nr, rgb, dL, event, ckpt, partial, lds);
+    else
+      blend_bwd_range<PX, NP>(*vp, (int)o.x, o.y, rg, ival, info_k, splats, nr, rgb, dL, event, ckpt, partial, lds);
     if (!segments) return;
     __syncthreads();
   }
@@ -907,17 +1277,17 @@ static void launch_blend_bwd_np(lodgs_frame* f, const float* d_dL, hipStream_t s
   const int ntiles = v.tiles_x * v.tiles_y;
   switch (f->blend_px_bwd) {
     case 1:
-      hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(kSegmentWgs + ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<1, NP>), dim3(kSegmentWgs + ntiles), dim3(256), 0, st, f->d_view_ren,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;
     case 4:
-      hipLaunchKernelGGL((k_blend_bwd<4, NP>), dim3(kSegmentWgs + ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<4, NP>), dim3(kSegmentWgs + ntiles), dim3(64), 0, st, f->d_view_ren,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;
     default:
-      hipLaunchKernelGGL((k_blend_bwd<2, NP>), dim3(kSegmentWgs + ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend_bwd<2, NP>), dim3(kSegmentWgs + ntiles), dim3(128), 0, st, f->d_view_ren,
                          f->ival, f->info_k, f->splats, f->ctr, f->r_rgb, d_dL, f->inst_event,
                          f->tile_order, f->seg_list, f->ckpt, f->inst_grad);
       break;

@@ -44,9 +44,8 @@ ViewConst make_view(const lodgs_camera& c, float tau);
 // Returns 0 below -87 and for NaN; clamps the argument at 88.
 // Written with selects rather than branches (same arithmetic on live lanes).
 __device__ __forceinline__ float fexp(float x) {
-  const bool live = x >= -87.0f;  // false for NaN
-  x = x > 88.0f ? 88.0f : x;
-  x = live ? x : 0.0f;
+  const bool live = x >= -87.0f;  // false for NaN; the value below counts only if true
+  x = fminf(x, 88.0f);
   const float n = __builtin_rintf(x * 1.44269502f);
   float r = __builtin_fmaf(-n, 0.693145752f, x);
   r = __builtin_fmaf(-n, 1.42860677e-06f, r);
@@ -289,25 +288,24 @@ __device__ __forceinline__ uint32_t splat_block_mask(const Splat& s, const MaskS
   return cols & rows & (15u * q4);
 }
 
+// The lanes of the wave that pass true (the type's own compare, where
+// __ballot and __any first make an integer of it).
+__device__ __forceinline__ uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool any_lane(bool p) { return ballot(p) != 0ull; }
+
 // Pixel layout of the blend kernels: a 16x16 tile is one workgroup of 4/PX
 // waves, PX pixels per lane, and each 16-lane row g of a wave covers 4x4
 // pixel blocks (lane l its pixel (l & 3, (l >> 2) & 3) of the block): block
 // column bx and, for pixel p, block row by, with
 //   PX = 1: wave w on the 8x8 quarter (w & 1, w >> 1): bx = 2 (w & 1) + (g & 1),
-//           by = 2 (w >> 1) + (g >> 1); or, SPREAD, bx = g, by = (w + g) & 3,
-//           so that every wave has one block in each block row and column (a
-//           band of heavy blocks, such as a horizon, spreads over the waves,
-//           which meet at every batch);
+//           by = 2 (w >> 1) + (g >> 1);
 //   PX = 2: wave w on rows [8 w, 8 w + 8): bx = g, by = 2 w + p;
 //   PX = 4: one wave: bx = g, by = p.
 // Block bits are block_bit(bx, by), as in splat_block_mask, whatever the
 // layout.
-template <int PX, bool SPREAD = false>
+template <int PX>
 __device__ __forceinline__ void blend_block(int wv, int g, int p, int& bx, int& by) {
-  if (PX == 1 && SPREAD) {
-    bx = g;
-    by = (wv + g) & 3;
-  } else if (PX == 1) {
+  if (PX == 1) {
     bx = 2 * (wv & 1) + (g & 1);
     by = 2 * (wv >> 1) + (g >> 1);
   } else if (PX == 2) {
@@ -319,28 +317,28 @@ __device__ __forceinline__ void blend_block(int wv, int g, int p, int& bx, int& 
   }
 }
 
-template <int PX, bool SPREAD = false>
+template <int PX>
 __device__ __forceinline__ void blend_pixel(int tx, int ty, int wv, int lane, int p, int& x, int& y) {
   int bx, by;
-  blend_block<PX, SPREAD>(wv, lane >> 4, p, bx, by);
+  blend_block<PX>(wv, lane >> 4, p, bx, by);
   x = tx * kTile + 4 * bx + (lane & 3);
   y = ty * kTile + 4 * by + ((lane >> 2) & 3);
 }
 
 // Block bit of pixel p of row g of wave w.
-template <int PX, bool SPREAD = false>
+template <int PX>
 __device__ __forceinline__ uint32_t blend_pixel_block(int wv, int g, int p) {
   int bx, by;
-  blend_block<PX, SPREAD>(wv, g, p, bx, by);
+  blend_block<PX>(wv, g, p, bx, by);
   return block_bit(bx, by);
 }
 
 // The blocks that row g of wave w covers.
-template <int PX, bool SPREAD = false>
+template <int PX>
 __device__ __forceinline__ uint32_t blend_row_blocks(int wv, int g) {
   uint32_t m = 0u;
 #pragma unroll
-  for (int p = 0; p < PX; ++p) m |= blend_pixel_block<PX, SPREAD>(wv, g, p);
+  for (int p = 0; p < PX; ++p) m |= blend_pixel_block<PX>(wv, g, p);
   return m;
 }
 

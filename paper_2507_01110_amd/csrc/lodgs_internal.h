@@ -161,13 +161,14 @@ struct lodgs_frame {
                           // clamp bits, 2 unused
   uint32_t* long_list;    // [max_selected] ranks (among the drawn ones) of the splats with many instances
   uint2* ranges;          // [max tiles]
-  uint32_t* tile_order;   // [max tiles] tiles, heaviest class first
+  uint4* tile_order;      // [max tiles] (tile, its range's begin and end, 0), heaviest class first
   uint32_t* tile_count;   // [max tiles] instances of each tile
   uint32_t* tile_cursor;  // [max tiles] next place in each tile's range
   float4* ckpt;           // [max_instances / kSegment + 1][256] (transmittance, 0 if stopped; colour) of the tile's
                           // pixels before the instances from the first place in a segmented tile's list on that
                           // is a multiple of kSegment behind the list's start, by that place / kSegment
-  uint2* seg_list;        // [max_instances / kSegmentHalf + 1] (tile, segment) of the segmented tiles
+  uint4* seg_list;        // [max_instances / kSegmentHalf + 1] segments: (tile, its range's begin, the segment's
+                          // begin and end)
   uint2* big_list;        // [max_instances / kSortChunkHalf + 1] (tile, chunk) of the tiles sorted in chunks
   float spt_scale;        // LoD noise factor on the distances to SPT roots (lodgs_frame_set_lod_noise)
   lodgs::ViewConst* d_view_sel;  // view constants of the last lod_select (device)

@@ -516,7 +516,7 @@ static_assert(kSortSmall == 2 * kSortChunkHalf, "the chunk list's length");
 
 __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __restrict__ count, int32_t ntiles,
                                                              FrameCounters* ctr, uint2* ranges, uint32_t* cursor,
-                                                             uint32_t* order, uint2* seg_list, uint2* big_list) {
+                                                             uint4* order, uint4* seg_list, uint2* big_list) {
   __shared__ uint32_t cnt[kTileClasses], pre[kTileClasses], post[kTileClasses];
   __shared__ uint32_t others[kTileClasses][kClassLanes];  // the other chunks' tiles: low half before, high half after
   __shared__ uint32_t half[2];
@@ -577,7 +577,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 #pragma unroll
   for (int w = 0; w < kOrderThreads / 64; ++w) start += wb[w] + (w < wv ? wt[w] : 0u);
   uint32_t key[kOrderBatch];  // class << 16 | rank within the chunk's class (rank < kOrderChunk)
-  uint32_t big_at[kOrderBatch], seg_at[kOrderBatch];
+  uint32_t big_at[kOrderBatch], seg_at[kOrderBatch], first[kOrderBatch];
   const uint64_t lt = lanemask_lt();
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) {
@@ -593,6 +593,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
       const int32_t tile = lo + k0 + k;
       ranges[tile] = make_uint2(start, start + m[k]);
       cursor[tile] = start;
+      first[k] = start;
       start += m[k];
       key[k] = ((uint32_t)c << 16) | (c == c0 ? base + (uint32_t)__popcll(same & lt) : atomicAdd(&cnt[c], 1u));
       if (m[k] > (uint32_t)kSegment) seg_at[k] = atomicAdd(&seg, (m[k] + kSegment - 1) / kSegment);
@@ -628,13 +629,15 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k)
     if (k0 + k < n) {
-      order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = (uint32_t)(lo + k0 + k);
+      const uint32_t tile = (uint32_t)(lo + k0 + k);
+      order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = make_uint4(tile, first[k], first[k] + m[k], 0u);
       if (m[k] > (uint32_t)kSegment)
         for (uint32_t q = 0; q * kSegment < m[k]; ++q)
-          seg_list[seg_base + seg_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
+          seg_list[seg_base + seg_at[k] + q] =
+              make_uint4(tile, first[k], first[k] + q * kSegment, first[k] + min(m[k], (q + 1) * kSegment));
       if (m[k] > (uint32_t)kSortSmall)
         for (uint32_t q = 0; q * kSortSmall < m[k]; ++q)
-          big_list[big_base + big_at[k] + q] = make_uint2((uint32_t)(lo + k0 + k), q);
+          big_list[big_base + big_at[k] + q] = make_uint2(tile, q);
     }
 }
 
@@ -819,7 +822,7 @@ constexpr int kSmallItems = kSortSmall / kSmallThreads;
 constexpr int kTileSortGrid = 1792;  // seven workgroups per CU: what the registers allow
 
 __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters* ctr, const uint2* __restrict__ ranges,
-                                                             const uint32_t* __restrict__ tile_order,
+                                                             const uint4* __restrict__ tile_order,
                                                              int32_t ntiles, const uint2* __restrict__ big_list,
                                                              unsigned long long* bkey,
                                                              const uint2* __restrict__ inst_info,
@@ -846,7 +849,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters
     if (it >= nm) {  // four tiles of at most 64 instances
       const int32_t at = nm + 4 * (it - nm) + (t >> 6);
       if (at < ntiles) {  // wave-uniform
-        const uint2 rg = ranges[tile_order[at]];
+        const uint4 o = tile_order[at];
+        const uint2 rg = make_uint2(o.y, o.z);
         const int m = (int)(rg.y - rg.x);
         if (m > 0) {
           const uint32_t k = (uint32_t)wave_sort(lane < m ? bkey[rg.x + lane] : ~0ull);
@@ -858,7 +862,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters
       }
       continue;
     }
-    const uint2 rg = ranges[tile_order[it]];
+    const uint4 o = tile_order[it];
+    const uint2 rg = make_uint2(o.y, o.z);
     if (rg.y - rg.x > (uint32_t)kSortSmall) continue;  // listed in chunks
     const int m = (int)(rg.y - rg.x);
     block_sort_small<kSmallThreads>(bkey + rg.x, keys, m);
@@ -945,10 +950,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_merge(const FrameCounter
 // wave-uniform.  The counting variant lists every instance in every row (the
 // algorithmic evaluation count: every splat of the tile up to termination).
 template <bool COUNT, int PX>
-__global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict__ vp, const uint2* __restrict__ ranges,
-                                                    const uint2* __restrict__ info_k,
+__global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict__ vp, const uint2* __restrict__ info_k,
                                                     const Splat* __restrict__ splats, const FrameCounters* ctr,
-                                                    const uint32_t* __restrict__ tile_order, float bg0, float bg1,
+                                                    const uint4* __restrict__ tile_order, float bg0, float bg1,
                                                     float bg2, float* rgb, uint32_t* event, unsigned long long* work,
                                                     float4* ckpt) {
   constexpr int NT = 256 / PX, NW = 4 / PX;
@@ -957,7 +961,8 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   __shared__ uint32_t ev[NT];
   __shared__ uint32_t bm[NT];
   __shared__ uint8_t hits[NW][4][NT];  // per row of each wave: the batch slots it replays, in order
-  const int tile = (int)tile_order[blockIdx.x];
+  const uint4 place = tile_order[blockIdx.x];
+  const int tile = (int)place.x;
   const int tx = tile % v.tiles_x, ty = tile / v.tiles_x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, g = lane >> 4;
   int px, pys[PX];
@@ -975,7 +980,7 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
     cr[p] = cg[p] = cb[p] = 0.0f;
   }
   const float fx = (float)px + 0.5f;
-  const uint2 rg = ranges[tile];
+  const uint2 rg = make_uint2(place.y, place.z);
   const uint32_t nr = (uint32_t)ctr->n_render;
   const float thr = 1.0f / 255.0f;
   unsigned long long n_eval = 0, n_contrib = 0;
@@ -1039,12 +1044,12 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
         cb[p] = con ? __builtin_fmaf(s.b, w, cb[p]) : cb[p];
         T[p] = con ? tt : T[p];
         act = act | live[p];
-        if (!COUNT && ((__ballot(hit) >> (lane & 48)) & 0xFFFFull) != 0ull) eb |= pbit[p];
+        if (!COUNT && ((ballot(hit) >> (lane & 48)) & 0xFFFFull) != 0ull) eb |= pbit[p];
       }
       if (!COUNT && (lane & 15) == 0 && eb != 0u) atomicOr(&ev[j], eb);
-      return !__any(act);
+      return !any_lane(act);
     };
-    if (__any(active) && nmax > 0) {  // wave-uniform
+    if (any_lane(active) && nmax > 0) {  // wave-uniform
       // two register sets, each loaded one list entry ahead of its use
       const uint8_t* hl = hits[wv][g];
       // (an entry is read unconditionally, within the row's NT bytes, and
@@ -1072,7 +1077,7 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
       unsigned long long mine = 0ull;
 #pragma unroll
       for (int b = 0; b < 16; ++b) {
-        const unsigned long long x = __ballot((e >> b) & 1u);
+        const unsigned long long x = ballot(((e >> b) & 1u) != 0u);
         mine = lane == b ? x : mine;
       }
       if (lane < 16 && wv * 64 < m) event_masks(event, rg.x, tile)[16 * ((b0 - rg.x) / 64 + wv) + lane] = mine;
@@ -1166,7 +1171,7 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
   }
   uint32_t b0 = rg.x;
   for (; b0 < rg.y; b0 += 64) {
-    if (!__any(live)) break;  // wave-uniform
+    if (!any_lane(live)) break;  // wave-uniform
     const int m = (int)min(64u, rg.y - b0);
     const bool mine = lane < m && sk0 < nr;
     rec[0][lane] = ra;
@@ -1177,7 +1182,7 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool h = mine && (bk0 & blend_row_blocks<1>(q, r)) != 0u;
-      const uint64_t hb = __ballot(h);
+      const uint64_t hb = ballot(h);
       if (h) hits[r][__popcll(hb & lt)] = (uint8_t)lane;
       nh[r] = __popcll(hb);
     }
@@ -1222,9 +1227,9 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
       cg = con ? __builtin_fmaf(s.g, w, cg) : cg;
       cb = con ? __builtin_fmaf(s.b, w, cb) : cb;
       T = con ? tt : T;
-      const uint64_t hb = __ballot(hit);  // all lanes
+      const uint64_t hb = ballot(hit);  // all lanes
       if ((lane & 15) == 0 && ((hb >> lane) & 0xFFFFull) != 0ull) atomicOr(&evr[j], pbit);
-      return !__any(live);
+      return !any_lane(live);
     };
     if (nmax > 0) {
       const uint8_t* hl = hits[g];
@@ -1255,7 +1260,7 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
     unsigned long long own = 0ull;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const unsigned long long x = __ballot((e >> b) & 1u);
+      const unsigned long long x = ballot(((e >> b) & 1u) != 0u);
       own = lane == b ? x : own;
     }
     if (lane < 4) ev64[16 * ((b0 - rg.x) / 64) + 4 * q + lane] = own;
@@ -1340,10 +1345,10 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
   };
   uint32_t b0 = rg.x;
   for (; b0 < rg.y; b0 += 64) {
-    if (!__any(T > 0.0f)) break;  // wave-uniform
+    if (!any_lane(T > 0.0f)) break;  // wave-uniform
     if (b0 > rg.x && (b0 - rg.x) % kSegment == 0) checkpoint(b0);
     const bool hit0 = mine(w0);
-    const uint64_t hb = __ballot(hit0);
+    const uint64_t hb = ballot(hit0);
     const int h = __popcll(hb), at = __popcll(hb & lt);
     if (hit0) {
       lds.a[at] = ra;
@@ -1380,7 +1385,7 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
       Tb = r >= 2 ? t2 : Tb;
       Tb = r == 3 ? t3 : Tb;
       const bool con = hit & (Tb * own >= 0.0001f);
-      const uint64_t hits = __ballot(hit & (Tb >= 0.0001f));  // (a pixel that had not stopped)
+      const uint64_t hits = ballot(hit & (Tb >= 0.0001f));  // (a pixel that had not stopped)
       rows_of(con ? alpha * Tb : 0.0f, w);
       c = w[0] > 0.0f ? __builtin_fmaf(col.x, w[0], c) : c;
       c = w[1] > 0.0f ? __builtin_fmaf(col.y, w[1], c) : c;
@@ -1389,13 +1394,13 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
       const uint64_t four = ((hits & 0xFFFFull) ? 1ull : 0ull) | ((hits & 0xFFFF0000ull) ? 2ull : 0ull) |
                             ((hits & 0xFFFF00000000ull) ? 4ull : 0ull) | ((hits >> 48) ? 8ull : 0ull);
       evm |= four << s;
-      if (__any((T > 0.0f) & (t4 < 0.0001f))) {  // wave-uniform: a pixel stops at one of the four
+      if (any_lane((T > 0.0f) & (t4 < 0.0001f))) {  // wave-uniform: a pixel stops at one of the four
         float Tl = t1 >= 0.0001f ? t1 : T;
         Tl = t2 >= 0.0001f ? t2 : Tl;
         Tl = t3 >= 0.0001f ? t3 : Tl;
         Tout = ((T > 0.0f) & (t4 < 0.0001f)) ? Tl : Tout;
         T = t4 >= 0.0001f ? t4 : 0.0f;
-        if (!__any(T > 0.0f)) break;
+        if (!any_lane(T > 0.0f)) break;
       } else {
         T = t4;
       }
@@ -1403,7 +1408,7 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
       b = nb;
       o = no;
     }
-    const uint64_t slots = __ballot(hit0 && ((evm >> at) & 1ull) != 0ull);
+    const uint64_t slots = ballot(hit0 && ((evm >> at) & 1ull) != 0ull);
     if (lane == 0) ev64[16 * ((b0 - rg.x) / 64)] = slots;
     __syncthreads();
     w0 = w1;
@@ -1428,9 +1433,9 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
 // instances on, us: 256-instance tiles of a 333 x 171 iteration 67 / 31 / 31 /
 // 38, an aerial 1080p view 63 / 42 / 36 / 48, a street view at 1080p (tiles of
 // up to 9035) 675 / 287 / 256 / 267 and at 4K 313 / 210 / 200 / 198.
-__global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ vp, const uint2* __restrict__ ranges,
+__global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ vp,
                                                   const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
-                                                  const FrameCounters* ctr, const uint32_t* __restrict__ tile_order,
+                                                  const FrameCounters* ctr, const uint4* __restrict__ tile_order,
                                                   int32_t ntiles, float bg0, float bg1, float bg2, float* rgb,
                                                   uint32_t* event, float4* ckpt) {
   __shared__ union {
@@ -1444,8 +1449,8 @@ __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ 
     for (int i = blockIdx.x; i < items; i += kHeavyWgs) {
       const int at = (i >> 7) * 8 + xcd, blk = (i >> 3) & 15;
       if (at >= ctr->n_heavy) continue;
-      const int tile = (int)tile_order[at];
-      blend_block_wave(*vp, tile, blk, ranges[tile], info_k, splats, nr, bg0, bg1, bg2, rgb, event, ckpt,
+      const uint4 o = tile_order[at];
+      blend_block_wave(*vp, (int)o.x, blk, make_uint2(o.y, o.z), info_k, splats, nr, bg0, bg1, bg2, rgb, event, ckpt,
                        lds.block);
       __syncthreads();
     }
@@ -1453,10 +1458,10 @@ __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ 
   }
   const int i = (int)blockIdx.x - kHeavyWgs, at = (i >> 5) * 8 + xcd, q = (i >> 3) & 3;
   if (at >= ntiles) return;
-  const int tile = (int)tile_order[at];
-  const uint2 rg = ranges[tile];
+  const uint4 o = tile_order[at];
+  const uint2 rg = make_uint2(o.y, o.z);
   if (rg.y - rg.x >= (uint32_t)kHeavyTile) return;
-  blend_quarter(*vp, tile, q, rg, info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.quarter);
+  blend_quarter(*vp, (int)o.x, q, rg, info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.quarter);
 }
 
 template <bool COUNT>
@@ -1466,23 +1471,23 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
   uint32_t* event = COUNT ? nullptr : f->inst_event;
   if (!COUNT && f->blend_px_fwd == 1) {
     hipLaunchKernelGGL(k_blend_fwd, dim3(kHeavyWgs + 32 * ((ntiles + 7) / 8)), dim3(64), 0, st, f->d_view_ren,
-                       f->ranges, f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1],
+                       f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1],
                        bg[2], d_rgb, event, f->ckpt);
     return;
   }
   switch (f->blend_px_fwd) {
     case 1:
-      hipLaunchKernelGGL((k_blend<COUNT, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend<COUNT, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work, f->ckpt);
       break;
     case 4:
-      hipLaunchKernelGGL((k_blend<COUNT, 4>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend<COUNT, 4>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work, f->ckpt);
       break;
     default:
-      hipLaunchKernelGGL((k_blend<COUNT, 2>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren, f->ranges,
+      hipLaunchKernelGGL((k_blend<COUNT, 2>), dim3(ntiles), dim3(128), 0, st, f->d_view_ren,
                          f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
                          d_rgb, event, work, f->ckpt);
       break;
@@ -1492,14 +1497,14 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
 int blend_output_arg(const void* func, int* n_args) {
   // k_blend_fwd (..., bg2, rgb, event, ckpt) and k_blend<false, PX> (..., bg2, rgb, event, work, ckpt)
   if (func == reinterpret_cast<const void*>(&k_blend_fwd)) {
-    *n_args = 13;
-    return 10;
+    *n_args = 12;
+    return 9;
   }
   if (func == reinterpret_cast<const void*>(&k_blend<false, 1>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 2>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 4>)) {
-    *n_args = 13;
-    return 9;
+    *n_args = 12;
+    return 8;
   }
   return -1;
 }
