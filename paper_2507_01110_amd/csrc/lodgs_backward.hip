@@ -9,6 +9,7 @@
 // EWA Jacobian, the camera transform, the covariance factorisation, the
 // quaternion normalisation, the sigmoid and the SH basis to the raw
 // parameters.
+#include <algorithm>
 #include <type_traits>
 
 #include "lodgs_internal.h"
@@ -947,102 +948,172 @@ __device__ __forceinline__ void splat_mean64(const Splat* splats, int64_t i, dou
   my = (double)m.z + (double)m.w;
 }
 
-// Splats with more than kLongSegment instances: one workgroup per splat turns
-// its instance partials into the splat's 2D sums (add_instance) in grad2d at
-// its rank among the drawn splats (and its contributing pixels in contrib).  Per-thread FP64 sums over independent unrolled loads, a
-// butterfly over the wave, the waves in order: a fixed order, so
-// deterministic.
-template <int NP>
-__global__ void __launch_bounds__(kBlock) k_long_sums(const FrameCounters* ctr, const uint32_t* long_list,
-                                                      const uint32_t* list,
-                                                      const uint32_t* inst_off, const float* __restrict__ partial,
-                                                      const Splat* __restrict__ splats, const ushort4* rect,
-                                                      double* grad2d, int32_t* contrib) {
-  __shared__ double part[kBlock / 64][10];
-  const int64_t n = ctr->n_drawn, nl = ctr->n_long;
-  const int64_t n_inst = (uint32_t)ctr->n_instances, n_cl = ctr->n_inst_clamped;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int64_t li = blockIdx.x; li < nl; li += gridDim.x) {  // block-uniform
-    const int64_t r = long_list[li];
-    const int64_t i = list[r];
-    const int64_t a0 = inst_off[r];
-    int64_t a = a0, b = r + 1 < n ? (int64_t)inst_off[r + 1] : n_inst;
-    a = a < n_cl ? a : n_cl;
-    b = b < n_cl ? b : n_cl;
-    const ushort4 q = rect[i];
-    double mx, my;
-    splat_mean64(splats, i, mx, my);
-    double g[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t q0 = a + threadIdx.x; q0 < b; q0 += 4 * kBlock) {
-      float t[4][NP];
+// The sum of x over the wave's lanes, in every lane (a fixed order).
+__device__ __forceinline__ double wave_sum64(double x) {
+  const auto halves = [](double v, uint32_t& lo, uint32_t& hi) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    lo = (uint32_t)u;
+    hi = (uint32_t)(u >> 32);
+  };
+  const auto join = [](uint32_t lo, uint32_t hi) { return __longlong_as_double((long long)((uint64_t)hi << 32 | lo)); };
+  uint32_t lo, hi;
+#define LODGS_DPP_ADD(ctrl)                                                                                    \
+  halves(x, lo, hi);                                                                                           \
+  x += join((uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, ctrl, 0xf, 0xf, true),                           \
+            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, ctrl, 0xf, 0xf, true))
+  LODGS_DPP_ADD(0xB1);   // quad_perm [1,0,3,2]
+  LODGS_DPP_ADD(0x4E);   // quad_perm [2,3,0,1]
+  LODGS_DPP_ADD(0x141);  // row_half_mirror
+  LODGS_DPP_ADD(0x140);  // row_mirror
+#undef LODGS_DPP_ADD
+  halves(x, lo, hi);
+  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  x = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+  halves(x, lo, hi);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return join(l32[0], h32[0]) + join(l32[1], h32[1]);
+}
+
+// A drawn splat's instances [a, b) in emission order, of which the first is
+// number a0, its tile rectangle and its mean.
+struct SplatRun {
+  uint32_t a, b, a0;
+  ushort4 q;
+  double mx, my;
+};
+__device__ __forceinline__ SplatRun splat_run(const FrameCounters* ctr, const uint32_t* inst_off, const Splat* splats,
+                                              const ushort4* rect, int64_t r, int64_t i) {
+  const uint32_t n_cl = (uint32_t)ctr->n_inst_clamped;
+  SplatRun s;
+  s.a0 = inst_off[r];
+  s.a = min(s.a0, n_cl);
+  s.b = min(r + 1 < ctr->n_drawn ? inst_off[r + 1] : (uint32_t)ctr->n_instances, n_cl);
+  s.q = rect[i];
+  splat_mean64(splats, i, s.mx, s.my);
+  return s;
+}
+
+// Adds the run's instances from `first` on, every `stride`-th, U loads at a
+// time.
+template <int NP, int U>
+__device__ __forceinline__ void add_run(double* g, const SplatRun& s, const float* __restrict__ partial, uint32_t first,
+                                        uint32_t stride) {
+  for (uint32_t q0 = s.a + first; q0 < s.b; q0 += U * stride) {  // (below 2^31 + 2^13)
+    float t[U][NP];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t k = q0 + (int64_t)u * kBlock;
+    for (int u = 0; u < U; ++u) {
+      const uint32_t k = q0 + u * stride;
 #pragma unroll
-        for (int c = 0; c < NP; ++c) t[u][c] = k < b ? partial[NP * k + c] : 0.0f;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t k = q0 + (int64_t)u * kBlock;
-        if (k < b) add_instance<NP>(g, t[u], (uint32_t)(k - a0), q, mx, my);
-      }
+      for (int c = 0; c < NP; ++c) t[u][c] = k < s.b ? partial[NP * (int64_t)k + c] : 0.0f;
     }
 #pragma unroll
-    for (int c = 0; c < 10; ++c)
-#pragma unroll
-      for (int d = 32; d > 0; d >>= 1) g[c] += __shfl_xor(g[c], d, 64);
-    if (lane == 0) {
-#pragma unroll
-      for (int c = 0; c < 10; ++c) part[wv][c] = g[c];
+    for (int u = 0; u < U; ++u) {
+      const uint32_t k = q0 + u * stride;
+      if (k < s.b) add_instance<NP>(g, t[u], k - s.a0, s.q, s.mx, s.my);
     }
-    __syncthreads();
-    if (threadIdx.x < 10) {
-      double sum = part[0][threadIdx.x];
-#pragma unroll
-      for (int w = 1; w < kBlock / 64; ++w) sum += part[w][threadIdx.x];
-      if (threadIdx.x < 9) grad2d[9 * r + threadIdx.x] = sum;
-      else if (NP == 11) contrib[i] = (int32_t)sum;  // a count, exact in FP64
-    }
-    __syncthreads();
   }
 }
 
-// Every drawn splat that the duplication kernel did not put on the long list
-// (those with more than kLongSegment tiles whose first instance was emitted):
-// one thread per splat, in selection order, so neighbouring threads read
-// neighbouring partials; FP64 sums in instance order (add_instance) into
-// grad2d at the splat's rank among the drawn ones (zero for a splat that an
-// instance overflow left without instances), and its number of contributing
-// pixels into contrib.
+// Every drawn splat's 2D sums from its instance partials (add_instance), into
+// grad2d at its rank among the drawn splats (zero for a splat that an instance
+// overflow left without instances), and its contributing pixels into contrib.
+// FP64 sums in orders that depend on the instance counts alone, so
+// deterministic.  By instances:
+//   up to kLongSegment     one thread, in selection order, so neighbouring
+//                          threads read neighbouring partials;
+//   up to kWaveSums        a wave (these and the longer ones from the list that
+//                          the duplication kernel made of the splats with more
+//                          than kLongSegment tiles whose first instance was
+//                          emitted);
+//   more                   a workgroup.
+// The first kLongWgs workgroups take the list, the others the other splats, at
+// the same time: the loops over one splat's instances are chains of loads.
+// In two launches, with 256 threads for every longer splat, against this, us:
+// 53 / 24 for a 1080p iteration (splats of up to 8160 instances), 90 / 52 for
+// a street view, 86 / 29 a view of a batch, 13 / 8 at 333 x 171.  Several loads
+// at a time in the one-thread loops (25 / 50 / 63 us for one, two, four), or
+// the wave on what has more than 8 or 12 instances, cost more than they hide.
+constexpr int kSumThreads = 512, kLongWgs = 512, kWaveSums = 1024;
 template <int NP>
-__global__ void __launch_bounds__(kBlock) k_splat_sums(const FrameCounters* ctr, const uint32_t* list,
-                                                       const uint32_t* inst_off,
-                                                       const float* __restrict__ partial,
-                                                       const Splat* __restrict__ splats, const ushort4* rect,
-                                                       double* grad2d, int32_t* contrib) {
-  const int64_t n = ctr->n_drawn;
-  const int64_t n_inst = (uint32_t)ctr->n_instances, n_cl = ctr->n_inst_clamped;
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t a0 = inst_off[r];
-    const int64_t i = list[r];
-    const ushort4 q = rect[i];
-    double mx, my;
-    splat_mean64(splats, i, mx, my);
-    if ((uint32_t)(q.y - q.x) * (uint32_t)(q.w - q.z) > kLongSegment && a0 < n_cl) continue;  // k_long_sums
-    int64_t b = r + 1 < n ? (int64_t)inst_off[r + 1] : n_inst;
-    const int64_t a = a0 < n_cl ? a0 : n_cl;
-    b = b < n_cl ? b : n_cl;
-    double g[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t k = a; k < b; ++k) {
-      float t[NP];
+__global__ void __launch_bounds__(kSumThreads) k_splat_sums(const FrameCounters* ctr, const uint32_t* long_list,
+                                                            const uint32_t* list, const uint32_t* inst_off,
+                                                            const float* __restrict__ partial,
+                                                            const Splat* __restrict__ splats, const ushort4* rect,
+                                                            double* grad2d, int32_t* contrib) {
+  constexpr int kWaves = kSumThreads / 64;
+  __shared__ double part[kWaves][10];
+  __shared__ uint32_t giant[kWaves];  // per wave: the splat it leaves to the workgroup
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (blockIdx.x < kLongWgs) {
+    const int64_t nl = ctr->n_long;
+    for (int64_t l0 = blockIdx.x; l0 < nl; l0 += (int64_t)kLongWgs * kWaves) {  // block-uniform
+      const int64_t li = l0 + (int64_t)wv * kLongWgs;
+      uint32_t left = 0xFFFFFFFFu;
+      if (li < nl) {  // wave-uniform
+        const int64_t r = long_list[li], i = list[r];
+        const SplatRun s = splat_run(ctr, inst_off, splats, rect, r, i);
+        if (s.b - s.a > (uint32_t)kWaveSums) {
+          left = (uint32_t)r;
+        } else {
+          double g[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+          add_run<NP, 2>(g, s, partial, lane, 64);
 #pragma unroll
-      for (int c = 0; c < NP; ++c) t[c] = partial[NP * k + c];
-      add_instance<NP>(g, t, (uint32_t)(k - a0), q, mx, my);
+          for (int c = 0; c < NP - 1; ++c) g[c] = wave_sum64(g[c]);
+          if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < 9; ++c) grad2d[9 * r + c] = g[c];
+            if (NP == 11) contrib[i] = (int32_t)g[9];  // a count, exact in FP64
+          }
+        }
+      }
+      if (lane == 0) giant[wv] = left;
+      __syncthreads();
+      for (int w = 0; w < kWaves; ++w) {
+        if (giant[w] == 0xFFFFFFFFu) continue;  // block-uniform
+        const int64_t r = giant[w], i = list[r];
+        const SplatRun s = splat_run(ctr, inst_off, splats, rect, r, i);
+        double g[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        add_run<NP, 2>(g, s, partial, threadIdx.x, kSumThreads);
+#pragma unroll
+        for (int c = 0; c < NP - 1; ++c) {
+          g[c] = wave_sum64(g[c]);
+          if (lane == 0) part[wv][c] = g[c];
+        }
+        __syncthreads();
+        if (threadIdx.x < NP - 1) {
+          double sum = part[0][threadIdx.x];
+#pragma unroll
+          for (int v = 1; v < kWaves; ++v) sum += part[v][threadIdx.x];
+          if (threadIdx.x < 9) grad2d[9 * r + threadIdx.x] = sum;
+          else contrib[i] = (int32_t)sum;
+        }
+        __syncthreads();
+      }
+      __syncthreads();
     }
-    double* dst = grad2d + 9 * r;
+    return;
+  }
+  const int64_t n = ctr->n_drawn;
+  const int64_t r0 = (int64_t)(blockIdx.x - kLongWgs) * kSumThreads + wv * 64;
+  const int64_t step = (int64_t)(gridDim.x - kLongWgs) * kSumThreads;
+  for (int64_t rw = r0; rw < n; rw += step) {  // wave-uniform
+    const int64_t r = rw + lane;
+    const bool in = r < n;
+    const int64_t i = in ? list[r] : 0;
+    SplatRun s = {0, 0, 0, make_ushort4(0, 0, 0, 0), 0.0, 0.0};
+    if (in) s = splat_run(ctr, inst_off, splats, rect, r, i);
+    const bool listed = (uint32_t)(s.q.y - s.q.x) * (uint32_t)(s.q.w - s.q.z) > kLongSegment &&
+                        s.a0 < (uint32_t)ctr->n_inst_clamped;
+    double g[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (in && !listed) add_run<NP, 1>(g, s, partial, 0, 1);
+    if (in && !listed) {
+      double* dst = grad2d + 9 * r;
 #pragma unroll
-    for (int c = 0; c < 9; ++c) dst[c] = g[c];
-    if (NP == 11) contrib[i] = (int32_t)g[9];
+      for (int c = 0; c < 9; ++c) dst[c] = g[c];
+      if (NP == 11) contrib[i] = (int32_t)g[9];
+    }
   }
 }
 
@@ -1250,10 +1321,11 @@ __global__ void __launch_bounds__(kBlock) k_project_bwd(SceneDev S, const ViewCo
 // The per-splat 2D sums of the instance partials (frame-local outputs).
 template <int NP>
 static void launch_splat_sums(lodgs_frame* f, hipStream_t st) {
-  hipLaunchKernelGGL(k_long_sums<NP>, dim3(1024), dim3(kBlock), 0, st, f->ctr, f->long_list, f->drawn_list,
-                     f->inst_off, f->inst_grad, f->splats, f->rect, f->grad2d, f->contrib);
-  hipLaunchKernelGGL(k_splat_sums<NP>, dim3(2048), dim3(kBlock), 0, st, f->ctr, f->drawn_list, f->inst_off,
-                     f->inst_grad, f->splats, f->rect, f->grad2d, f->contrib);
+  // up to half a million threads for the splats that take one each
+  const int64_t wgs = std::min<int64_t>((f->caps.max_selected + kSumThreads - 1) / kSumThreads, 1024);
+  hipLaunchKernelGGL(k_splat_sums<NP>, dim3((uint32_t)(kLongWgs + std::max<int64_t>(wgs, 1))), dim3(kSumThreads), 0, st,
+                     f->ctr, f->long_list, f->drawn_list, f->inst_off, f->inst_grad, f->splats, f->rect, f->grad2d,
+                     f->contrib);
 }
 
 // Colour and projection backward into the gradient arrays (and the node

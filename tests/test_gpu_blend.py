@@ -75,3 +75,10 @@ def test_pixels_that_stop(scene, n, distance):
 def test_segments(scene, n):
     # lists that end at, before and behind the backward's segments of 256
     check(*scene, n, 16, 16)
+
+
+@pytest.mark.parametrize("width,height", [(96, 80), (128, 72), (512, 496), (608, 560), (640, 640)])
+def test_splats_over_many_tiles(scene, width, height):
+    # one splat's instances around a thread's (32), a wave's (1024) and a
+    # workgroup's share, its neighbours with few
+    check(*scene, 40, width, height, 8.0)
