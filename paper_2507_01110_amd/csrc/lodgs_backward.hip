@@ -837,7 +837,7 @@ __device__ __forceinline__ void blend_bwd_blocks(const ViewConst& v, int tile, u
 // the tile order.
 constexpr int kSegmentWgs = 4096;
 template <int PX, int NP>
-__global__ void __launch_bounds__(256 / PX, PX == 1 ? 5 : 1) k_blend_bwd(const ViewConst* __restrict__ vp,
+__global__ void __launch_bounds__(256 / PX, PX == 1 ? (NP == 10 ? 5 : 4) : 1) k_blend_bwd(const ViewConst* __restrict__ vp,
                                                         const uint32_t* __restrict__ ival,
                                                         const uint2* __restrict__ info_k,
                                                         const Splat* __restrict__ splats, const FrameCounters* ctr,
@@ -863,21 +863,25 @@ __global__ void __launch_bounds__(256 / PX, PX == 1 ? 5 : 1) k_blend_bwd(const V
   }
 }
 
-// Projection backward, FP64 (per splat): the forward chain is replayed and the
-// 2D gradients (mean2D, conic, opacity, colour) are carried to the raw
-// parameters.
-// Zeroes the per-selection gradient rows (splats that were not drawn keep 0):
-// each group's rows [0, n_render) are one contiguous span, cleared with
-// consecutive lanes on consecutive words.
-__global__ void __launch_bounds__(kBlock) k_zero_sel(const FrameCounters* ctr, int nc, lodgs_grads sel) {
+// Zeroes the per-selection gradient rows of the selected splats that were not
+// drawn (the others' rows are written whole by the colour and projection
+// backward): 16 lanes take a row.
+template <int NC>
+__device__ __forceinline__ void zero_undrawn(const FrameCounters* ctr, const uint32_t* __restrict__ tiles,
+                                             const lodgs_grads& sel, int64_t group, int64_t groups) {
   const int64_t n = ctr->n_render;
-  float* const arr[5] = {sel.d_means, sel.d_log_scales, sel.d_quats, sel.d_opacity_logits, sel.d_sh};
-  const int w[5] = {3, 3, 4, 1, nc};
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-  for (int g = 0; g < 5; ++g) {
-    float* a = arr[g];
-    if (!a) continue;
-    for (int64_t e = t0; e < n * w[g]; e += stride) a[e] = 0.0f;
+  const int l = threadIdx.x & 15;
+  float* const arr = l < 3 ? sel.d_means : (l < 6 ? sel.d_log_scales : (l < 10 ? sel.d_quats : sel.d_opacity_logits));
+  const int w = l < 6 ? 3 : (l < 10 ? 4 : 1), c = l < 3 ? l : (l < 6 ? l - 3 : (l < 10 ? l - 6 : 0));
+  for (int64_t i = group; i < n; i += groups) {
+    if (tiles[i] != 0u) continue;
+    if (arr && l < 11) arr[w * i + c] = 0.0f;
+    if (!sel.d_sh) continue;
+    if (NC % 4 == 0) {
+      if (l < NC / 4) reinterpret_cast<float4*>(sel.d_sh + NC * i)[l] = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else {
+      for (int k = l; k < NC; k += 16) sel.d_sh[NC * i + k] = 0.0f;
+    }
   }
 }
 
@@ -1127,15 +1131,27 @@ __global__ void __launch_bounds__(kSumThreads) k_splat_sums(const FrameCounters*
 // colour sums in grad2d.  The forward's per-splat record holds the view
 // direction, 1 / distance and the clamp bits, so no node parameter but the
 // coefficients is read.
+// With per-selection rows, kZeroWgs further workgroups clear the rows of the
+// splats that were not drawn (a launch of its own that cleared all rows took
+// 8.8 us for a 1080p iteration and 4.9 at 333 x 171; with it here the kernel
+// takes 16.8 and 6.4, without 9.9 and 4.9).
+constexpr uint32_t kColorBwdWgs = 16384, kZeroWgs = 2048;
 template <int DEG>
 __global__ void __launch_bounds__(kBlock) k_color_bwd(const int32_t* idx, const FrameCounters* ctr,
                                                       const uint32_t* drawn_list, const float* __restrict__ dcol,
-                                                      double* grad2d, float* sel_sh, float* node_sh) {
+                                                      double* grad2d, lodgs_grads sel, float* node_sh,
+                                                      const uint32_t* __restrict__ tiles) {
   constexpr int nb = (DEG + 1) * (DEG + 1), nc = 3 * nb;
+  if (blockIdx.x >= kColorBwdWgs) {  // block-uniform
+    zero_undrawn<nc>(ctr, tiles, sel, (int64_t)(blockIdx.x - kColorBwdWgs) * (kBlock / 16) + (threadIdx.x >> 4),
+                     (int64_t)(gridDim.x - kColorBwdWgs) * (kBlock / 16));
+    return;
+  }
+  float* const sel_sh = sel.d_sh;
   const int64_t n = ctr->n_drawn;
   const int lane = threadIdx.x & 63, sub = lane & 15;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int64_t waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+  const int64_t waves = ((int64_t)kColorBwdWgs * blockDim.x) >> 6;
   for (int64_t g0 = wave * 4; g0 < n; g0 += waves * 4) {  // wave-uniform
     const int64_t dr = g0 + (lane >> 4);  // drawn rank
     if (dr >= n) continue;
@@ -1207,6 +1223,9 @@ __global__ void __launch_bounds__(kBlock) k_color_bwd(const int32_t* idx, const 
 // the 2D gradients of grad2d[r] are carried to the mean, scales, rotation and
 // opacity logit; grad2d[r][6..8] already holds dL/dmean through the view
 // direction.
+// Projection backward, FP64 (per splat): the forward chain is replayed and the
+// 2D gradients (mean2D, conic, opacity, colour) are carried to the raw
+// parameters.
 template <int DEG>
 __global__ void __launch_bounds__(kBlock) k_project_bwd(SceneDev S, const ViewConst* __restrict__ vp, const int32_t* idx,
                                                         const FrameCounters* ctr, const uint32_t* drawn_list,
@@ -1335,8 +1354,9 @@ static void launch_scatter_deg(const SceneDev& S, lodgs_frame* f, const lodgs_gr
                                bool contrib, hipStream_t st) {
   // 16 lanes per splat: one pass covers 256k drawn splats, so each 16-lane
   // group runs its latency-bound chain of dependent loads once
-  hipLaunchKernelGGL(k_color_bwd<DEG>, dim3(16384), dim3(kBlock), 0, st, f->r_idx, f->ctr, f->drawn_list, f->dcol,
-                     f->grad2d, sel.d_sh, nodes.d_sh);
+  const bool rows = sel.d_means || sel.d_log_scales || sel.d_quats || sel.d_opacity_logits || sel.d_sh;
+  hipLaunchKernelGGL(k_color_bwd<DEG>, dim3(kColorBwdWgs + (rows ? kZeroWgs : 0)), dim3(kBlock), 0, st, f->r_idx, f->ctr,
+                     f->drawn_list, f->dcol, f->grad2d, sel, nodes.d_sh, f->tiles);
   ContribStats cs{f->contrib, nullptr, nullptr, nullptr};
   if (contrib) cs = ContribStats{f->contrib, f->last_contrib, f->contrib_count, f->contrib_iteration};
   hipLaunchKernelGGL(k_project_bwd<DEG>, dim3(1024), dim3(kBlock), 0, st, S, f->d_view_ren, f->r_idx, f->ctr,
@@ -1392,7 +1412,6 @@ void launch_backward(lodgs_frame* f, const float* d_dL, const lodgs_grads* sel, 
     const SceneDev& S = render_params(f);
     const bool contrib = f->partials_np == kPartial && f->last_contrib;
     lodgs_grads none{nullptr, nullptr, nullptr, nullptr, nullptr};
-    if (sel) hipLaunchKernelGGL(k_zero_sel, dim3(1024), dim3(kBlock), 0, st, f->ctr, S.n_coef, *sel);
     const lodgs_grads gs = sel ? *sel : none, gn = nodes ? *nodes : none;
     switch (S.sh_degree) {
       case 0: launch_scatter_deg<0>(S, f, gs, gn, contrib, st); break;

@@ -82,3 +82,32 @@ def test_splats_over_many_tiles(scene, width, height):
     # one splat's instances around a thread's (32), a wave's (1024) and a
     # workgroup's share, its neighbours with few
     check(*scene, 40, width, height, 8.0)
+
+
+@pytest.mark.parametrize("degree", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 700])
+def test_rows_of_splats_that_were_not_drawn(degree, n):
+    # selection-indexed gradients: rows hold whatever they held before, some of
+    # the splats lie behind the camera
+    import torch
+    from paper_2507_01110_amd.lodgs import Frame, Scene, grads_like
+    tree = scenegen.build_tree(configs.tiny_spec(n=2000, seed=3, sh_degree=degree))
+    S = Scene(tree)
+    cam = scenegen.camera_look_at((0.5, 0.2, 0.3), (4.0, 1.0, 2.0), (0.0, 0.0, 1.0), 64, 48)
+    positions = np.arange(n) * (S.n_nodes // n)
+    F = oracle.OracleFrame(tree, S.perm[positions].astype(np.int32), cam)
+    dL = np.random.default_rng(n).standard_normal((48, 64, 3)).astype(np.float32)
+    _, g_o = F.backward(dL.astype(np.float64))
+    f = Frame(S, n, 1 << 20, 64, 48)
+    print("rows", degree, n, F.info()["n_visible"], flush=True)
+    f.render(cam, idx=torch.from_numpy(np.ascontiguousarray(positions, np.int32)).cuda(),
+             count=torch.tensor([n], dtype=torch.int32, device="cuda"))
+    sel = grads_like(S, n, zero=False)
+    for t in sel.values():
+        t.fill_(float("nan"))
+    f.backward(torch.from_numpy(dL).cuda(), sel=sel)
+    got = np.concatenate([sel[k].reshape(n, -1).cpu().numpy().astype(np.float64) for k in GROUPS], axis=1)
+    none = ~np.any(g_o, axis=1)
+    assert not np.any(got[none])
+    for k, s in GROUPS.items():
+        assert np.linalg.norm(got[:, s] - g_o[:, s]) <= 1e-3 * max(np.linalg.norm(g_o[:, s]), 1e-12), k
