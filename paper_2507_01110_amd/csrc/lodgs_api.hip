@@ -80,7 +80,7 @@ void stage_end(lodgs_frame* f, hipStream_t st) {
 
 namespace {
 __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                           int64_t cap, uint32_t* tile_count) {
+                           int64_t cap, uint32_t* tile_count, unsigned long long* run_sums) {
   int64_t n = 0;
   if (mode == kViewRender) {
     n = *d_count;
@@ -88,6 +88,7 @@ __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int 
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t ntiles = (int64_t)v.tiles_x * v.tiles_y;
     for (int64_t i = t0; i < ntiles; i += stride) tile_count[i] = 0u;
+    for (int64_t i = t0; i * kDrawnRun < n; i += stride) run_sums[i] = 0ull;
     if (t0 != 0) return;
   }
   *dst = v;
@@ -107,10 +108,10 @@ __global__ void k_set_view(ViewConst v, ViewConst* dst, FrameCounters* ctr, int 
 }  // namespace
 
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, uint32_t* tile_count, hipStream_t st) {
+                     int64_t cap, uint32_t* tile_count, unsigned long long* run_sums, hipStream_t st) {
   // a render's clearing: a few thousand words, spread over 32 workgroups
   const int grid = mode == kViewRender ? 32 : 1, block = mode == kViewRender ? kBlock : 1;
-  hipLaunchKernelGGL(k_set_view, dim3(grid), dim3(block), 0, st, v, dst, ctr, mode, d_count, cap, tile_count);
+  hipLaunchKernelGGL(k_set_view, dim3(grid), dim3(block), 0, st, v, dst, ctr, mode, d_count, cap, tile_count, run_sums);
 }
 
 void launch_blend_count(lodgs_frame* f, hipStream_t st);
@@ -601,7 +602,7 @@ struct lodgs_graph {
 namespace lodgs {
 
 // Arguments of the kernels that take a captured graph's views.
-constexpr int kSelectBeginArgs = 6, kSetViewArgs = 7;
+constexpr int kSelectBeginArgs = 6, kSetViewArgs = 8;
 
 // Replaces argument `arg` of a captured kernel node (nargs arguments) by the
 // pointer value v.

@@ -95,6 +95,11 @@ int build_spt_radius(lodgs_scene* s);
 }  // namespace lodgs
 
 // Device counters of a frame (one struct in device memory).
+// Selection positions of one sum that the projection leaves for the drawn
+// scan: 64 (a wave stores its own) up to kDrawnWide positions, kDrawnRun (waves
+// add up) beyond, where every workgroup of the scan would read too many.
+constexpr int64_t kDrawnRun = 2048, kDrawnWide = 524288;
+
 struct FrameCounters {
   int32_t status;
   int32_t n_selected;
@@ -143,7 +148,8 @@ struct lodgs_frame {
   lodgs::Splat* splats;   // [max_selected]
   uint32_t* depth_key;    // [max_selected]
   uint32_t* tiles;        // [max_selected]
-  uint2* wave_sums;       // [ceil(max_selected / 64)] per 64 selection positions: tile count, drawn splats
+  uint2* wave_sums;       // [ceil(kDrawnWide / 64)] up to kDrawnWide positions: per 64, tile count and drawn splats
+  unsigned long long* run_sums;  // [ceil(max_selected / kDrawnRun)] beyond: per kDrawnRun, tile count, drawn splats << 32
   uint32_t* inst_off;     // [max_selected] first instance of each drawn splat (selection order)
   uint32_t* chunk_first;  // [max_instances / 64 + 1] rank of the splat holding each 64-instance chunk's first
   uint32_t* drawn_list;   // [max_selected] selection positions of the drawn splats (selection order)
@@ -295,7 +301,7 @@ constexpr int kViewOnly = 0, kViewSelect = 1, kViewRender = 2;
 __global__ void k_select_begin(ViewConst v, ViewConst* dst, FrameCounters* ctr, SceneDev S, uint32_t flags,
                                uint8_t* utest);
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,
-                     int64_t cap, uint32_t* tile_count, hipStream_t st);
+                     int64_t cap, uint32_t* tile_count, unsigned long long* run_sums, hipStream_t st);
 
 int hip_fail(hipError_t e, const char* what);
 
@@ -372,7 +378,8 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->splats, ns);
   fn(f->depth_key, ns);
   fn(f->tiles, ns);
-  fn(f->wave_sums, (ns + 63) / 64);
+  fn(f->wave_sums, ((ns < (size_t)kDrawnWide ? ns : (size_t)kDrawnWide) + 63) / 64);
+  fn(f->run_sums, (ns + kDrawnRun - 1) / kDrawnRun);
   fn(f->inst_off, ns);
   fn(f->chunk_first, ni / 64 + 1);
   fn(f->drawn_list, ns);

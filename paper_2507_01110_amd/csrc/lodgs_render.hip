@@ -163,7 +163,8 @@ template <int DEG>
 __global__ void __launch_bounds__(kBlock, 3) k_project(SceneDev S, const ViewConst* __restrict__ vp, const int32_t* idx,
                                                     const int32_t* d_count, int64_t cap, Splat* splats,
                                                     uint32_t* depth_key, uint32_t* tiles, ushort4* rect,
-                                                    float* dcol, uint2* wave_sums) {
+                                                    float* dcol, uint2* wave_sums,
+                                                    unsigned long long* run_sums) {
   const ViewConst v = *vp;
   const int64_t n = clamp_count(d_count, cap);
   const int lane = threadIdx.x & 63;
@@ -197,7 +198,10 @@ __global__ void __launch_bounds__(kBlock, 3) k_project(SceneDev S, const ViewCon
     const uint32_t drawn = (uint32_t)__popcll(__ballot(t != 0u));
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) t += __shfl_xor(t, d, 64);  // (a splat has at most 2^20 tiles)
-    if (lane == 0) wave_sums[i0 >> 6] = make_uint2(t, drawn);
+    if (lane == 0) {
+      if (n <= kDrawnWide) wave_sums[i0 >> 6] = make_uint2(t, drawn);
+      else if (drawn != 0u) atomicAdd(&run_sums[i0 / kDrawnRun], (unsigned long long)drawn << 32 | t);
+    }
   }
 }
 
@@ -206,43 +210,49 @@ __global__ void __launch_bounds__(kBlock, 3) k_project(SceneDev S, const ViewCon
 // position as its place in the list of drawn positions and the index of its
 // first instance, and for each 64-instance chunk the rank of the splat that
 // holds its first instance (k_dup's chunks).  A workgroup takes a tile of 2
-// positions per thread (8 above kDrawnWide) and adds up the projection's sums
-// of all positions before it itself, so none waits for another (look-back over
-// tiles numbered by ticket: 6.2 us at 170K positions, 16 at 1.5M).
+// positions per thread and adds up the projection's sums of all positions
+// before it itself, so none waits for another (look-back over tiles numbered
+// by ticket: 6.2 us at 170K positions, 16 at 1.5M).  Above kDrawnWide they are
+// sums of 2048 positions, which the projection's waves make with atomics (2 us
+// of a small view's projection, so not below): 12.8 us for a street view with
+// 0.95M drawn splats, where sums of 64 and 8 positions a thread took 16.2.
 constexpr int kDrawnThreads = 1024;
-constexpr int64_t kDrawnWide = 524288;
+constexpr int kDrawnItems = 2;
+static_assert(kDrawnThreads * kDrawnItems == kDrawnRun, "a tile is a run");
 
-template <int ITEMS>
 __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, const uint2* __restrict__ wave_sums,
-                                           int64_t n, int64_t tile, bool last, FrameCounters* ctr, uint32_t* list,
-                                           uint32_t* off, uint32_t* chunk_first, int64_t chunks,
-                                           uint32_t (*wt)[kDrawnThreads / 64]) {
+                                           const unsigned long long* __restrict__ run_sums, int64_t n, int64_t tile,
+                                           bool last, FrameCounters* ctr, uint32_t* list, uint32_t* off,
+                                           uint32_t* chunk_first, int64_t chunks, uint32_t (*wt)[kDrawnThreads / 64]) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t i0 = (tile * kDrawnThreads + t) * ITEMS;
-  uint32_t v[ITEMS];
-  if (i0 + ITEMS <= n) {
-    if (ITEMS == 8) {
-      const uint4 a = *reinterpret_cast<const uint4*>(tiles + i0), b = *reinterpret_cast<const uint4*>(tiles + i0 + 4);
-      v[0] = a.x; v[1] = a.y; v[2 % ITEMS] = a.z; v[3 % ITEMS] = a.w;
-      v[4 % ITEMS] = b.x; v[5 % ITEMS] = b.y; v[6 % ITEMS] = b.z; v[7 % ITEMS] = b.w;
-    } else {
-      const uint2 a = *reinterpret_cast<const uint2*>(tiles + i0);
-      v[0] = a.x; v[1] = a.y;
-    }
+  const int64_t i0 = (tile * kDrawnThreads + t) * kDrawnItems;
+  uint32_t v[kDrawnItems];
+  if (i0 + kDrawnItems <= n) {
+    const uint2 a = *reinterpret_cast<const uint2*>(tiles + i0);
+    v[0] = a.x; v[1] = a.y;
   } else {
 #pragma unroll
-    for (int k = 0; k < ITEMS; ++k) v[k] = i0 + k < n ? tiles[i0 + k] : 0u;
+    for (int k = 0; k < kDrawnItems; ++k) v[k] = i0 + k < n ? tiles[i0 + k] : 0u;
   }
   uint32_t bc = 0, bd = 0;  // this thread's part of the positions before the tile
+  if (n <= kDrawnWide) {
 #pragma unroll 4
-  for (int64_t i = t; i < tile * (kDrawnThreads * ITEMS / 64); i += kDrawnThreads) {
-    const uint2 a = wave_sums[i];
-    bc = add_sat(bc, a.x);
-    bd += a.y;
+    for (int64_t i = t; i < tile * (kDrawnRun / 64); i += kDrawnThreads) {
+      const uint2 a = wave_sums[i];
+      bc = add_sat(bc, a.x);
+      bd += a.y;
+    }
+  } else {
+#pragma unroll 4
+    for (int64_t i = t; i < tile; i += kDrawnThreads) {
+      const unsigned long long a = run_sums[i];
+      bc = add_sat(bc, (uint32_t)a);
+      bd += (uint32_t)(a >> 32);
+    }
   }
   uint32_t c = 0, d = 0;
 #pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
+  for (int k = 0; k < kDrawnItems; ++k) {
     c += v[k];
     d += v[k] != 0u ? 1u : 0u;
   }
@@ -284,7 +294,7 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, c
   od += pd;
   oc = add_sat(oc, pc);
 #pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
+  for (int k = 0; k < kDrawnItems; ++k) {
     const uint32_t end = add_sat(oc, v[k]);
     uint32_t ch = 0, ch_end = 0;  // the chunks that start in [oc, end)
     if (v[k] != 0u) {
@@ -308,17 +318,15 @@ __device__ __forceinline__ void drawn_tile(const uint32_t* __restrict__ tiles, c
 }
 
 __global__ void __launch_bounds__(kDrawnThreads) k_drawn_scan(const uint32_t* __restrict__ tiles,
-                                                              const uint2* __restrict__ wave_sums, FrameCounters* ctr,
-                                                              uint32_t* list, uint32_t* off, uint32_t* chunk_first,
-                                                              int64_t icap) {
+                                                              const uint2* __restrict__ wave_sums,
+                                                              const unsigned long long* __restrict__ run_sums,
+                                                              FrameCounters* ctr, uint32_t* list, uint32_t* off,
+                                                              uint32_t* chunk_first, int64_t icap) {
   __shared__ uint32_t wt[4][kDrawnThreads / 64];
   const int64_t n = ctr->n_render, chunks = (icap + 63) / 64;
-  const bool wide = n > kDrawnWide;
-  const int64_t per = wide ? 8 * kDrawnThreads : 2 * kDrawnThreads, ntiles = (n + per - 1) / per;
+  const int64_t ntiles = (n + kDrawnRun - 1) / kDrawnRun;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {  // block-uniform
-    const bool last = tile == ntiles - 1;
-    if (wide) drawn_tile<8>(tiles, wave_sums, n, tile, last, ctr, list, off, chunk_first, chunks, wt);
-    else drawn_tile<2>(tiles, wave_sums, n, tile, last, ctr, list, off, chunk_first, chunks, wt);
+    drawn_tile(tiles, wave_sums, run_sums, n, tile, tile == ntiles - 1, ctr, list, off, chunk_first, chunks, wt);
     __syncthreads();
   }
 }
@@ -1524,12 +1532,13 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   const SceneDev& S = render_params(f);
   const int64_t cap = f->caps.max_selected, icap = f->caps.max_instances;
   stage_begin(f, LODGS_STAGE_PROJECT, st);
-  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, f->tile_count, st);
+  launch_set_view(v, f->d_view_ren, f->ctr, kViewRender, d_count, cap, f->tile_count, f->run_sums, st);
   const int pgrid = 2048;
   switch (S.sh_degree) {
 #define LODGS_PROJECT(D)                                                                                         \
   hipLaunchKernelGGL(k_project<D>, dim3(pgrid), dim3(kBlock), 0, st, S, f->d_view_ren, d_idx, d_count, cap,   \
-                     f->splats, f->depth_key, f->tiles, f->rect, f->dcol, f->wave_sums)
+                     f->splats, f->depth_key, f->tiles, f->rect, f->dcol, f->wave_sums,        \
+                     f->run_sums)
     case 0: LODGS_PROJECT(0); break;
     case 1: LODGS_PROJECT(1); break;
     case 2: LODGS_PROJECT(2); break;
@@ -1539,7 +1548,7 @@ void launch_render(lodgs_frame* f, const int32_t* d_idx, const int32_t* d_count,
   stage_end(f, st);
   const int ntiles = v.tiles_x * v.tiles_y;
   stage_begin(f, LODGS_STAGE_DUPLICATE, st);
-  hipLaunchKernelGGL(k_drawn_scan, dim3(512), dim3(kDrawnThreads), 0, st, f->tiles, f->wave_sums, f->ctr, f->drawn_list,
+  hipLaunchKernelGGL(k_drawn_scan, dim3(512), dim3(kDrawnThreads), 0, st, f->tiles, f->wave_sums, f->run_sums, f->ctr, f->drawn_list,
                      f->inst_off, f->chunk_first, icap);
   const int32_t dup_lds = ntiles <= kLdsTiles ? ntiles : 0;
   hipLaunchKernelGGL(k_dup, dim3(kDupGrid), dim3(kDupThreads), 4 * ((dup_lds + 1) / 2), st, f->ctr, f->drawn_list,

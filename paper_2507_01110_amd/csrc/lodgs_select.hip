@@ -655,7 +655,7 @@ void launch_select_full(lodgs_frame* f, const ViewConst& v, uint32_t flags, int3
   const bool bfs = (flags & LODGS_CUT_BFS) != 0;
   const int64_t n_words = cut_bit_words(S.n_nodes);
   stage_begin(f, LODGS_STAGE_SELECT, st);
-  launch_set_view(v, f->d_view_sel, f->ctr, kViewSelect, nullptr, 0, nullptr, st);
+  launch_set_view(v, f->d_view_sel, f->ctr, kViewSelect, nullptr, 0, nullptr, nullptr, st);
   int cgrid = (int)((n_words + kBlock - 1) / kBlock);
   cgrid = cgrid < 1 ? 1 : (cgrid > 2048 ? 2048 : cgrid);
   hipLaunchKernelGGL(k_cut_clear, dim3(cgrid), dim3(kBlock), 0, st, f->cut_bits, n_words,
