@@ -327,6 +327,12 @@ int lodgs_frame_create(const lodgs_scene* scene, const lodgs_frame_caps* caps, l
     (void)hipGetLastError();
     return set_error(LODGS_E_OOM, "lodgs_frame_create: device allocation failed");
   }
+  // what a render keeps per instance in emission order is its own, the gradient
+  // partials are a backward's, which follows it: they share memory
+  static_assert(sizeof(float) * lodgs::kPartial >= 2 * sizeof(uint2) + sizeof(unsigned long long), "they fit");
+  f->inst_key = reinterpret_cast<uint2*>(f->inst_grad);
+  f->inst_info = f->inst_key + caps->max_instances;
+  f->bucket_key = reinterpret_cast<unsigned long long*>(f->inst_info + caps->max_instances);
   const SceneDev& S = scene->dev;
   const size_t ns = (size_t)caps->max_selected;
   FrameCounters c;

@@ -90,6 +90,7 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // rows in order and writes one NP-float partial per (splat, tile) instance at
 // the instance's emission index, with zeros for instances that no pixel
 // reached.  No order depends on timing: the result is deterministic.
+
 // LDS of a workgroup of the blend backward.
 template <int PX, int NP>
 struct BlendBwdLds {

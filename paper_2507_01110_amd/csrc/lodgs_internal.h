@@ -154,9 +154,9 @@ struct lodgs_frame {
   uint32_t* chunk_first;  // [max_instances / 64 + 1] rank of the splat holding each 64-instance chunk's first
   uint32_t* drawn_list;   // [max_selected] selection positions of the drawn splats (selection order)
   ushort4* rect;          // [max_selected]
-  uint2* inst_key;        // [max_instances] (tile, depth bits) in emission order
-  uint2* inst_info;       // [max_instances] (selection position of the splat, block mask), emission order
-  unsigned long long* bucket_key;  // [max_instances] (depth bits << 32 | emission index) by tile
+  uint2* inst_key;        // [max_instances] (tile, depth bits) in emission order (in inst_grad's memory)
+  uint2* inst_info;       // [max_instances] (selection position of the splat, block mask), emission order (likewise)
+  unsigned long long* bucket_key;  // [max_instances] (depth bits << 32 | emission index) by tile (likewise)
   uint32_t* ival;         // [max_instances] emission index of each instance, in (tile, depth) order
   uint2* info_k;          // [max_instances] the instances' words in that order
   float* inst_grad;       // [max_instances][kPartial] per-instance partials (emission order)
@@ -384,9 +384,6 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->chunk_first, ni / 64 + 1);
   fn(f->drawn_list, ns);
   fn(f->rect, ns);
-  fn(f->inst_key, ni);
-  fn(f->inst_info, ni);
-  fn(f->bucket_key, ni);
   fn(f->ival, ni);
   fn(f->info_k, ni);
   fn(f->inst_grad, (size_t)kPartial * ni);

@@ -21,10 +21,11 @@
 //             launches (82 of a 512 x 512 view's 164 us; 288 us of a street
 //             view with 0.95M drawn splats and 2.1M instances), the five
 //             kernels above take 24 and 160 us there.
-//  k_blend    one workgroup per tile, PX pixels per lane; splat records are
-//             staged in LDS one batch per workgroup size; each 16-lane row
-//             (4x4 pixel blocks) replays only the splats whose alpha >= 1/255
-//             ellipse reaches one of its blocks (elsewhere the result is known).
+//  k_blend_fwd  a wave per 8x8 quarter or per 4x4 block of a tile; k_blend is
+//             its general form, one workgroup per tile with PX pixels per
+//             lane, and the evaluation count.  A 4x4 block replays only the
+//             splats whose alpha >= 1/255 ellipse reaches it (elsewhere the
+//             result is known).
 #include "lodgs_internal.h"
 #include "lodgs_proj.h"
 
@@ -948,9 +949,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_merge(const FrameCounter
 // instances, every row lists the instances whose block mask (k_dup) meets
 // its blocks and replays only those, in order: elsewhere alpha < 1/255 at
 // every pixel.  The rows of a wave step through their lists together, each on
-// its own splat.  For every instance that it replays, the forward records in
-// event[k] the blocks where some pixel blended the splat or stopped on it;
-// elsewhere the splat changed nothing, which lets the backward skip it there.
+// its own splat.  The forward records the blocks where some pixel blended an
+// instance or stopped on it (event_masks); elsewhere the splat changed
+// nothing, which lets the backward skip it there.
 // alpha = min(0.99, o e^power), skipped below 1/255; a pixel stops before its
 // transmittance would drop below 1e-4.  Splat records are staged in LDS one
 // batch per workgroup size and read into registers one list entry ahead; the
