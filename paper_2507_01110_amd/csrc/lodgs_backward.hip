@@ -607,6 +607,10 @@ __device__ __forceinline__ void blend_bwd_blocks(const ViewConst& v, int tile, u
       GQ = __builtin_fmaf(G2, s.w, __builtin_fmaf(G1, s.z, G0 * s.y));
     }
   }
+  // A splat that only stops pixels of a block has weights of 0 there, and 0
+  // times a derivative that is not finite is not 0: then its sums go to a slot
+  // past the batch.
+  const bool odd = any_lane(!((G0 - G0) + (G1 - G1) + (G2 - G2) == 0.0f));
   for (int t = threadIdx.x; t < (int)(sizeof lds.acc / sizeof(float)); t += 256) (&lds.acc[0][0][0])[t] = 0.0f;
   if (threadIdx.x < 64) lds.rec[NB + row][lane & 15] = 0.0f;
   // the right operands (this lane: column lane & 15, pixels (m, row) of the
@@ -712,6 +716,14 @@ __device__ __forceinline__ void blend_bwd_blocks(const ViewConst& v, int tile, u
         wave_fence();
         const float4 ao = lds.fac[wv][0][4 * (lane & 15) + row], aw = lds.fac[wv][1][4 * (lane & 15) + row];
         const float4 bg = lds.grad[wv][lane];
+        if (odd) {  // wave-uniform; bit 4 step + row of `some`: the splat has a weight
+          uint64_t some = ballot((aw.x != 0.0f) | (aw.y != 0.0f) | (aw.z != 0.0f) | (aw.w != 0.0f));
+          some |= some >> 32;
+          some |= some >> 16;
+          if (lane < 16 && ((some >> lane) & 1ull) == 0ull)
+            lds.hits[wv][t + (lane >> 2)][lane & 3] = (uint8_t)(NB + (lane >> 2));
+          wave_fence();
+        }
         slots = *reinterpret_cast<const uint32_t*>(&lds.hits[wv][t + row][0]);
         d1 = d2 = float4_t{0.f, 0.f, 0.f, 0.f};
         float4_t d3 = d2;  // (two shorter chains round less)
