@@ -339,6 +339,7 @@ int lodgs_frame_create(const lodgs_scene* scene, const lodgs_frame_caps* caps, l
   std::memset(&c, 0, sizeof c);
   c.spt_count = S.n_spt;
   c.n_bit_words = (int32_t)lodgs::cut_bit_words(S.n_nodes);
+  c.n_cut_tiles = (int32_t)lodgs::cut_tiles(S);
   e = hipMemcpy(f->ctr, &c, sizeof c, hipMemcpyHostToDevice);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_iota, dim3(1024), dim3(256), 0, 0, f->iota, (int64_t)ns);

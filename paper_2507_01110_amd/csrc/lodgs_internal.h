@@ -112,7 +112,7 @@ struct FrameCounters {
   int32_t n_inst_clamped;
   int32_t n_chunks;      // SPT candidate chunks of the last select
   int32_t n_bit_words;   // constant: words of the comparator cuts' node bitmask
-  int32_t upper_plus_high;
+  int32_t n_cut_tiles;   // constant: cut_tiles
   int32_t spt_count;     // constant n_spt
   int32_t n_long;        // drawn splats with more than kLongSegment instances
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
@@ -139,6 +139,8 @@ struct lodgs_frame {
   uint32_t* cut_first;    // [cut_tiles] first chunk of each SPT tile
   int2* cut_chunks;       // [cut_chunks] first node, SPT
   uint16_t* chunk_count;  // [cut_chunks] selected nodes
+  uint32_t* cut_runs;     // [kCutRuns] selected nodes of each run of chunks
+  uint32_t* cut_place;    // [cut_tiles, if above kWideTiles] selected nodes before each tile
   // comparator cuts (allocated when the scene has its hierarchy attached)
   uint32_t* cut_bits;     // [n_bit_words] one bit per node, selected
   int32_t* frontier[2];   // [max_selected] BFS frontiers (ping-pong)
@@ -251,6 +253,11 @@ constexpr int kCutTile = 256;
 inline int64_t upper_tiles(const SceneDev& S) { return ((int64_t)S.n_upper + kCutTile - 1) / kCutTile; }
 inline int64_t cut_tiles(const SceneDev& S) { return upper_tiles(S) + ((int64_t)S.n_spt + kCutTile - 1) / kCutTile; }
 inline int64_t cut_chunks(const SceneDev& S) { return (int64_t)S.n_spt + S.n_nodes / 512 + 1; }
+// Runs that the chunks are taken in, a wave each, and the tiles above which
+// their counts are scanned in launches of their own.
+constexpr int kCutRuns = 4096;
+constexpr int64_t kWideTiles = 1024;
+inline int64_t cut_places(const SceneDev& S) { return cut_tiles(S) > kWideTiles ? cut_tiles(S) : 0; }
 
 // The tile order's chunks (k_tile_scan): as many as keep a chunk to
 // kOrderChunk tiles, of equal size but for the last.
@@ -375,6 +382,8 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->cut_first, (size_t)cut_tiles(S));
   fn(f->cut_chunks, (size_t)cut_chunks(S));
   fn(f->chunk_count, (size_t)cut_chunks(S));
+  fn(f->cut_runs, (size_t)kCutRuns);
+  fn(f->cut_place, (size_t)cut_places(S));
   fn(f->splats, ns);
   fn(f->depth_key, ns);
   fn(f->tiles, ns);

@@ -88,15 +88,19 @@ size_t layout(const SceneDev& S, unsigned char* base, lodgs_frame* f) {
   g.cut_first = c.take<uint32_t>((size_t)lodgs::cut_tiles(S));
   g.cut_chunks = c.take<int2>((size_t)lodgs::cut_chunks(S));
   g.chunk_count = c.take<uint16_t>((size_t)lodgs::cut_chunks(S));
+  g.cut_runs = c.take<uint32_t>(lodgs::kCutRuns);
+  g.cut_place = c.take<uint32_t>((size_t)lodgs::cut_places(S));
+  g.block_sums = c.take<uint32_t>(lodgs::kScanGrid + 1);
   return c.off;
 }
 
 // Every counter the cut reads starts from a known value (a kernel, not a
 // memset, so the call can sit in a captured graph).
-__global__ void k_noalloc_counters(FrameCounters* c, int32_t n_spt) {
+__global__ void k_noalloc_counters(FrameCounters* c, int32_t n_spt, int32_t n_cut_tiles) {
   FrameCounters z{};
   z.status = LODGS_OK;
   z.spt_count = n_spt;
+  z.n_cut_tiles = n_cut_tiles;
   *c = z;
 }
 
@@ -129,7 +133,8 @@ extern "C" int lodgs_lod_select_noalloc(const lodgs_scene* scene, const lodgs_ca
   f.open_event = nullptr;
   layout(scene->dev, base, &f);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_noalloc_counters, dim3(1), dim3(1), 0, st, f.ctr, scene->dev.n_spt);
+  hipLaunchKernelGGL(k_noalloc_counters, dim3(1), dim3(1), 0, st, f.ctr, scene->dev.n_spt,
+                     (int32_t)lodgs::cut_tiles(scene->dev));
   lodgs::launch_select(&f, lodgs::make_view(*cam, tau), flags, d_idx, capacity, d_count, st);
   e = hipGetLastError();
   return e == hipSuccess ? LODGS_OK : lodgs::hip_fail(e, "lodgs_lod_select_noalloc");

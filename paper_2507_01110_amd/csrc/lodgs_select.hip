@@ -16,8 +16,9 @@
 // Step 2 (k_cut_count): a wave per chunk counts its selected candidates (r_min
 // <= X_j).
 // Step 3 (k_cut_write): the selected nodes are written in layout order, a wave
-// per chunk, at the sum of the counts before it.
-// Four launches and no workgroup that waits for another.  A small view's cut is
+// per run of chunks, at the sum of the counts before it.
+// Four launches and no workgroup that waits for another (scenes of more than
+// kWideTiles tiles: two more, which scan the tiles' counts).  A small view's cut is
 // bound by the launches' latency: 18 us on a 32,767-node scene and 38 on 12M
 // nodes, street level (nine launches, with two-kernel scans: 31 and 48).  Tiles numbered by ticket that look back over published
 // counts took longer than adding the counts up (a contended ticket costs 0.1
@@ -162,6 +163,7 @@ __global__ void __launch_bounds__(kBlock) k_anc_fill(SceneDev S, int32_t D, int3
 // layout order: the upper nodes', then the SPTs').  The SPT prefixes' chunks
 // hold at most kChunk candidates.
 constexpr int32_t kChunk = 512;
+constexpr uint32_t kManyChunks = 1024, kOwnChunks = 8;  // of a tile, of an SPT
 constexpr int kChunkGrid = 1024;  // workgroups over the chunks, four waves each
 static_assert(kCutTile == kBlock, "one upper node or SPT per thread");
 
@@ -245,26 +247,61 @@ __global__ void __launch_bounds__(kBlock) k_cut_upper(SceneDev S, const ViewCons
   }
   if (tot) {
     const uint32_t base = s_base + at;
-    for (uint32_t q = 0; q < c; ++q)
-      chunks[base + q] = make_int2(b + (int32_t)q * kChunk, (int32_t)j);
+    const bool many = tot > kManyChunks;  // block-uniform
+    if (!many || c <= kOwnChunks) {
+      for (uint32_t q = 0; q < c; ++q) chunks[base + q] = make_int2(b + (int32_t)q * kChunk, (int32_t)j);
+    }
+    if (many) {  // the long ones' by their waves
+      for (uint64_t more = __ballot(c > kOwnChunks); more; more &= more - 1) {  // wave-uniform
+        const int l = __builtin_ctzll(more);
+        const uint32_t to = __shfl(base, l, 64), n = __shfl(c, l, 64);
+        const int32_t from = __shfl(b, l, 64), own = __shfl((int32_t)j, l, 64);
+        for (uint32_t q = lane; q < n; q += 64) chunks[to + q] = make_int2(from + (int32_t)q * kChunk, own);
+      }
+    }
   }
 }
 
-// A chunk's selected candidates: bit q of the result is set when this lane's
-// q-th one (node c.x + 64 q + lane) is.  The candidates are requested together.
-__device__ __forceinline__ uint32_t chunk_bits(const SceneDev& S, const int32_t* __restrict__ spt_high,
-                                               const float* __restrict__ spt_X, const int2& c) {
-  const int lane = threadIdx.x & 63;
-  const float X = spt_X[c.y];
-  const int32_t end = S.spt_begin[c.y] + spt_high[c.y];  // of the SPT's prefix
-  float rm[kChunk / 64];
-#pragma unroll
-  for (int q = 0; q < kChunk / 64; ++q) rm[q] = c.x + 64 * q + lane < end ? S.r_min[(int64_t)c.x + 64 * q + lane] : 0.0f;
-  uint32_t bits = 0u;
-#pragma unroll
-  for (int q = 0; q < kChunk / 64; ++q) bits |= c.x + 64 * q + lane < end && rm[q] <= X ? 1u << q : 0u;
-  return bits;
+// What the waves need of the chunks of a run: a lane holds one of up to 64.
+struct LaneChunk {
+  int32_t node, spt, end;  // first candidate, SPT, end of the SPT's prefix
+  float X;
+};
+
+__device__ __forceinline__ LaneChunk load_chunk(const SceneDev& S, const int32_t* __restrict__ spt_high,
+                                                const float* __restrict__ spt_X, const int2* __restrict__ chunks,
+                                                int g0, int m) {
+  const auto load = [&](int c) -> LaneChunk {
+    const int2 ch = chunks[c];
+    return {ch.x, ch.y, S.spt_begin[ch.y] + spt_high[ch.y], spt_X[ch.y]};
+  };
+  if (m == 1) return load(g0);  // (by scalar loads, which take less time)
+  return load(min(g0 + (int)(threadIdx.x & 63), g0 + m - 1));
 }
+
+__device__ __forceinline__ int32_t lane_value(int32_t x, int l) { return __builtin_amdgcn_readlane(x, l); }
+
+// This lane's candidates of a chunk: the q-th one is the chunk's first + 64 q +
+// lane.  They are requested together; the selected ones are the bits of
+// selected().
+struct ChunkNodes {
+  int32_t node, end;
+  float X, r_min[kChunk / 64];
+  __device__ __forceinline__ ChunkNodes(const SceneDev& S, int32_t first, int32_t end_, float X_)
+      : node(first + (int32_t)(threadIdx.x & 63)), end(end_), X(X_) {
+#pragma unroll
+    for (int q = 0; q < kChunk / 64; ++q) r_min[q] = node + 64 * q < end ? S.r_min[(int64_t)node + 64 * q] : 0.0f;
+  }
+  __device__ __forceinline__ ChunkNodes(const SceneDev& S, const LaneChunk& c, int l)
+      : ChunkNodes(S, lane_value(c.node, l), lane_value(c.end, l),
+                   __int_as_float(lane_value(__float_as_int(c.X), l))) {}
+  __device__ __forceinline__ uint32_t selected() const {
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int q = 0; q < kChunk / 64; ++q) bits |= node + 64 * q < end && r_min[q] <= X ? 1u << q : 0u;
+    return bits;
+  }
+};
 
 __device__ __forceinline__ uint32_t wave_total(uint32_t x) {
 #pragma unroll
@@ -272,42 +309,54 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t x) {
   return x;
 }
 
-// The chunks' selected candidates, and their sums by tile (and, for the cut
-// cache, by SPT).  A workgroup takes a run of chunks, each wave a part of it,
-// and adds the run's sum over a tile with one atomic: one per chunk made the
-// few visible tiles' words the bound (54 us for a 12M-node street view).
+// The chunks' selected candidates, and their sums by run, by tile (and, for
+// the cut cache, by SPT).  The list is cut in kCutRuns runs, a wave each; a
+// workgroup adds its runs' sum over a tile with one atomic: one per chunk made
+// the few visible tiles' words the bound (54 us for a 12M-node street view).
 constexpr int kCountThreads = 1024, kCountWaves = kCountThreads / 64, kCountGrid = 256;
+static_assert(kCountGrid * kCountWaves == kCutRuns && kChunkGrid * (kBlock / 64) == kCutRuns, "a wave per run");
+__device__ __forceinline__ int run_length(int n) { return (n + kCutRuns - 1) / kCutRuns; }
 
 __global__ void __launch_bounds__(kCountThreads) k_cut_count(SceneDev S, const FrameCounters* ctr,
                                                              const int32_t* __restrict__ spt_high,
                                                              const float* __restrict__ spt_X,
                                                              const int2* __restrict__ chunks, int32_t n_upper_tiles,
-                                                             uint16_t* chunk_count, uint32_t* selected,
+                                                             uint16_t* chunk_count, uint32_t* selected, uint32_t* runs,
                                                              uint32_t* spt_sel) {
   __shared__ int32_t w_tile[kCountWaves];   // the wave's last tile (-1: none) ...
   __shared__ uint32_t w_sum[kCountWaves];   // ... and what it has not yet added to it
   const int n = ctr->n_chunks, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int per = (n + kCountGrid * kCountWaves - 1) / (kCountGrid * kCountWaves);  // chunks of a wave
-  const int c0 = ((int)blockIdx.x * kCountWaves + wv) * per, c1 = min(c0 + per, n);
+  const int per = run_length(n), run = (int)blockIdx.x * kCountWaves + __builtin_amdgcn_readfirstlane(wv);
+  const int c0 = run * per, c1 = min(c0 + per, n);
   if ((int)blockIdx.x * kCountWaves * per >= n) return;  // block-uniform
   int32_t tile = -1;
-  uint32_t sum = 0;
-  for (int c = c0; c < c1; ++c) {  // wave-uniform
-    const int2 ch = chunks[c];
-    const uint32_t k = wave_total((uint32_t)__popc(chunk_bits(S, spt_high, spt_X, ch)));
-    const int32_t own = n_upper_tiles + ch.y / kCutTile;
-    if (own != tile && sum != 0u) {
-      if (lane == 0) atomicAdd(&selected[tile], sum);
-      sum = 0;
+  uint32_t sum = 0, all = 0;
+  for (int g0 = c0; g0 < c1; g0 += 64) {  // wave-uniform
+    const int m = min(64, c1 - g0);
+    const LaneChunk ch = load_chunk(S, spt_high, spt_X, chunks, g0, m);
+    uint32_t mine = 0;
+    for (int l = 0; l < m; ++l) {
+      const uint32_t bits = ChunkNodes(S, ch, l).selected();
+      uint32_t k = 0;
+#pragma unroll
+      for (int q = 0; q < kChunk / 64; ++q) k += (uint32_t)__popcll(__ballot((bits >> q) & 1u));
+      const int32_t own = n_upper_tiles + lane_value(ch.spt, l) / kCutTile;
+      if (own != tile && sum != 0u) {
+        if (lane == 0) atomicAdd(&selected[tile], sum);
+        sum = 0;
+      }
+      tile = own;
+      sum += k;
+      all += k;
+      mine = lane == l ? k : mine;
     }
-    tile = own;
-    sum += k;
-    if (lane == 0) {
-      chunk_count[c] = (uint16_t)k;  // at most kChunk
-      if (spt_sel && k) atomicAdd(&spt_sel[ch.y], k);
+    if (lane < m) {
+      chunk_count[g0 + lane] = (uint16_t)mine;  // at most kChunk
+      if (spt_sel && mine) atomicAdd(&spt_sel[ch.spt], mine);
     }
   }
   if (lane == 0) {
+    runs[run] = all;
     w_tile[wv] = tile;
     w_sum[wv] = sum;
   }
@@ -315,37 +364,48 @@ __global__ void __launch_bounds__(kCountThreads) k_cut_count(SceneDev S, const F
   // the first wave of a tile adds the sums of all waves that ended in it
   if (threadIdx.x < kCountWaves && w_tile[threadIdx.x] >= 0) {
     const int32_t mine = w_tile[threadIdx.x];
-    uint32_t all = 0;
+    uint32_t sums = 0;
     bool lead = true;
     for (int w = 0; w < kCountWaves; ++w) {
       if (w_tile[w] == mine) {
         lead = lead && w >= (int)threadIdx.x;
-        all += w_sum[w];
+        sums += w_sum[w];
       }
     }
-    if (lead && all) atomicAdd(&selected[mine], all);
+    if (lead && sums) atomicAdd(&selected[mine], sums);
   }
 }
 
 // The first n_upper_tiles workgroups write their tile's selected upper nodes,
-// the others take the chunks, a wave each: a tile's place is the sum of the
-// counts of the tiles before it, a chunk's that of its tile and of the chunks
-// before it there.  The last workgroup publishes the totals.
+// the others take the runs of chunks, a wave each: a tile's place is the sum
+// of the counts of the tiles before it, a chunk's that of its tile and of the
+// chunks before it there (whole runs by their sums), and is carried on to the
+// run's next chunks of that tile.  The last workgroup publishes the totals.
+// Up to kWideTiles tiles a wave adds up the tiles before its own itself (at
+// most 16 loads a lane); beyond, `place` holds those sums, made by a scan.
+// When all waves added up all tiles and every chunk its tile's earlier chunks,
+// the cut grew with the square of the scene.  Before / now, whole cuts, us:
+// one-node SPTs of 100K leaves 111 / 69, 400K 515 / 233, 1.6M 3225 / 700; one
+// SPT of 1.6M leaves 232 / 45.
 __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t* __restrict__ upper_sel,
                                                       int32_t n_upper_tiles, int32_t ntiles,
                                                       const uint32_t* __restrict__ selected,
+                                                      const uint32_t* __restrict__ place,
                                                       const uint4* __restrict__ sums,
                                                       const uint32_t* __restrict__ first,
                                                       const int32_t* __restrict__ spt_high,
                                                       const float* __restrict__ spt_X,
                                                       const int2* __restrict__ chunks,
-                                                      const uint16_t* __restrict__ chunk_count, int32_t* idx,
+                                                      const uint16_t* __restrict__ chunk_count,
+                                                      const uint32_t* __restrict__ runs, int32_t* idx,
                                                       int64_t capacity, FrameCounters* ctr, int32_t* d_count) {
   __shared__ uint32_t wt[kBlock / 64];
+  __shared__ uint32_t total[4][kBlock / 64];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const uint64_t lt = lanemask_lt();
   // selected nodes of the tiles [0, tile), the whole wave adding up
   const auto before = [&](int tile) -> uint32_t {
+    if (place) return place[tile];
     uint32_t x = 0;
 #pragma unroll 4
     for (int i = lane; i < tile; i += 64) x += selected[i];
@@ -363,44 +423,88 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
     return;
   }
   if (blockIdx.x == gridDim.x - 1) {  // block-uniform: the totals
-    if (wv == 0) {
-      const uint32_t n = before(ntiles);
-      uint32_t o[3] = {0u, 0u, 0u};
-      for (int i = lane; i < ntiles; i += 64) {
-        const uint4 x = sums[i];
-        o[0] += x.x;
-        o[1] += x.y;
-        o[2] += x.z;
-      }
+    const int threads = place ? kBlock : 64;
+    if (t >= threads) return;  // whole waves
+    uint32_t o[4] = {0u, 0u, 0u, 0u};
+#pragma unroll 4
+    for (int i = t; i < ntiles; i += threads) {
+      const uint4 x = sums[i];
+      o[0] += x.x;
+      o[1] += x.y;
+      o[2] += x.z;
+      o[3] += selected[i];
+    }
 #pragma unroll
-      for (int k = 0; k < 3; ++k) o[k] = wave_total(o[k]);
-      if (lane == 0) {
-        ctr->n_selected = (int32_t)n;
-        ctr->n_upper_selected = (int32_t)o[0];
-        ctr->n_spt_visible = (int32_t)o[1];
-        ctr->sum_high = (int32_t)o[2];
-        *d_count = (int32_t)n;
-        if ((int64_t)n > capacity) ctr->status = LODGS_E_CAPACITY;
+    for (int k = 0; k < 4; ++k) o[k] = wave_total(o[k]);
+    if (place) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (lane == 0) total[k][wv] = o[k];
       }
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = total[k][0] + total[k][1] + total[k][2] + total[k][3];
+    }
+    if (t == 0) {
+      const uint32_t n = o[3];
+      ctr->n_selected = (int32_t)n;
+      ctr->n_upper_selected = (int32_t)o[0];
+      ctr->n_spt_visible = (int32_t)o[1];
+      ctr->sum_high = (int32_t)o[2];
+      *d_count = (int32_t)n;
+      if ((int64_t)n > capacity) ctr->status = LODGS_E_CAPACITY;
     }
     return;
   }
-  const int n = ctr->n_chunks, nw = ((int)gridDim.x - n_upper_tiles - 1) * (kBlock / 64);
-  for (int c = ((int)blockIdx.x - n_upper_tiles) * (kBlock / 64) + wv; c < n; c += nw) {
-    if (chunk_count[c] == 0u) continue;  // wave-uniform
-    const int2 ch = chunks[c];
-    const int tile = n_upper_tiles + ch.y / kCutTile;
-    const uint32_t bits = chunk_bits(S, spt_high, spt_X, ch);
-    uint32_t x = 0;
-    for (int i = (int)first[tile] + lane; i < c; i += 64) x += chunk_count[i];
-    uint32_t pos0 = before(tile) + wave_total(x);
+  const int n = ctr->n_chunks, run = ((int)blockIdx.x - n_upper_tiles) * (kBlock / 64) + wv;
+  // writes a chunk's selected candidates from place pos0 on, returns the place after them
+  const auto write = [&](const ChunkNodes& nodes, uint32_t pos0) -> uint32_t {
+    const uint32_t bits = nodes.selected();
 #pragma unroll
     for (int q = 0; q < kChunk / 64; ++q) {
       const bool p = (bits >> q) & 1u;
-      const uint64_t m = __ballot(p);
-      const uint32_t pos = pos0 + (uint32_t)__popcll(m & lt);
-      if (p && pos < capacity) idx[pos] = ch.x + 64 * q + lane;
-      pos0 += (uint32_t)__popcll(m);
+      const uint64_t mask = __ballot(p);
+      const uint32_t pos = pos0 + (uint32_t)__popcll(mask & lt);
+      if (p && pos < capacity) idx[pos] = nodes.node + 64 * q;
+      pos0 += (uint32_t)__popcll(mask);
+    }
+    return pos0;
+  };
+  if (n <= kCutRuns) {  // a run is one chunk
+    if (run >= n || chunk_count[run] == 0u) return;
+    const int2 ch = chunks[run];
+    const ChunkNodes nodes(S, ch.x, S.spt_begin[ch.y] + spt_high[ch.y], spt_X[ch.y]);
+    const int tile = n_upper_tiles + ch.y / kCutTile;
+    uint32_t x = 0;
+    for (int i = (int)first[tile] + lane; i < run; i += 64) x += chunk_count[i];
+    write(nodes, before(tile) + wave_total(x));
+    return;
+  }
+  const int per = run_length(n), r = __builtin_amdgcn_readfirstlane(run);
+  const int c0 = r * per, c1 = min(c0 + per, n);
+  int32_t tile = -1;
+  uint32_t pos0 = 0;
+  for (int g0 = c0; g0 < c1; g0 += 64) {  // wave-uniform
+    const int m = min(64, c1 - g0);
+    const uint32_t count = lane < m ? chunk_count[g0 + lane] : 0u;
+    const LaneChunk ch = load_chunk(S, spt_high, spt_X, chunks, g0, m);
+    for (uint64_t left = __ballot(count != 0u); left; left &= left - 1) {
+      const int l = __builtin_ctzll(left);
+      const int32_t own = n_upper_tiles + lane_value(ch.spt, l) / kCutTile;
+      const ChunkNodes nodes(S, ch, l);
+      if (own != tile) {
+        tile = own;
+        // the chunks before this one in the tile: from the tile's first to the
+        // next run, whole runs, and this run's
+        const int c = g0 + l, a = (int)first[tile];
+        const int ra = min((a + per - 1) / per, r);
+        uint32_t x = 0;
+        for (int i = a + lane; i < min(ra * per, c); i += 64) x += chunk_count[i];
+        for (int i = ra + lane; i < r; i += 64) x += runs[i];
+        for (int i = max(a, c0) + lane; i < c; i += 64) x += chunk_count[i];
+        pos0 = before(tile) + wave_total(x);
+      }
+      pos0 = write(nodes, pos0);
     }
   }
 }
@@ -505,10 +609,14 @@ void launch_select(lodgs_frame* f, const ViewConst& v, uint32_t flags, int32_t* 
                      f->upper_sel, f->spt_high, f->spt_X, f->ctr, n_upper_tiles, f->cut_selected, f->cut_sums,
                      f->cut_first, f->cut_chunks, C);
   hipLaunchKernelGGL(k_cut_count, dim3(kCountGrid), dim3(kCountThreads), 0, st, S, f->ctr, f->spt_high, f->spt_X,
-                     f->cut_chunks, n_upper_tiles, f->chunk_count, f->cut_selected, C.spt_sel);
+                     f->cut_chunks, n_upper_tiles, f->chunk_count, f->cut_selected, f->cut_runs, C.spt_sel);
+  const bool wide = tiles > kWideTiles;
+  if (wide)
+    scan_exclusive(LoadArray{f->cut_selected}, &f->ctr->n_cut_tiles, tiles, f->block_sums, f->cut_place, nullptr, st);
   hipLaunchKernelGGL(k_cut_write, dim3(n_upper_tiles + kChunkGrid + 1), dim3(kBlock), 0, st, S, f->upper_sel,
-                     n_upper_tiles, tiles, f->cut_selected, f->cut_sums, f->cut_first, f->spt_high, f->spt_X,
-                     f->cut_chunks, f->chunk_count, d_idx, capacity, f->ctr, d_count);
+                     n_upper_tiles, tiles, f->cut_selected, wide ? f->cut_place : (const uint32_t*)nullptr, f->cut_sums,
+                     f->cut_first, f->spt_high, f->spt_X, f->cut_chunks, f->chunk_count, f->cut_runs, d_idx, capacity,
+                     f->ctr, d_count);
   stage_end(f, st);
 }
 

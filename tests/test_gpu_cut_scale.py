@@ -1,0 +1,77 @@
+"""The HSPT cut on scenes far from the usual SPT size: one-node SPTs by the
+hundred thousand (more tiles of the cut than its waves add up themselves, runs
+of several hundred chunks over several tiles) and one SPT of millions of nodes
+(whole runs of chunks inside one tile).  Selected sets are compared with the
+oracle's exactly; and the time grows with the scene, not with its square."""
+import numpy as np
+import pytest
+
+import oracle
+import scenegen
+from scenegen import configs
+
+pytestmark = pytest.mark.gpu
+
+
+def make(leaves, one_spt):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    spec = configs.tiny_spec(n=leaves, seed=5, sh_degree=0)
+    spec.half_extent = 10.0 * (leaves / 16384.0) ** (1.0 / 3.0)
+    tree = scenegen.build_tree(spec)
+    lv = tree.log_scales.astype(np.float64).sum(axis=1)
+    tree.log_volume_threshold = float(lv.max() + 1.0 if one_spt else lv.min() - 1.0)
+    ext = spec.half_extent
+    return tree, [scenegen.camera_look_at((0.0, 0.0, 3.0 * ext), (0.0, 0.0, 0.0), (0.0, 1.0, 0.0), 64, 64),
+                  scenegen.camera_look_at((0.3 * ext, 0.2 * ext, 0.0), (ext, -0.5 * ext, 0.2 * ext), (0.0, 0.0, 1.0), 96, 64)]
+
+
+@pytest.mark.parametrize("leaves,one_spt", [(130_000, False), (133_000, False), (900_000, False), (1_060_000, True),
+                                            (2_300_000, True)])
+def test_cut_of_small_and_large_spts(leaves, one_spt):
+    import torch
+    from paper_2507_01110_amd.lodgs import Frame, Scene
+    print("cut", leaves, one_spt, flush=True)
+    tree, cams = make(leaves, one_spt)
+    O = oracle.OracleScene(tree)
+    S = Scene(tree)
+    f = Frame(S, S.n_nodes, 1 << 16, 96, 64)
+    idx = torch.empty(S.n_nodes, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(1, dtype=torch.int32, device="cuda")
+    for cam in cams:
+        for tau in (0.0, 4.0):
+            for cull in (True, False):
+                ids, _ = O.select(cam, tau, cull=cull)
+                want = O.pos_of[ids]
+                f.lod_select(cam, tau, cull=cull)
+                n = int(f.count.item())
+                assert n == len(want)
+                assert np.array_equal(f.idx[:n].cpu().numpy(), want)
+                st = f.stats()
+                assert st["status"] == 0 and st["n_selected"] == n
+                assert st["n_upper_selected"] == int((want < S.n_upper).sum())
+                S.lod_select_noalloc(cam, tau, idx, cnt, cull=cull)
+                assert int(cnt.item()) == n and torch.equal(idx[:n], f.idx[:n])
+
+
+def test_time_of_the_cut_grows_with_the_scene():
+    import torch
+    from paper_2507_01110_amd.lodgs import Frame, Scene
+    us = []
+    for leaves in (100_000, 1_600_000):
+        tree, cams = make(leaves, False)
+        S = Scene(tree)
+        f = Frame(S, S.n_nodes, 1 << 16, 64, 64)
+        f.lod_select(cams[0], 0.0)
+        best = float("inf")
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            f.lod_select(cams[0], 0.0)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        us.append(best)
+    print("us", us, flush=True)
+    assert us[1] <= 16.0 * us[0], us  # 16 times the nodes
