@@ -197,12 +197,12 @@ int lodgs_lod_select(lodgs_frame* frame, const lodgs_camera* cam, float tau, uin
 /* For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc): the HSPT cut of
  * lodgs_lod_select with no frame.  Its workspace (counters, view constants, 2
- * bytes per upper node, 8 per SPT and the candidate chunks, about 30 bytes per
- * 512 nodes) lives in one static device array of 21/16
- * LODGS_NOALLOC_SCRATCH_BYTES per GPU, held until the process ends; the call
- * allocates nothing.  Same arguments and output contract as lodgs_lod_select
- * (selected positions ascending in d_idx, the full count in *d_count, a
- * count above capacity meaning the list was cut short), with the scene in
+ * bytes per upper node, 16 per SPT, 8 per 512 nodes and 28 per 256 upper nodes
+ * or SPTs) lives in one static device array of LODGS_NOALLOC_SCRATCH_BYTES and
+ * 1 MiB per GPU, held until the process ends; the call allocates nothing.
+ * Same arguments and output contract as lodgs_lod_select (selected positions
+ * ascending in d_idx, the full count in *d_count, a count above capacity
+ * meaning the list was cut short), with the scene in
  * place of the frame and flags limited to LODGS_CULL | LODGS_CONSERVATIVE
  * (else LODGS_E_INVALID).  A scene for which 2 bytes per upper node, 12 per
  * SPT and two words per compaction segment exceed LODGS_NOALLOC_SCRATCH_BYTES

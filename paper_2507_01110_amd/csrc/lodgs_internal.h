@@ -137,8 +137,7 @@ struct lodgs_frame {
   uint32_t* cut_selected; // [cut_tiles] per tile of the cut: selected nodes
   uint4* cut_sums;        // [cut_tiles] and selected upper nodes, visible SPTs, candidates, 0
   uint32_t* cut_first;    // [cut_tiles] first chunk of each SPT tile
-  int2* cut_chunks;       // [cut_chunks] first node, SPT
-  uint16_t* chunk_count;  // [cut_chunks] selected nodes
+  uint2* cut_chunks;      // [cut_chunks] SPT, index in the SPT << 10 | selected nodes
   uint32_t* cut_runs;     // [kCutRuns] selected nodes of each run of chunks
   uint32_t* cut_place;    // [cut_tiles, if above kWideTiles] selected nodes before each tile
   // comparator cuts (allocated when the scene has its hierarchy attached)
@@ -381,7 +380,6 @@ void frame_arrays(lodgs_frame* f, const SceneDev& S, const lodgs_frame_caps& cap
   fn(f->cut_sums, (size_t)cut_tiles(S));
   fn(f->cut_first, (size_t)cut_tiles(S));
   fn(f->cut_chunks, (size_t)cut_chunks(S));
-  fn(f->chunk_count, (size_t)cut_chunks(S));
   fn(f->cut_runs, (size_t)kCutRuns);
   fn(f->cut_place, (size_t)cut_places(S));
   fn(f->splats, ns);

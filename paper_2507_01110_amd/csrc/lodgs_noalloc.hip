@@ -16,7 +16,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = LODGS_NOALLOC_SCRATCH_BYTES / 16 * 21;
+constexpr size_t kScratchBytes = LODGS_NOALLOC_SCRATCH_BYTES + (1u << 20);
 constexpr int kMaxDevices = 64;
 constexpr size_t kAlign = 256;
 
@@ -57,10 +57,11 @@ struct Carve {
 };
 
 // The bytes that decide whether a scene is taken (LODGS_NOALLOC_SCRATCH_BYTES
-// at most): 2 per upper node, 12 per SPT and two words per compaction segment,
-// with the counters, the view and 512 scan words.  The workspace itself is at
-// most a quarter larger (10 bytes against 8 for every 512 nodes), which
-// kScratchBytes leaves room for.
+// at most): 2 per upper node, 12 per SPT and two words per compaction segment
+// (64 upper nodes, an SPT, 512 nodes), with the counters, the view and 512 scan
+// words.  The workspace takes 4 bytes less per SPT and 1/16 less per upper
+// node, 28 more per 256 of either and 20 KB, so at most 0.8 MB more for the 16.8M upper
+// nodes that the limit admits, which kScratchBytes leaves room for.
 size_t scene_bytes(const SceneDev& S) {
   Carve c{nullptr};
   (void)c.take<FrameCounters>(1);
@@ -86,8 +87,7 @@ size_t layout(const SceneDev& S, unsigned char* base, lodgs_frame* f) {
   g.cut_selected = c.take<uint32_t>((size_t)lodgs::cut_tiles(S));
   g.cut_sums = c.take<uint4>((size_t)lodgs::cut_tiles(S));
   g.cut_first = c.take<uint32_t>((size_t)lodgs::cut_tiles(S));
-  g.cut_chunks = c.take<int2>((size_t)lodgs::cut_chunks(S));
-  g.chunk_count = c.take<uint16_t>((size_t)lodgs::cut_chunks(S));
+  g.cut_chunks = c.take<uint2>((size_t)lodgs::cut_chunks(S));
   g.cut_runs = c.take<uint32_t>(lodgs::kCutRuns);
   g.cut_place = c.take<uint32_t>((size_t)lodgs::cut_places(S));
   g.block_sums = c.take<uint32_t>(lodgs::kScanGrid + 1);

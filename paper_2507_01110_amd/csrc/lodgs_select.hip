@@ -162,18 +162,19 @@ __global__ void __launch_bounds__(kBlock) k_anc_fill(SceneDev S, int32_t D, int3
 // A tile of the cut: kCutTile upper nodes, or kCutTile SPTs (tiles follow the
 // layout order: the upper nodes', then the SPTs').  The SPT prefixes' chunks
 // hold at most kChunk candidates.
+// A chunk is listed as (SPT, index in the SPT << 10 | selected candidates).
 constexpr int32_t kChunk = 512;
+constexpr uint32_t kChunkCount = 1023u;  // the count's bits
 constexpr uint32_t kManyChunks = 1024, kOwnChunks = 8;  // of a tile, of an SPT
 constexpr int kChunkGrid = 1024;  // workgroups over the chunks, four waves each
 static_assert(kCutTile == kBlock, "one upper node or SPT per thread");
 
 // Per tile: the upper nodes' decisions and their count, or the SPTs' candidate
-// prefixes and their chunks (first node, SPT), which a tile appends to the
-// list in order (the tiles in any order: first[tile] is where).
+// prefixes and their chunks, which a tile appends to the list in order (the tiles in any order: first[tile] is where).
 __global__ void __launch_bounds__(kBlock) k_cut_upper(SceneDev S, const ViewConst* __restrict__ vp, uint32_t flags,
                                                       const uint8_t* utest, uint8_t* upper_sel, int32_t* spt_high,
                                                       float* spt_X, FrameCounters* ctr, int32_t n_upper_tiles, uint32_t* selected,
-                                                      uint4* sums, uint32_t* first, int2* chunks, CacheDev C) {
+                                                      uint4* sums, uint32_t* first, uint2* chunks, CacheDev C) {
   __shared__ uint32_t wt[kBlock / 64];
   __shared__ uint32_t w3[3][kBlock / 64];
   __shared__ uint32_t s_base;
@@ -249,14 +250,13 @@ __global__ void __launch_bounds__(kBlock) k_cut_upper(SceneDev S, const ViewCons
     const uint32_t base = s_base + at;
     const bool many = tot > kManyChunks;  // block-uniform
     if (!many || c <= kOwnChunks) {
-      for (uint32_t q = 0; q < c; ++q) chunks[base + q] = make_int2(b + (int32_t)q * kChunk, (int32_t)j);
+      for (uint32_t q = 0; q < c; ++q) chunks[base + q] = make_uint2((uint32_t)j, q << 10);
     }
     if (many) {  // the long ones' by their waves
       for (uint64_t more = __ballot(c > kOwnChunks); more; more &= more - 1) {  // wave-uniform
         const int l = __builtin_ctzll(more);
-        const uint32_t to = __shfl(base, l, 64), n = __shfl(c, l, 64);
-        const int32_t from = __shfl(b, l, 64), own = __shfl((int32_t)j, l, 64);
-        for (uint32_t q = lane; q < n; q += 64) chunks[to + q] = make_int2(from + (int32_t)q * kChunk, own);
+        const uint32_t to = __shfl(base, l, 64), n = __shfl(c, l, 64), own = __shfl((uint32_t)j, l, 64);
+        for (uint32_t q = lane; q < n; q += 64) chunks[to + q] = make_uint2(own, q << 10);
       }
     }
   }
@@ -264,16 +264,22 @@ __global__ void __launch_bounds__(kBlock) k_cut_upper(SceneDev S, const ViewCons
 
 // What the waves need of the chunks of a run: a lane holds one of up to 64.
 struct LaneChunk {
+  uint32_t word;           // as listed
   int32_t node, spt, end;  // first candidate, SPT, end of the SPT's prefix
   float X;
 };
 
+// A chunk's first candidate, from its SPT's first node.
+__device__ __forceinline__ int32_t chunk_node(int32_t begin, uint32_t word) {
+  return begin + (int32_t)(word >> 10) * kChunk;
+}
+
 __device__ __forceinline__ LaneChunk load_chunk(const SceneDev& S, const int32_t* __restrict__ spt_high,
-                                                const float* __restrict__ spt_X, const int2* __restrict__ chunks,
-                                                int g0, int m) {
+                                                const float* __restrict__ spt_X, const uint2* chunks, int g0, int m) {
   const auto load = [&](int c) -> LaneChunk {
-    const int2 ch = chunks[c];
-    return {ch.x, ch.y, S.spt_begin[ch.y] + spt_high[ch.y], spt_X[ch.y]};
+    const uint2 ch = chunks[c];
+    const int32_t b = S.spt_begin[ch.x];
+    return {ch.y, chunk_node(b, ch.y), (int32_t)ch.x, b + spt_high[ch.x], spt_X[ch.x]};
   };
   if (m == 1) return load(g0);  // (by scalar loads, which take less time)
   return load(min(g0 + (int)(threadIdx.x & 63), g0 + m - 1));
@@ -320,9 +326,8 @@ __device__ __forceinline__ int run_length(int n) { return (n + kCutRuns - 1) / k
 __global__ void __launch_bounds__(kCountThreads) k_cut_count(SceneDev S, const FrameCounters* ctr,
                                                              const int32_t* __restrict__ spt_high,
                                                              const float* __restrict__ spt_X,
-                                                             const int2* __restrict__ chunks, int32_t n_upper_tiles,
-                                                             uint16_t* chunk_count, uint32_t* selected, uint32_t* runs,
-                                                             uint32_t* spt_sel) {
+                                                             uint2* chunks, int32_t n_upper_tiles, uint32_t* selected,
+                                                             uint32_t* runs, uint32_t* spt_sel) {
   __shared__ int32_t w_tile[kCountWaves];   // the wave's last tile (-1: none) ...
   __shared__ uint32_t w_sum[kCountWaves];   // ... and what it has not yet added to it
   const int n = ctr->n_chunks, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -351,7 +356,7 @@ __global__ void __launch_bounds__(kCountThreads) k_cut_count(SceneDev S, const F
       mine = lane == l ? k : mine;
     }
     if (lane < m) {
-      chunk_count[g0 + lane] = (uint16_t)mine;  // at most kChunk
+      chunks[g0 + lane].y = ch.word | mine;  // at most kChunk
       if (spt_sel && mine) atomicAdd(&spt_sel[ch.spt], mine);
     }
   }
@@ -395,8 +400,7 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
                                                       const uint32_t* __restrict__ first,
                                                       const int32_t* __restrict__ spt_high,
                                                       const float* __restrict__ spt_X,
-                                                      const int2* __restrict__ chunks,
-                                                      const uint16_t* __restrict__ chunk_count,
+                                                      const uint2* __restrict__ chunks,
                                                       const uint32_t* __restrict__ runs, int32_t* idx,
                                                       int64_t capacity, FrameCounters* ctr, int32_t* d_count) {
   __shared__ uint32_t wt[kBlock / 64];
@@ -471,12 +475,14 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
     return pos0;
   };
   if (n <= kCutRuns) {  // a run is one chunk
-    if (run >= n || chunk_count[run] == 0u) return;
-    const int2 ch = chunks[run];
-    const ChunkNodes nodes(S, ch.x, S.spt_begin[ch.y] + spt_high[ch.y], spt_X[ch.y]);
-    const int tile = n_upper_tiles + ch.y / kCutTile;
+    if (run >= n) return;
+    const uint2 ch = chunks[run];
+    if ((ch.y & kChunkCount) == 0u) return;
+    const int32_t b = S.spt_begin[ch.x];
+    const ChunkNodes nodes(S, chunk_node(b, ch.y), b + spt_high[ch.x], spt_X[ch.x]);
+    const int tile = n_upper_tiles + (int)ch.x / kCutTile;
     uint32_t x = 0;
-    for (int i = (int)first[tile] + lane; i < run; i += 64) x += chunk_count[i];
+    for (int i = (int)first[tile] + lane; i < run; i += 64) x += chunks[i].y & kChunkCount;
     write(nodes, before(tile) + wave_total(x));
     return;
   }
@@ -486,9 +492,8 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
   uint32_t pos0 = 0;
   for (int g0 = c0; g0 < c1; g0 += 64) {  // wave-uniform
     const int m = min(64, c1 - g0);
-    const uint32_t count = lane < m ? chunk_count[g0 + lane] : 0u;
     const LaneChunk ch = load_chunk(S, spt_high, spt_X, chunks, g0, m);
-    for (uint64_t left = __ballot(count != 0u); left; left &= left - 1) {
+    for (uint64_t left = __ballot(lane < m && (ch.word & kChunkCount) != 0u); left; left &= left - 1) {
       const int l = __builtin_ctzll(left);
       const int32_t own = n_upper_tiles + lane_value(ch.spt, l) / kCutTile;
       const ChunkNodes nodes(S, ch, l);
@@ -499,9 +504,9 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
         const int c = g0 + l, a = (int)first[tile];
         const int ra = min((a + per - 1) / per, r);
         uint32_t x = 0;
-        for (int i = a + lane; i < min(ra * per, c); i += 64) x += chunk_count[i];
+        for (int i = a + lane; i < min(ra * per, c); i += 64) x += chunks[i].y & kChunkCount;
         for (int i = ra + lane; i < r; i += 64) x += runs[i];
-        for (int i = max(a, c0) + lane; i < c; i += 64) x += chunk_count[i];
+        for (int i = max(a, c0) + lane; i < c; i += 64) x += chunks[i].y & kChunkCount;
         pos0 = before(tile) + wave_total(x);
       }
       pos0 = write(nodes, pos0);
@@ -609,13 +614,13 @@ void launch_select(lodgs_frame* f, const ViewConst& v, uint32_t flags, int32_t* 
                      f->upper_sel, f->spt_high, f->spt_X, f->ctr, n_upper_tiles, f->cut_selected, f->cut_sums,
                      f->cut_first, f->cut_chunks, C);
   hipLaunchKernelGGL(k_cut_count, dim3(kCountGrid), dim3(kCountThreads), 0, st, S, f->ctr, f->spt_high, f->spt_X,
-                     f->cut_chunks, n_upper_tiles, f->chunk_count, f->cut_selected, f->cut_runs, C.spt_sel);
+                     f->cut_chunks, n_upper_tiles, f->cut_selected, f->cut_runs, C.spt_sel);
   const bool wide = tiles > kWideTiles;
   if (wide)
     scan_exclusive(LoadArray{f->cut_selected}, &f->ctr->n_cut_tiles, tiles, f->block_sums, f->cut_place, nullptr, st);
   hipLaunchKernelGGL(k_cut_write, dim3(n_upper_tiles + kChunkGrid + 1), dim3(kBlock), 0, st, S, f->upper_sel,
                      n_upper_tiles, tiles, f->cut_selected, wide ? f->cut_place : (const uint32_t*)nullptr, f->cut_sums,
-                     f->cut_first, f->spt_high, f->spt_X, f->cut_chunks, f->chunk_count, f->cut_runs, d_idx, capacity,
+                     f->cut_first, f->spt_high, f->spt_X, f->cut_chunks, f->cut_runs, d_idx, capacity,
                      f->ctr, d_count);
   stage_end(f, st);
 }

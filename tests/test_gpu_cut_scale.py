@@ -75,3 +75,28 @@ def test_time_of_the_cut_grows_with_the_scene():
         us.append(best)
     print("us", us, flush=True)
     assert us[1] <= 16.0 * us[0], us  # 16 times the nodes
+
+
+@pytest.mark.parametrize("leaves,taken", [(1_515_000, True), (1_525_000, False)])
+def test_largest_scene_of_the_allocation_free_cut(leaves, taken):
+    # one-node SPTs: 2 (upper) + 20 (SPTs) + 8 (segments per 512 of 2 nodes a
+    # leaf) / 256 + 4 / 64 bytes a leaf against LODGS_NOALLOC_SCRATCH_BYTES
+    import torch
+    from paper_2507_01110_amd import _lib
+    from paper_2507_01110_amd.lodgs import Frame, Scene
+    assert (leaves * (22 + 2 * 8 / 512 + 4 / 64) + 4096 < 32 << 20) == taken
+    tree, cams = make(leaves, False)
+    S = Scene(tree)
+    idx = torch.empty(S.n_nodes, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(1, dtype=torch.int32, device="cuda")
+    if not taken:
+        with pytest.raises(_lib.LodgsError) as e:
+            S.lod_select_noalloc(cams[0], 0.0, idx, cnt)
+        assert e.value.code == _lib.E_CAPACITY
+        return
+    f = Frame(S, S.n_nodes, 1 << 16, 64, 64)
+    for tau in (0.0, 2.0):
+        f.lod_select(cams[0], tau)
+        S.lod_select_noalloc(cams[0], tau, idx, cnt)
+        n = int(f.count.item())
+        assert int(cnt.item()) == n and torch.equal(idx[:n], f.idx[:n])
