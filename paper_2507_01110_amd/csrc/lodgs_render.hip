@@ -766,19 +766,20 @@ __device__ __forceinline__ unsigned long long wave_sort(unsigned long long v) {
 }
 #undef LODGS_DPP64
 
-// Sorts in[0, m) into keys (LDS; 0 < m <= THREADS * ITEMS, itself a power of two;
-// distinct keys below ~0) with the whole workgroup: runs of 64 in registers,
-// then rounds that merge neighbouring runs, every key finding its place by a
-// binary search of the other run (the searches of a thread's keys run side by
-// side).  Places past m hold ~0, so that every run is whole.
-template <int THREADS, int ITEMS>
+// Sorts in[0, m) (STAGED: keys[0, m) itself) into keys (LDS; 0 < m <= THREADS
+// * ITEMS, itself a power of two; distinct keys below ~0) with the whole
+// workgroup: runs of 64 in registers, then rounds that merge neighbouring runs,
+// every key finding its place by a binary search of the other run (the searches
+// of a thread's keys run side by side).  Places past m hold ~0, so that every
+// run is whole.
+template <int THREADS, int ITEMS, bool STAGED>
 __device__ __forceinline__ void block_sort(const unsigned long long* in, unsigned long long* keys, int m) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   int whole = 64;
   while (whole < m) whole *= 2;
   for (int r = wv; r * 64 < whole; r += THREADS / 64) {  // wave-uniform
     const int j = r * 64 + lane;
-    keys[j] = r * 64 < m ? wave_sort(j < m ? in[j] : ~0ull) : ~0ull;
+    keys[j] = r * 64 < m ? wave_sort(j < m ? (STAGED ? keys[j] : in[j]) : ~0ull) : ~0ull;
   }
   __syncthreads();
   for (int w = 64; w < m; w *= 2) {  // block-uniform
@@ -809,13 +810,13 @@ __device__ __forceinline__ void block_sort(const unsigned long long* in, unsigne
 }
 
 // block_sort with as many keys per thread as m needs.
-template <int THREADS>
+template <int THREADS, bool STAGED = false>
 __device__ __forceinline__ void block_sort_small(const unsigned long long* in, unsigned long long* keys, int m) {
   static_assert(kSortSmall == 8 * THREADS, "eight keys per thread at most");
-  if (m <= THREADS) block_sort<THREADS, 1>(in, keys, m);
-  else if (m <= 2 * THREADS) block_sort<THREADS, 2>(in, keys, m);
-  else if (m <= 4 * THREADS) block_sort<THREADS, 4>(in, keys, m);
-  else block_sort<THREADS, 8>(in, keys, m);
+  if (m <= THREADS) block_sort<THREADS, 1, STAGED>(in, keys, m);
+  else if (m <= 2 * THREADS) block_sort<THREADS, 2, STAGED>(in, keys, m);
+  else if (m <= 4 * THREADS) block_sort<THREADS, 4, STAGED>(in, keys, m);
+  else block_sort<THREADS, 8, STAGED>(in, keys, m);
 }
 
 // Sorts the tiles' keys: the listed chunks of large tiles (in place, for
@@ -885,17 +886,145 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters
   }
 }
 
-// Puts the sorted chunks of a large tile together, one workgroup per chunk: a
-// key's place in its tile is its index in its chunk and, for every other
-// chunk, the number of smaller keys there, found by a binary search of the
-// chunk staged in LDS.  All chunks of all large tiles work at once, which
-// counts more here than the extra comparisons of a tile of many chunks.
+// How many of keys[lo, hi) (ascending) are below v, and lo.
+__device__ __forceinline__ int keys_below(const unsigned long long* __restrict__ keys, int lo, int hi,
+                                          unsigned long long v) {
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (keys[mid] < v) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// LDS of a tile's split; thread t keeps what it knows of chunks t, t + 256, ...
+// (where v's place lies, [lo, hi] as lo | hi << 16, and the last place tried).
+struct SplitLds {
+  uint32_t window[kSortSmall];
+  uint16_t at[kSortSmall];
+};
+
+// A value with exactly `rank` of a tile's n keys below it, the whole workgroup
+// halving [lo, hi): fewer are below lo, more below hi (the keys are distinct).
+// The keys are sorted chunks of kSortSmall.  The windows hold from one split to
+// a later one of the same tile; a tile of more chunks than they have room for
+// is searched whole each time.
+__device__ __forceinline__ unsigned long long split_keys(const unsigned long long* __restrict__ keys, uint32_t n,
+                                                         uint32_t rank, unsigned long long lo, unsigned long long hi,
+                                                         SplitLds& lds, uint32_t (*part)[kSmallThreads / 64]) {
+  const uint32_t t = threadIdx.x, nc = (n + kSortSmall - 1) / kSortSmall;
+  const bool kept = nc <= (uint32_t)kSortSmall;
+  __syncthreads();  // `part` may still be read
+  for (int turn = 0; turn < 64; ++turn) {  // block-uniform; 64 halvings end any range
+    const unsigned long long v = lo + (hi - lo) / 2;
+    uint32_t below = 0;
+    for (uint32_t c = t; c < nc; c += kSmallThreads) {
+      const uint32_t w = kept ? lds.window[c] : (uint32_t)min(n - c * kSortSmall, (uint32_t)kSortSmall) << 16;
+      const int k = keys_below(keys + c * kSortSmall, (int)(w & 0xFFFFu), (int)(w >> 16), v);
+      if (kept) lds.at[c] = (uint16_t)k;
+      below += (uint32_t)k;
+    }
+    below = wave_add(below);
+    if ((t & 63u) == 0u) part[turn & 1][t >> 6] = below;
+    __syncthreads();
+    below = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallThreads / 64; ++w) below += part[turn & 1][w];
+    if (kept) {
+      for (uint32_t c = t; c < nc; c += kSmallThreads) {
+        const uint32_t w = lds.window[c], k = lds.at[c];
+        // (found: what lies above stays open for a split at a higher rank)
+        lds.window[c] = below == rank ? k | min(n - c * kSortSmall, (uint32_t)kSortSmall) << 16
+                                      : (below < rank ? (w & 0xFFFF0000u) | k : (w & 0xFFFFu) | k << 16);
+      }
+    }
+    if (below == rank) return v;
+    if (below < rank) lo = v;
+    else hi = v;
+  }
+  return hi;
+}
+
+// A workgroup's share of a tile of many sorted chunks: the keys of ranks [kSortSmall
+// w, kSortSmall (w + 1)), found by splitting the tile at both ends, gathered
+// from all chunks and sorted.
+__device__ __forceinline__ void merge_share(const unsigned long long* __restrict__ keys_in, uint32_t n, uint32_t w,
+                                            unsigned long long* keys, uint32_t (*part)[kSmallThreads / 64]) {
+  const uint32_t t = threadIdx.x, lane = t & 63u, nc = (n + kSortSmall - 1) / kSortSmall;
+  static_assert(sizeof(SplitLds) <= sizeof(unsigned long long) * kSortSmall, "the windows lie where the keys will");
+  SplitLds& lds = *reinterpret_cast<SplitLds*>(keys);
+  unsigned long long least = ~0ull, most = 0ull;
+  for (uint32_t c = t; c < nc; c += kSmallThreads) {
+    const uint32_t len = min(n - c * kSortSmall, (uint32_t)kSortSmall);
+    if (c < (uint32_t)kSortSmall) lds.window[c] = len << 16;
+    least = min(least, keys_in[c * kSortSmall]);
+    most = max(most, keys_in[c * kSortSmall + len - 1]);
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    least = min(least, __shfl_xor(least, d, 64));
+    most = max(most, __shfl_xor(most, d, 64));
+  }
+  __shared__ unsigned long long ends[2][kSmallThreads / 64];
+  if (lane == 0) {
+    ends[0][t >> 6] = least;
+    ends[1][t >> 6] = most;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kSmallThreads / 64; ++k) {
+    least = min(least, ends[0][k]);
+    most = max(most, ends[1][k]);
+  }
+  unsigned long long from = 0ull, to = ~0ull;
+  if (w > 0) from = split_keys(keys_in, n, kSortSmall * w, least, most + 1, lds, part);
+  if (w + 1 < nc) to = split_keys(keys_in, n, kSortSmall * (w + 1), w > 0 ? from : least, most + 1, lds, part);
+  __syncthreads();
+  uint32_t base = 0;
+  for (uint32_t c0 = 0; c0 < nc; c0 += kSmallThreads) {  // block-uniform
+    const uint32_t c = c0 + t;
+    uint32_t a = 0, len = 0;
+    if (c < nc) {
+      const unsigned long long* in = keys_in + c * kSortSmall;
+      const int all = (int)min(n - c * kSortSmall, (uint32_t)kSortSmall);
+      a = (uint32_t)keys_below(in, 0, all, from);
+      len = (uint32_t)keys_below(in, (int)a, all, to) - a;
+      a += c * kSortSmall;
+    }
+    uint32_t tot;
+    const uint32_t at = base + block_exclusive_scan(len, part[0], &tot);
+    base += tot;
+    len = min(len, kSortSmall - min(at, (uint32_t)kSortSmall));  // (the shares hold no more)
+    if (len <= 8u) {
+      for (uint32_t q = 0; q < len; ++q) keys[at + q] = keys_in[a + q];
+    }
+    for (uint64_t more = __ballot(len > 8u); more; more &= more - 1) {  // wave-uniform
+      const int l = __builtin_ctzll(more);
+      const uint32_t from_l = __shfl(a, l, 64), at_l = __shfl(at, l, 64), len_l = __shfl(len, l, 64);
+      for (uint32_t q = lane; q < len_l; q += 64) keys[at_l + q] = keys_in[from_l + q];
+    }
+  }
+  __syncthreads();
+  block_sort_small<kSmallThreads, true>(nullptr, keys, (int)min(base, (uint32_t)kSortSmall));
+}
+
+// Puts the sorted chunks of a large tile together, one workgroup per chunk.  In
+// a tile of up to kMergeChunks chunks a key's place is its index in its chunk
+// and, for every other chunk, the number of smaller keys there, found by a
+// binary search of the chunk staged in LDS: all chunks of all large tiles work
+// at once, but the work grows with the square of the chunks.  In a tile of more
+// a workgroup takes a share of the places instead (merge_share), which reads
+// every chunk at some tens of places only.  Sort and merge of one tile of 8, 16,
+// 24, 64, 256 and 1024 chunks, us: all by counting 51 / 77 / 102 / 222 / 835 /
+// 3866, all by shares 90 / 102 / 103 / 126 / 137 / 970.
+constexpr uint32_t kMergeChunks = 24;
 __global__ void __launch_bounds__(kSmallThreads) k_tile_merge(const FrameCounters* ctr, const uint2* __restrict__ ranges,
                                                               const uint2* __restrict__ big_list,
                                                               const unsigned long long* __restrict__ bkey,
                                                               const uint2* __restrict__ inst_info,
                                                               uint2* __restrict__ info_k, uint32_t* __restrict__ ival) {
   __shared__ unsigned long long keys[kSortSmall];
+  __shared__ uint32_t part[2][kSmallThreads / 64];
   const int t = threadIdx.x;
   const int nb = ctr->n_big;
   for (int li = blockIdx.x; li < nb; li += gridDim.x) {  // block-uniform
@@ -903,6 +1032,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_merge(const FrameCounter
     const uint2 rg = ranges[e.x];
     const uint32_t x = rg.x + e.y * kSortSmall, nc = (rg.y - rg.x + kSortSmall - 1) / kSortSmall;
     const int m = (int)min(rg.y - x, (uint32_t)kSortSmall);
+    if (nc > kMergeChunks) {  // block-uniform
+      merge_share(bkey + rg.x, rg.y - rg.x, e.y, keys, part);
+      for (int j = t; j < m; j += kSmallThreads) {
+        const uint32_t k = (uint32_t)keys[j];
+        ival[x + j] = k;
+        info_k[x + j] = inst_info[k];
+      }
+      __syncthreads();
+      continue;
+    }
     unsigned long long v[kSmallItems];
     uint32_t at[kSmallItems];
 #pragma unroll
