@@ -495,6 +495,9 @@ __global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const u
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderBatch = 2;  // consecutive tiles per thread
 static_assert(kOrderChunk == kOrderThreads * kOrderBatch, "two tiles per thread");
+// A tile of up to this many instances has its segments and sort chunks listed by
+// its own thread (one thread for a tile of 1M: 152 us, its wave: 9).
+constexpr uint32_t kOwnTile = 32768;
 
 constexpr int kTileClasses = 128;
 __device__ __forceinline__ int tile_class(uint32_t n) {
@@ -586,7 +589,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 #pragma unroll
   for (int w = 0; w < kOrderThreads / 64; ++w) start += wb[w] + (w < wv ? wt[w] : 0u);
   uint32_t key[kOrderBatch];  // class << 16 | rank within the chunk's class (rank < kOrderChunk)
-  uint32_t big_at[kOrderBatch], seg_at[kOrderBatch], first[kOrderBatch];
+  uint32_t big_at[kOrderBatch] = {}, seg_at[kOrderBatch] = {}, first[kOrderBatch] = {};
   const uint64_t lt = lanemask_lt();
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) {
@@ -636,18 +639,29 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kOrderBatch; ++k)
-    if (k0 + k < n) {
-      const uint32_t tile = (uint32_t)(lo + k0 + k);
+  for (int k = 0; k < kOrderBatch; ++k) {
+    const uint32_t tile = (uint32_t)(lo + k0 + k);
+    const bool in = k0 + k < n;
+    if (in) {
       order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = make_uint4(tile, first[k], first[k] + m[k], 0u);
-      if (m[k] > (uint32_t)kSegment)
+      if (m[k] > (uint32_t)kSegment && m[k] <= kOwnTile)
         for (uint32_t q = 0; q * kSegment < m[k]; ++q)
           seg_list[seg_base + seg_at[k] + q] =
               make_uint4(tile, first[k], first[k] + q * kSegment, first[k] + min(m[k], (q + 1) * kSegment));
-      if (m[k] > (uint32_t)kSortSmall)
+      if (m[k] > (uint32_t)kSortSmall && m[k] <= kOwnTile)
         for (uint32_t q = 0; q * kSortSmall < m[k]; ++q)
           big_list[big_base + big_at[k] + q] = make_uint2(tile, q);
     }
+    // a longer tile's lists are its wave's to write
+    for (uint64_t more = __ballot(in && m[k] > kOwnTile); more; more &= more - 1) {  // wave-uniform
+      const int l = __builtin_ctzll(more);
+      const uint32_t tl = __shfl(tile, l, 64), f = __shfl(first[k], l, 64), len = __shfl(m[k], l, 64);
+      const uint32_t seg_to = seg_base + __shfl(seg_at[k], l, 64), big_to = big_base + __shfl(big_at[k], l, 64);
+      for (uint32_t q = lane; q * kSegment < len; q += 64)
+        seg_list[seg_to + q] = make_uint4(tl, f, f + q * kSegment, f + min(len, (q + 1) * kSegment));
+      for (uint32_t q = lane; q * kSortSmall < len; q += 64) big_list[big_to + q] = make_uint2(tl, q);
+    }
+  }
 }
 
 // The instances' sort keys (depth bits, emission index) into their tile's

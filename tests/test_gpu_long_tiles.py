@@ -101,3 +101,23 @@ def test_time_of_the_sort_grows_with_the_list(scene):
     print("us", us, flush=True)
     # 8 times the list, on a chip that the shorter one leaves half idle at least
     assert us[1] <= 4.0 * us[0], us
+
+
+def test_time_of_the_tile_scan_hardly_grows_with_one_list(scene):
+    # the segments and sort chunks of a long tile are listed by many threads
+    import torch
+    tree, S, cam, depth = scene
+    us = []
+    for n in (CHUNK, 512 * CHUNK):
+        positions = (np.arange(n, dtype=np.int64) * 7919 + 13) % S.n_nodes
+        f, idx, cnt = render(S, cam, positions, n)
+        f.set_timing(True)
+        best = float("inf")
+        for _ in range(5):
+            f.render(cam, idx=idx, count=cnt)
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * f.timings()["ranges"][0])
+        us.append(best)
+        f.set_timing(False)
+    print("us", us, flush=True)
+    assert us[1] <= 4.0 * us[0], us
