@@ -116,7 +116,7 @@ struct FrameCounters {
   int32_t spt_count;     // constant n_spt
   int32_t n_long;        // drawn splats with more than kLongSegment instances
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
-  int32_t n_heavy;       // tiles of at least kHeavyTile instances: the first of the tile order
+  int32_t n_heavy;       // tiles blended by a wave per 4x4 block: the first of the tile order
   int32_t n_seg;         // segments of the tiles of more than kSegment instances
   int32_t n_mid;         // tiles of at least 64 instances: likewise
 };
@@ -168,7 +168,7 @@ struct lodgs_frame {
                           // clamp bits, 2 unused
   uint32_t* long_list;    // [max_selected] ranks (among the drawn ones) of the splats with many instances
   uint2* ranges;          // [max tiles]
-  uint4* tile_order;      // [max tiles] (tile, its range's begin and end, 0), heaviest class first
+  uint4* tile_order;      // [max tiles] (tile, its range's begin and end, 1 if blended by blocks), heaviest class first
   uint32_t* tile_count;   // [max tiles] instances of each tile
   uint32_t* tile_cursor;  // [max tiles] next place in each tile's range
   float4* ckpt;           // [max_instances / kSegment + 1][256] (transmittance, 0 if stopped; colour) of the tile's
@@ -267,7 +267,7 @@ __host__ __device__ inline int32_t tile_chunk(int32_t ntiles) {
   return (ntiles + c - 1) / c;
 }
 
-// Tiles of at least this many instances are blended by a wave per 4x4 block.
+// Tiles of fewer instances are never blended by a wave per 4x4 block.
 constexpr int kHeavyBits = 9;  // bit length of kHeavyTile
 constexpr int kHeavyTile = 1 << (kHeavyBits - 1);
 

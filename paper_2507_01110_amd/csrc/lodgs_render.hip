@@ -506,6 +506,10 @@ __device__ __forceinline__ int tile_class(uint32_t n) {
   return bl * 4 + sub;  // < kTileClasses
 }
 constexpr int kHeavyClass = 4 * kHeavyBits;  // class of kHeavyTile instances
+// The class from which on tiles are blended by a wave per 4x4 block, in an image
+// of n instances (k_blend_fwd says why).
+constexpr uint32_t kHeavyShare = 2048;
+__device__ __forceinline__ int heavy_class(uint32_t n) { return max(kHeavyClass, tile_class(n / kHeavyShare)); }
 constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
 constexpr int kClassLanes = 32;  // copies of a class's counter
 
@@ -537,6 +541,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   __shared__ uint32_t seg, seg_base;  // and blend segments
   const int32_t per = tile_chunk(ntiles), lo = blockIdx.x * per;
   const int32_t n = min(per, ntiles - lo);
+  const int heavy = heavy_class((uint32_t)ctr->n_inst_clamped);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int32_t k0 = t * kOrderBatch;
   uint32_t m[kOrderBatch], sum = 0, before = 0;
@@ -633,7 +638,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   if (c < kTileClasses) {
     const uint32_t above = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
     pre[c] += above;
-    if (blockIdx.x == 0 && c == kHeavyClass - 1) ctr->n_heavy = (int32_t)above;
+    if (blockIdx.x == 0 && c == heavy - 1) ctr->n_heavy = (int32_t)above;
     // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
     if (blockIdx.x == 0 && c == kWaveClass - 1) ctr->n_mid = (int32_t)above;
   }
@@ -643,7 +648,8 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
     const uint32_t tile = (uint32_t)(lo + k0 + k);
     const bool in = k0 + k < n;
     if (in) {
-      order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] = make_uint4(tile, first[k], first[k] + m[k], 0u);
+      order[pre[key[k] >> 16] + (key[k] & 0xFFFFu)] =
+          make_uint4(tile, first[k], first[k] + m[k], (int)(key[k] >> 16) >= heavy ? 1u : 0u);
       if (m[k] > (uint32_t)kSegment && m[k] <= kOwnTile)
         for (uint32_t q = 0; q * kSegment < m[k]; ++q)
           seg_list[seg_base + seg_at[k] + q] =
@@ -1270,9 +1276,9 @@ __global__ void __launch_bounds__(256 / PX) k_blend(const ViewConst* __restrict_
   }
 }
 
-// A tile of at least kHeavyTile instances is blended by 16 waves, one per 4x4
-// block (blend_block_wave), others by four, one per 8x8 quarter
-// (blend_quarter).  The waves of a tile run on one XCD (workgroups go to the
+// A tile far longer than the others is blended by 16 waves, one per 4x4 block
+// (blend_block_wave), the others by four, one per 8x8 quarter (blend_quarter).
+// The waves of a tile run on one XCD (workgroups go to the
 // XCDs in turn), so its words and records are read into one L2.
 constexpr int kHeavyWgs = 4096;  // single-wave workgroups that take the heavy tiles' blocks in turn
 
@@ -1292,10 +1298,11 @@ struct QuarterLds {
   uint32_t evr[64];     // per slot: this quarter's event bits
 };
 
+template <bool LONG>
 __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int q, uint2 rg,
                                               const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
                                               uint32_t nr, float bg0, float bg1, float bg2, float* rgb,
-                                              uint32_t* event, QuarterLds& lds) {
+                                              uint32_t* event, float4* ckpt, QuarterLds& lds) {
   float4 (&rec)[3][64] = lds.rec;
   uint8_t (&hits)[4][64] = lds.hits;
   uint32_t (&evr)[64] = lds.evr;
@@ -1331,9 +1338,14 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
     rb = r[1];
     rc = r[2];
   }
+  // the pixels' state before instance k of the list (a segment's first)
+  const auto checkpoint = [&](uint32_t k) {
+    ckpt[256 * (int64_t)(k / kSegment) + 16 * (py & 15) + (px & 15)] = make_float4(live ? T : 0.0f, cr, cg, cb);
+  };
   uint32_t b0 = rg.x;
   for (; b0 < rg.y; b0 += 64) {
     if (!any_lane(live)) break;  // wave-uniform
+    if (LONG && b0 > rg.x && (b0 - rg.x) % kSegment == 0) checkpoint(b0);
     const int m = (int)min(64u, rg.y - b0);
     const bool mine = lane < m && sk0 < nr;
     rec[0][lane] = ra;
@@ -1432,7 +1444,10 @@ __device__ __forceinline__ void blend_quarter(const ViewConst& v, int tile, int 
     sk1 = sk2;
     bk1 = bk2;
   }
-  // batches of the tile that this quarter never reached
+  // segments and batches of the tile that this quarter never reached
+  for (uint32_t k = b0 > rg.x ? rg.x + (b0 - rg.x + kSegment - 1) / kSegment * kSegment : rg.x + kSegment;
+       LONG && k < rg.y; k += kSegment)
+    checkpoint(k);
   const uint32_t nb = (rg.y - rg.x + 63) / 64;
   for (uint32_t k = (b0 - rg.x) / 64 + (lane >> 2); k < nb; k += 16) ev64[16 * k + 4 * q + (lane & 3)] = 0ull;
   if (inside) {
@@ -1591,10 +1606,16 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
 // Forward blend.  The first kHeavyWgs single-wave workgroups take the heavy
 // tiles' blocks in turn, the others the quarters of the other tiles, in the
 // tile order.  What bounds it is the longest tile's chain of steps, then the
-// instructions.  Quarters alone against blocks for tiles of 128, 256 and 512
-// instances on, us: 256-instance tiles of a 333 x 171 iteration 67 / 31 / 31 /
-// 38, an aerial 1080p view 63 / 42 / 36 / 48, a street view at 1080p (tiles of
-// up to 9035) 675 / 287 / 256 / 267 and at 4K 313 / 210 / 200 / 198.
+// instructions.  Blocks shorten the chains and read a tile's list four times as
+// often, so they are for tiles that would end after all others: those of at
+// least kHeavyTile instances and of a 2048th of the image's.  Quarters alone
+// against blocks for tiles of 128, 256 and 512 instances on, us: a 333 x 171
+// iteration 67 / 31 / 31 / 38, a 1080p iteration 63 / 42 / 36 / 48.  Blocks from
+// 256 instances on against from a 2048th (a 1024th) on, us: a street view at
+// 1080p (2.1M instances, tiles of up to 9035) 262 / 220 (217) and at 4K 196 /
+// 192 (190), a 1080p iteration 35.0 / 35.1 (35.8); clouds of small splats, whose
+// tiles are all long: 2M leaves at 1080p 563 / 229 (236), 6M 1356 / 518 (518), 2M
+// at 1024 x 1024 473 / 367 (213).
 __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ vp,
                                                   const uint2* __restrict__ info_k, const Splat* __restrict__ splats,
                                                   const FrameCounters* ctr, const uint4* __restrict__ tile_order,
@@ -1621,9 +1642,13 @@ __global__ void __launch_bounds__(64) k_blend_fwd(const ViewConst* __restrict__ 
   const int i = (int)blockIdx.x - kHeavyWgs, at = (i >> 5) * 8 + xcd, q = (i >> 3) & 3;
   if (at >= ntiles) return;
   const uint4 o = tile_order[at];
-  const uint2 rg = make_uint2(o.y, o.z);
-  if (rg.y - rg.x >= (uint32_t)kHeavyTile) return;
-  blend_quarter(*vp, (int)o.x, q, rg, info_k, splats, nr, bg0, bg1, bg2, rgb, event, lds.quarter);
+  if (o.w != 0u) return;
+  if (o.z - o.y > (uint32_t)kSegment)
+    blend_quarter<true>(*vp, (int)o.x, q, make_uint2(o.y, o.z), info_k, splats, nr, bg0, bg1, bg2, rgb, event, ckpt,
+                        lds.quarter);
+  else
+    blend_quarter<false>(*vp, (int)o.x, q, make_uint2(o.y, o.z), info_k, splats, nr, bg0, bg1, bg2, rgb, event, ckpt,
+                         lds.quarter);
 }
 
 template <bool COUNT>
