@@ -482,6 +482,7 @@ __global__ void __launch_bounds__(kBlock) k_cut_write(SceneDev S, const uint8_t*
     const ChunkNodes nodes(S, chunk_node(b, ch.y), b + spt_high[ch.x], spt_X[ch.x]);
     const int tile = n_upper_tiles + (int)ch.x / kCutTile;
     uint32_t x = 0;
+#pragma unroll 4
     for (int i = (int)first[tile] + lane; i < run; i += 64) x += chunks[i].y & kChunkCount;
     write(nodes, before(tile) + wave_total(x));
     return;
