@@ -872,7 +872,7 @@ __global__ void __launch_bounds__(256 / PX, PX == 1 ? (NP == 10 ? 5 : 4) : 1) k_
   for (int i = segments ? (int)blockIdx.x : (int)blockIdx.x - kSegmentWgs; i < end; i += kSegmentWgs) {
     const uint4 o = segments ? seg_list[i] : tile_order[i];
     const uint2 rg = segments ? make_uint2(o.z, o.w) : make_uint2(o.y, o.z);
-    if (!segments && rg.y - rg.x > (uint32_t)kSegment) return;
+    if (!segments && (rg.y - rg.x > (uint32_t)kSegment || rg.x == rg.y)) return;
     if constexpr (PX == 1)
       blend_bwd_blocks<NP>(*vp, (int)o.x, o.y, rg, ival, info_k, splats, nr, rgb, dL, event, ckpt, partial, lds);
     else
