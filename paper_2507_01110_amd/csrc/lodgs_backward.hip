@@ -91,12 +91,12 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 // the instance's emission index, with zeros for instances that no pixel
 // reached.  No order depends on timing: the result is deterministic.
 
-// LDS of a workgroup of the blend backward.
+// LDS of a workgroup of the blend backward (two or four pixels per lane; a batch
+// is an instance per thread).
 template <int PX, int NP>
 struct BlendBwdLds {
-  // NB instances per batch: at most one per thread, and at most 128, which
-  // keeps the per-wave LDS rows small enough for several workgroups per CU
-  static constexpr int NT = 256 / PX, NW = 4 / PX, NB = NT < 128 ? NT : 128;
+  static_assert(PX == 2 || PX == 4, "one pixel per lane: BlocksBwdLds");
+  static constexpr int NW = 4 / PX, NB = 256 / PX;
   // the first 12 floats of each splat record (mean, axis, power, opacity,
   // colour): all a replay reads, at a 12-word stride that spreads the rows'
   // reads of different slots over the banks
@@ -124,7 +124,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
                                                 const float* __restrict__ rgb, const float* __restrict__ dL,
                                                 const uint32_t* __restrict__ event, const float4* __restrict__ ckpt,
                                                 float* __restrict__ partial, BlendBwdLds<PX, NP>& lds) {
-  constexpr int NT = 256 / PX, NW = 4 / PX, NB = BlendBwdLds<PX, NP>::NB;
+  constexpr int NW = 4 / PX, NB = BlendBwdLds<PX, NP>::NB;
   using BatchRec = typename BlendBwdLds<PX, NP>::BatchRec;
   auto& batch = lds.batch;
   auto& bid = lds.bid;
@@ -171,16 +171,12 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     eyy[p] = ey[p] * ey[p];
   }
   const float thr = 1.0f / 255.0f;
-  for (int t = threadIdx.x; t < NW * NP * NB; t += NT) (&acc[0][0][0])[t] = 0.0f;
-  // The last NB threads load: thread NT - NB + j holds batch slot j, the
-  // words (emission index, splat, whether the instance has an event) of this
-  // batch and the next, and the splat record of this batch (only for an
-  // instance with events: the others are never replayed), so the loads overlap
-  // the replay of the batch before.  The first threads write the partials out after a replay, so with
-  // four waves the staging of the next batch and the write-out of the last
-  // run on different waves.
-  const int ld = (int)threadIdx.x - (NT - NB);  // the loaded slot (loaders only)
-  const bool loader = ld >= 0;
+  for (int t = threadIdx.x; t < NW * NP * NB; t += NB) (&acc[0][0][0])[t] = 0.0f;
+  // Thread j holds batch slot j: the words (emission index, splat, whether the
+  // instance has an event) of this batch and the next, and the splat record of
+  // this batch (only for an instance with events: the others are never
+  // replayed), so the loads overlap the replay of the batch before.
+  const int ld = (int)threadIdx.x;
   const unsigned long long* const ev64 = event_masks(event, first, tile) + 16 * ((rg.x - first) / 64);
   const uint32_t nbt = (rg.y - rg.x + 63) / 64;
   // e, i of the loaded slot, and lane l % 16's event mask of the 64 slots that
@@ -189,7 +185,6 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     const uint32_t k = b + (uint32_t)ld;
     e = i = 0u;
     mk = 0ull;
-    if (!loader) return;
     if (k < rg.y) {
       e = ival[k];
       i = info_k[k].x;
@@ -214,7 +209,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
   };
   auto record = [&](uint32_t i, unsigned long long mk, float4& a, float4& b, float4& c) {
     a = b = c = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (loader && any_event(mk) && i < nr) {  // i >= nr only follows an instance overflow (no events)
+    if (any_event(mk) && i < nr) {  // i >= nr only follows an instance overflow (no events)
       const float4* r = reinterpret_cast<const float4*>(splats + i);
       a = r[0];
       b = r[1];
@@ -236,22 +231,19 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     // behind the batch's barrier (no block-wide count, which takes three)
     const bool wave_act = any_lane(active);
     if (lane == 0) wave_active[wv] = wave_act ? 1u : 0u;
-    if (loader) {
-      bid[ld] = e0;
-      if (lane < 16) emask[ld >> 6][lane] = w0;
-      float4* dst = reinterpret_cast<float4*>(&batch[ld]);  // mean, axis, power, opacity, colour
-      dst[0] = ra;
-      dst[1] = rb;
-      dst[2] = rc;
-    }
+    bid[ld] = e0;
+    if (lane < 16) emask[ld >> 6][lane] = w0;
+    float4* staged = reinterpret_cast<float4*>(&batch[ld]);  // mean, axis, power, opacity, colour
+    staged[0] = ra;
+    staged[1] = rb;
+    staged[2] = rc;
     __syncthreads();
     uint32_t block_act = 0u;
 #pragma unroll
     for (int w = 0; w < NW; ++w) block_act |= wave_active[w];
     if (block_act == 0u) break;  // every pixel of the tile has stopped (the same flags for all threads)
-    // the emission index this thread writes out to after the replay, read
-    // now: a loader may stage the next batch while the write-out runs
-    const uint32_t out_bid = bid[threadIdx.x % NB];
+    // the emission index this thread writes out to after the replay
+    const uint32_t out_bid = bid[ld];
     record(i1, w1, ra, rb, rc);
     uint32_t e2, i2;
     unsigned long long w2;
@@ -445,7 +437,7 @@ __device__ __forceinline__ void blend_bwd_range(const ViewConst& v, int tile, ui
     w1 = w2;
   }
   // instances that no pixel of the tile reached
-  for (uint32_t k = b0 + threadIdx.x; k < rg.y; k += NT) {
+  for (uint32_t k = b0 + threadIdx.x; k < rg.y; k += NB) {
     float* dst = partial + NP * (int64_t)ival[k];
 #pragma unroll
     for (int c = 0; c < NP; ++c) dst[c] = 0.0f;

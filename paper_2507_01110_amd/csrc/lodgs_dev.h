@@ -342,23 +342,6 @@ __device__ __forceinline__ uint32_t blend_row_blocks(int wv, int g) {
   return m;
 }
 
-// Sum over the 64 lanes of a wave with DPP lane moves, result in lane 63:
-// swaps inside quads, row rotations by 4 and 8 (every lane then holds its
-// 16-lane row's sum), then the row broadcasts 15 and 31 fold the rows into
-// the last one.  Lanes that do not take part must pass 0.
-#define LODGS_DPP(x, ctrl, row_mask) \
-  __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, row_mask, 0xf, false))
-__device__ __forceinline__ float wave_sum_to_lane63(float v) {
-  v += LODGS_DPP(v, 0xB1, 0xf);   // quad_perm [1,0,3,2]
-  v += LODGS_DPP(v, 0x4E, 0xf);   // quad_perm [2,3,0,1]
-  v += LODGS_DPP(v, 0x124, 0xf);  // row_ror 4
-  v += LODGS_DPP(v, 0x128, 0xf);  // row_ror 8
-  v += LODGS_DPP(v, 0x142, 0xa);  // row_bcast 15 into rows 1 and 3
-  v += LODGS_DPP(v, 0x143, 0xc);  // row_bcast 31 into rows 2 and 3
-  return v;
-}
-#undef LODGS_DPP
-
 // Grid-stride bounds for kernels whose element count lives in device memory.
 __device__ __forceinline__ int64_t clamp_count(const int32_t* d_n, int64_t cap) {
   int64_t n = *d_n;

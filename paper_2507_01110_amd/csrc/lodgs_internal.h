@@ -94,12 +94,12 @@ int build_ancestor_table(lodgs_scene* s);
 int build_spt_radius(lodgs_scene* s);
 }  // namespace lodgs
 
-// Device counters of a frame (one struct in device memory).
 // Selection positions of one sum that the projection leaves for the drawn
 // scan: 64 (a wave stores its own) up to kDrawnWide positions, kDrawnRun (waves
 // add up) beyond, where every workgroup of the scan would read too many.
 constexpr int64_t kDrawnRun = 2048, kDrawnWide = 524288;
 
+// Device counters of a frame (one struct in device memory).
 struct FrameCounters {
   int32_t status;
   int32_t n_selected;
@@ -214,8 +214,8 @@ struct lodgs_frame {
 
 namespace lodgs {
 
-// A drawn splat with more instances than this has its instance partials
-// summed by a whole workgroup in the backward (listed by the duplication).
+// A drawn splat with more instances than this (listed by the duplication) has
+// its instance partials summed by a wave in the backward, or by a workgroup.
 constexpr uint32_t kLongSegment = 32;
 // The wave's list of batch slots j < m whose mask bits meet `want` (every
 // slot j < m if ALL), in slot order, written to list; returns its length
@@ -303,7 +303,7 @@ constexpr int kSortChunkHalf = 1024;
 // starts the stage's counters: kViewSelect clears the select counters,
 // kViewRender sets n_render = clamp(*d_count, 0, cap) and clears the render's
 // counters; the other threads clear the tiles' instance counts (kViewRender).
-constexpr int kViewOnly = 0, kViewSelect = 1, kViewRender = 2;
+constexpr int kViewSelect = 1, kViewRender = 2;
 __global__ void k_select_begin(ViewConst v, ViewConst* dst, FrameCounters* ctr, SceneDev S, uint32_t flags,
                                uint8_t* utest);
 void launch_set_view(const ViewConst& v, ViewConst* dst, FrameCounters* ctr, int mode, const int32_t* d_count,

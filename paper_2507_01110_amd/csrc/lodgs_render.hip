@@ -1656,17 +1656,15 @@ static void launch_blend(lodgs_frame* f, const ViewConst& v, const float bg[3], 
   const int ntiles = v.tiles_x * v.tiles_y;
   unsigned long long* work = COUNT ? f->work : nullptr;
   uint32_t* event = COUNT ? nullptr : f->inst_event;
-  if (!COUNT && f->blend_px_fwd == 1) {
-    hipLaunchKernelGGL(k_blend_fwd, dim3(kHeavyWgs + 32 * ((ntiles + 7) / 8)), dim3(64), 0, st, f->d_view_ren,
-                       f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1],
-                       bg[2], d_rgb, event, f->ckpt);
-    return;
-  }
   switch (f->blend_px_fwd) {
     case 1:
-      hipLaunchKernelGGL((k_blend<COUNT, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren,
-                         f->info_k, f->splats, f->ctr, f->tile_order, bg[0], bg[1], bg[2],
-                         d_rgb, event, work, f->ckpt);
+      if constexpr (COUNT)
+        hipLaunchKernelGGL((k_blend<true, 1>), dim3(ntiles), dim3(256), 0, st, f->d_view_ren, f->info_k, f->splats,
+                           f->ctr, f->tile_order, bg[0], bg[1], bg[2], d_rgb, event, work, f->ckpt);
+      else
+        hipLaunchKernelGGL(k_blend_fwd, dim3(kHeavyWgs + 32 * ((ntiles + 7) / 8)), dim3(64), 0, st, f->d_view_ren,
+                           f->info_k, f->splats, f->ctr, f->tile_order, ntiles, bg[0], bg[1], bg[2], d_rgb, event,
+                           f->ckpt);
       break;
     case 4:
       hipLaunchKernelGGL((k_blend<COUNT, 4>), dim3(ntiles), dim3(64), 0, st, f->d_view_ren,
@@ -1687,8 +1685,7 @@ int blend_output_arg(const void* func, int* n_args) {
     *n_args = 12;
     return 9;
   }
-  if (func == reinterpret_cast<const void*>(&k_blend<false, 1>) ||
-      func == reinterpret_cast<const void*>(&k_blend<false, 2>) ||
+  if (func == reinterpret_cast<const void*>(&k_blend<false, 2>) ||
       func == reinterpret_cast<const void*>(&k_blend<false, 4>)) {
     *n_args = 12;
     return 8;
