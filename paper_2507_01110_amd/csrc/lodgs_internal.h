@@ -273,15 +273,22 @@ constexpr int kHeavyTile = 1 << (kHeavyBits - 1);
 
 // Forward events: per tile, for each batch of 64 of its instances (in order)
 // and each 4x4 block (the bits of block_bit), the mask of the batch's
-// instances that blended or stopped at a pixel of the block.  The tile whose
-// range starts at `begin` has its masks from word begin + 64 tile on (rounded up to a
-// mask): 32 words for every 64 instances or part of them.
-__host__ __device__ inline size_t event_words(size_t instances, size_t tiles) { return instances + 64 * tiles + 2; }
+// instances that blended or stopped at a pixel of the block: 16 masks for every
+// 64 instances or part of them.  The tile whose range starts at `begin` has its
+// masks from mask begin / 4 + 16 min(tile, begin) on: at most `begin` tiles
+// before it hold instances, and a quarter of a tile's n instances and 16 masks
+// more are at least 16 for each batch of it.
+__host__ __device__ inline size_t event_words(size_t instances, size_t tiles) {
+  return 2 * (instances / 4 + 16 * (tiles < instances ? tiles : instances) + 16);
+}
+__device__ __forceinline__ int64_t event_mask(uint32_t begin, int tile) {
+  return (int64_t)(begin >> 2) + 16 * (int64_t)min((uint32_t)tile, begin);
+}
 __device__ __forceinline__ unsigned long long* event_masks(uint32_t* event, uint32_t begin, int tile) {
-  return reinterpret_cast<unsigned long long*>(event) + (((int64_t)begin + 64 * (int64_t)tile + 1) >> 1);
+  return reinterpret_cast<unsigned long long*>(event) + event_mask(begin, tile);
 }
 __device__ __forceinline__ const unsigned long long* event_masks(const uint32_t* event, uint32_t begin, int tile) {
-  return reinterpret_cast<const unsigned long long*>(event) + (((int64_t)begin + 64 * (int64_t)tile + 1) >> 1);
+  return reinterpret_cast<const unsigned long long*>(event) + event_mask(begin, tile);
 }
 
 // A tile of more than kSegment instances is taken by the blend backward in
