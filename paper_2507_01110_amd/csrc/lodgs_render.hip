@@ -507,9 +507,11 @@ __device__ __forceinline__ int tile_class(uint32_t n) {
 }
 constexpr int kHeavyClass = 4 * kHeavyBits;  // class of kHeavyTile instances
 // The class from which on tiles are blended by a wave per 4x4 block, in an image
-// of n instances (k_blend_fwd says why).
-constexpr uint32_t kHeavyShare = 2048;
-__device__ __forceinline__ int heavy_class(uint32_t n) { return max(kHeavyClass, tile_class(n / kHeavyShare)); }
+// of n instances and `many` tiles of at least kHeavyTile (k_blend_fwd says why).
+constexpr uint32_t kHeavyShare = 2048, kHeavyFew = 512;
+__device__ __forceinline__ int heavy_class(uint32_t n, uint32_t many) {
+  return many <= kHeavyFew ? kHeavyClass : max(kHeavyClass, tile_class(n / kHeavyShare));
+}
 constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
 constexpr int kClassLanes = 32;  // copies of a class's counter
 
@@ -539,9 +541,10 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
   __shared__ uint32_t wt[kOrderThreads / 64], wb[kOrderThreads / 64];
   __shared__ uint32_t big, big_base;  // this chunk's large tiles' sort chunks
   __shared__ uint32_t seg, seg_base;  // and blend segments
+  __shared__ uint32_t many;  // the image's tiles of at least kHeavyTile instances
   const int32_t per = tile_chunk(ntiles), lo = blockIdx.x * per;
   const int32_t n = min(per, ntiles - lo);
-  const int heavy = heavy_class((uint32_t)ctr->n_inst_clamped);
+  const uint32_t n_inst = (uint32_t)ctr->n_inst_clamped;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int32_t k0 = t * kOrderBatch;
   uint32_t m[kOrderBatch], sum = 0, before = 0;
@@ -635,14 +638,17 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
     if (lane == 63) half[wv] = incl;
   }
   __syncthreads();
+  uint32_t above = 0;
   if (c < kTileClasses) {
-    const uint32_t above = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
+    above = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
     pre[c] += above;
-    if (blockIdx.x == 0 && c == heavy - 1) ctr->n_heavy = (int32_t)above;
+    if (c == kHeavyClass - 1) many = above;
     // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
     if (blockIdx.x == 0 && c == kWaveClass - 1) ctr->n_mid = (int32_t)above;
   }
   __syncthreads();
+  const int heavy = heavy_class(n_inst, many);
+  if (blockIdx.x == 0 && c == heavy - 1) ctr->n_heavy = (int32_t)above;
 #pragma unroll
   for (int k = 0; k < kOrderBatch; ++k) {
     const uint32_t tile = (uint32_t)(lo + k0 + k);
@@ -1608,7 +1614,9 @@ __device__ __forceinline__ void blend_block_wave(const ViewConst& v, int tile, i
 // tile order.  What bounds it is the longest tile's chain of steps, then the
 // instructions.  Blocks shorten the chains and read a tile's list four times as
 // often, so they are for tiles that would end after all others: those of at
-// least kHeavyTile instances and of a 2048th of the image's.  Quarters alone
+// least kHeavyTile instances and, where more than kHeavyFew tiles hold that many,
+// of a 2048th of the image's (fewer long tiles leave the chip room: 6M leaves at
+// 256 x 256 342 us with that share, 224 without).  Quarters alone
 // against blocks for tiles of 128, 256 and 512 instances on, us: a 333 x 171
 // iteration 67 / 31 / 31 / 38, a 1080p iteration 63 / 42 / 36 / 48.  Blocks from
 // 256 instances on against from a 2048th (a 1024th) on, us: a street view at
