@@ -118,7 +118,7 @@ struct FrameCounters {
   int32_t n_big;         // chunks of tiles too large for one workgroup's sort
   int32_t n_heavy;       // tiles blended by a wave per 4x4 block: the first of the tile order
   int32_t n_seg;         // segments of the tiles of more than kSegment instances
-  int32_t n_mid;         // tiles of at least 64 instances: likewise
+  int32_t n_mid;         // tiles of at least 64 instances: the first of the tile order
 };
 
 struct lodgs_frame {

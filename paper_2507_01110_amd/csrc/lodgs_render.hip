@@ -19,8 +19,8 @@
 //             No splat or instance passes through a global radix sort: a sort
 //             by depth of the splats and one by tile of the instances took 18
 //             launches (82 of a 512 x 512 view's 164 us; 288 us of a street
-//             view with 0.95M drawn splats and 2.1M instances), the five
-//             kernels above take 24 and 160 us there.
+//             view with 0.95M drawn splats and 2.1M instances), the six
+//             kernels from k_drawn_scan on take 28 and 162 us there.
 //  k_blend_fwd  a wave per 8x8 quarter or per 4x4 block of a tile; k_blend is
 //             its general form, one workgroup per tile with PX pixels per
 //             lane, and the evaluation count.  A 4x4 block replays only the
@@ -352,7 +352,8 @@ __global__ void __launch_bounds__(kDrawnThreads) k_drawn_scan(const uint32_t* __
 // The tiles' counts: a workgroup counts its own instances per tile in LDS (16
 // bits each) and adds its non-zero counts to tile_count; where the image has
 // more than kLdsTiles tiles, or a workgroup more instances than 16 bits hold,
-// every instance adds to tile_count itself.
+// every instance adds to tile_count itself (3.3M instances at 4096 x 2048, 32768
+// tiles, and at 4112 x 2064, 33153: 68 and 104 us).
 //
 // One workgroup of 16 waves per CU, so the counters are cleared and added up
 // 256 times a launch, not once for every few hundred instances (a 4K view's
@@ -486,8 +487,12 @@ __global__ void __launch_bounds__(kDupThreads) k_dup(FrameCounters* ctr, const u
 // of each class lie before and after it (kept by lane, so that no two lanes of
 // an LDS operation meet).  An order of each chunk by itself, interleaved,
 // was shorter to make (6 against 8 us), but where one part of the image is
-// heavier its tiles started late: 132 against 101 us for the blend backward of
-// an aerial 1080p view.  Within its chunk a tile takes its rank in its class
+// heavier its tiles started late: 132 against 102 us for the blend backward of
+// a 1080p iteration, 151 against 138 of an aerial 1080p view (before its later
+// changes).  What all workgroups read grows with the square of the image's
+// tiles: 7 us at 1080p, 16 at 4K, 82 at 8192 x 8192 and 350 at 16384 x 16384,
+// the largest image (531 and 2157 with the ranges and the order in two kernels).
+// Within its chunk a tile takes its rank in its class
 // from an LDS counter; the order within a chunk and class is whatever the LDS
 // atomics give.  The lanes of a wave whose tiles share the first lane's class
 // (empty tiles, mostly) count with one atomic: same-address LDS atomics run
@@ -512,7 +517,7 @@ constexpr uint32_t kHeavyShare = 2048, kHeavyFew = 512;
 __device__ __forceinline__ int heavy_class(uint32_t n, uint32_t many) {
   return many <= kHeavyFew ? kHeavyClass : max(kHeavyClass, tile_class(n / kHeavyShare));
 }
-constexpr int kWaveClass = 4 * 7;  // class of 64 instances: a tile above it holds more than 64
+constexpr int kWaveClass = 4 * 7;  // class of 64 to 79 instances: a tile below it holds fewer than 64
 constexpr int kClassLanes = 32;  // copies of a class's counter
 
 // The sum of x over the wave's lanes, in every lane.
@@ -643,7 +648,6 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
     above = half[0] + half[1] - (incl + (wv == 1 ? half[0] : 0u));
     pre[c] += above;
     if (c == kHeavyClass - 1) many = above;
-    // class kWaveClass holds 64..79 instances: those with 64 go with the tiles above
     if (blockIdx.x == 0 && c == kWaveClass - 1) ctr->n_mid = (int32_t)above;
   }
   __syncthreads();
@@ -682,7 +686,8 @@ __global__ void __launch_bounds__(kOrderThreads) k_tile_scan(const uint32_t* __r
 // instance of each tile takes the tile's places with one atomic and hands
 // them to the others; only the counters of tiles it meets are touched.  Bound
 // by those atomics (27 G/s over the chip): 22 us for 2.1M instances.
-// Images of more than kBucketLdsTiles tiles take a place per instance.
+// Images of more than kBucketLdsTiles tiles take a place per instance (3.3M
+// instances at 32768 and at 33153 tiles: 33 and 96 us).
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketItems = 8;   // at most, per thread
 constexpr int kBucketGrid = 512;  // a CU takes two where the counters leave room
@@ -875,14 +880,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_tile_sort(const FrameCounters
     for (int j = t; j < m; j += kSmallThreads) bkey[x + j] = keys[j];
     __syncthreads();
   }
-  // the tile order: a workgroup for each tile of more than 64 instances, then
+  // the tile order: a workgroup for each tile of at least 64 instances, then
   // a wave for each other one; the first items go to the workgroups after
   // those that took the last chunks
   const int32_t nm = ctr->n_mid, items = nm + (ntiles - nm + 3) / 4;
   int32_t it = (int32_t)blockIdx.x - nb % (int32_t)gridDim.x;
   if (it < 0) it += (int32_t)gridDim.x;
   for (; it < items; it += (int32_t)gridDim.x) {  // block-uniform
-    if (it >= nm) {  // four tiles of at most 64 instances
+    if (it >= nm) {  // four tiles of fewer than 64 instances
       const int32_t at = nm + 4 * (it - nm) + (t >> 6);
       if (at < ntiles) {  // wave-uniform
         const uint4 o = tile_order[at];

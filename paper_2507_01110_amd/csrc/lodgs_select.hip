@@ -19,7 +19,7 @@
 // per run of chunks, at the sum of the counts before it.
 // Four launches and no workgroup that waits for another (scenes of more than
 // kWideTiles tiles: two more, which scan the tiles' counts).  A small view's cut is
-// bound by the launches' latency: 18 us on a 32,767-node scene and 38 on 12M
+// bound by the launches' latency: 18 us on a 32,767-node scene and 36 on 12M
 // nodes, street level (nine launches, with two-kernel scans: 31 and 48).  Tiles numbered by ticket that look back over published
 // counts took longer than adding the counts up (a contended ticket costs 0.1
 // to 0.2 us a tile here), and a wave per SPT left the SPTs of tens of
