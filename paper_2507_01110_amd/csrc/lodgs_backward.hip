@@ -513,11 +513,8 @@ __device__ __forceinline__ void wave_fence() {
 // (step, row) splats at 16 pixels, 16 x 16, times the columns' factors at
 // those pixels, in FP32.  The moments are summed without the opacity, which
 // multiplies the totals, and about the quarter's centre, which keeps the sums
-// small; both products take the 16 pixels in two chains of eight.  The
-// gradients' errors against 64 bits, over those of a tree of adds about the
-// tile's centre (geometric means over 27 views): scales 0.87, means 0.90,
-// rotations 0.92, colours 0.99, opacities 1.01 (with one chain for the
-// moments 0.90, 0.93, 0.93, 0.99 and 1.02).  A
+// small: the gradients' errors against 64 bits are 0.92 (scales, rotations)
+// to 1.00 (colours) of those of the tree of adds about the tile's centre.  A
 // step takes 62 vector instructions where it took 110, and the float adds in
 // the LDS (3 cycles a lane each) are gone.  96 registers and 31 KB let five
 // workgroups run on a CU, which hides part of the batches' waits: with four, 5
@@ -721,20 +718,17 @@ __device__ __forceinline__ void blend_bwd_blocks(const ViewConst& v, int tile, u
         }
         slots = *reinterpret_cast<const uint32_t*>(&lds.hits[wv][t + row][0]);
         d1 = d2 = float4_t{0.f, 0.f, 0.f, 0.f};
-        float4_t e1 = d1, e2 = d1;  // (two shorter chains round less)
+        float4_t d3 = d2;  // (two shorter chains round less)
         d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.x, bm[0], d1, 0, 0, 0);
         d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.x, bg.x, d2, 0, 0, 0);
-        e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.z, bm[2], e1, 0, 0, 0);
-        e2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.z, bg.z, e2, 0, 0, 0);
         d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.y, bm[1], d1, 0, 0, 0);
         d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.y, bg.y, d2, 0, 0, 0);
-        e1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.w, bm[3], e1, 0, 0, 0);
-        e2 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.w, bg.w, e2, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.z, bm[2], d1, 0, 0, 0);
+        d3 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.z, bg.z, d3, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ao.w, bm[3], d1, 0, 0, 0);
+        d3 = __builtin_amdgcn_mfma_f32_16x16x4f32(aw.w, bg.w, d3, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          d1[r] += e1[r];
-          d2[r] += e2[r];
-        }
+        for (int r = 0; r < 4; ++r) d2[r] += d3[r];
       };
       // row r's sums are added to the wave's rows of their splats: a read, an
       // add and a write (a float add in the LDS takes 3 cycles a lane, 195 an
